@@ -49,15 +49,17 @@ def code_digest(paths) -> str:
 
 
 def measured_traffic():
-    """HBM bytes per launch of the two sweep kernels ({"local": B, "global": B}) from
-    the committed counter record (FETCH_SIZE + WRITE_SIZE, copy-calibrated), or None
-    once the kernel code differs from the code the counters were taken on."""
+    """HBM bytes per step of the localized launch and of the global launch with its anchor
+    ({"local": B, "global": B}) from the committed counter record (FETCH_SIZE + WRITE_SIZE,
+    copy-calibrated), or None once the kernel code differs from the code the counters were
+    taken on."""
     try:
         rec = json.load(open(TRAFFIC_RECORD))
         if code_digest(rec["sources"]) != rec["code_sha256"]:
             return None
-        return {k: rec[k]["fetch_bytes_per_launch"] + rec[k]["write_bytes_per_launch"]
-                for k in ("local", "global")}
+        b = {k: rec[k]["fetch_bytes_per_launch"] + rec[k]["write_bytes_per_launch"]
+             for k in ("local", "global", "anchor")}
+        return {"local": b["local"], "global": b["global"] + b["anchor"]}
     except (OSError, ValueError, KeyError, TypeError):
         return None
 
@@ -147,8 +149,9 @@ def gpu_leg(w, steps, warmup, G=0, W=0, target=None, count_work=True):
     info = ctx.info()
     cyc = w.global_every
     # a step is one cycle: its localized sweeps (one launch of the localized-sweep
-    # kernel) and then its global sweeps (one launch of the global-sweep kernel), as
-    # amh_sweep(cyc) issues them; events on the launch stream around each
+    # kernel) and then its global sweeps with their anchor (one launch of the global-sweep
+    # kernel and one of the anchor kernel), as amh_sweep(cyc) issues them; events on the
+    # launch stream around each
     n_glob = w.n_global
     n_loc = cyc - n_glob
     stream = torch.cuda.current_stream()
@@ -759,7 +762,7 @@ def main():
     glob, loc = pair_evals_per_cycle(w.L, w.window_d, cyc)
     dense_pairs = (glob + loc) * w.n_chains
     # rooflines on the work each kernel executes per launch (a step = one launch of the
-    # localized-sweep kernel and one of the global-sweep kernel): the schedule's fixed
+    # localized-sweep kernel, and one of the global-sweep kernel with its anchor launch): the schedule's fixed
     # part plus the counted global-sweep part, averaged over the timed steps, over the
     # kernel's average launch duration (HIP events on the launch stream)
     per_launch = {k: v / args.steps for k, v in r["counted"].items()}
@@ -786,12 +789,12 @@ def main():
                            "frac": gb / l2y if l2y else None}}
 
     traffic = measured_traffic() if w.name == sy.CFG2.name else None
-    roof_g = roof(ex["global"], glob_s, f"sweep_kernel<{Gg}, 2> (global sweeps)",
+    roof_g = roof(ex["global"], glob_s, f"global_kernel ({Gg} chains per workgroup) and anchor_kernel",
                   traffic.get("global") if traffic else None)
     roof_g["dense_equivalent"] = {"pairs_per_launch": glob * w.n_chains,
                                   "note": "every changed pair of the rectangle counted, culled or not; "
                                           "not executed work"}
-    roof_l = roof(ex["local"], loc_s, f"sweep_kernel<{Gl}, 1> (localized sweeps)",
+    roof_l = roof(ex["local"], loc_s, f"local_kernel<{Gl}> (localized sweeps)",
                   traffic.get("local") if traffic else None)
     a_step = ex["step"]["flops"] / step_s
     cnt = r["counters"]

@@ -167,17 +167,18 @@ amh_status amh_set_work_counters(amh_ctx* ctx, int64_t* counters_dev);
  * (AMH_E_NUMERIC) raised by earlier calls. */
 amh_status amh_poll(amh_ctx* ctx);
 
-/* Launch shape chosen for the context (chains and wavefronts per workgroup and LDS
- * bytes of a launch that runs any sweeps: the batched launches' own-shape plan) and
- * the current sweep index.  amh_sweep runs a range of sweeps as one launch per run of
- * consecutive sweeps of one kind, localized or global; amh_info_launches gives their
- * shapes. */
+/* Launch shape chosen for the context (chains and wavefronts per workgroup: the batched
+ * launches' own-shape plan; the LDS bytes of the larger of its localized and global
+ * launches) and the current sweep index.  amh_sweep runs a range of sweeps as one launch
+ * per run of consecutive sweeps of one kind, localized or global, and one per anchor;
+ * amh_info_launches gives their shapes. */
 amh_status amh_info(amh_ctx* ctx, int32_t* chains_per_group, int32_t* waves_per_group,
                     int32_t* lds_bytes, int64_t* t);
 
 /* Launch shapes of amh_sweep's localized-sweep launches (consecutive localized sweeps
  * of a workgroup's chains are pipelined over its wavefronts) and global-sweep
- * launches: chains and wavefronts per workgroup and LDS bytes.  Any output pointer
+ * launches (a workgroup's wavefronts are divided among its chains): chains and
+ * wavefronts per workgroup and LDS bytes.  Any output pointer
  * may be NULL. */
 amh_status amh_info_launches(amh_ctx* ctx, int32_t* local_chains_per_group, int32_t* local_waves_per_group,
                              int32_t* local_lds_bytes, int32_t* global_chains_per_group,
@@ -333,6 +334,8 @@ amh_status amh_server_destroy(amh_server* server);
  * parallelism), so one launch can advance the chains of several proteins: each
  * workgroup runs one chain group of one member, with the LDS of the launch sized
  * for its longest member and the grid ordered by decreasing work per workgroup.
+ * Localized runs, global runs and anchors of the members are launched in turn; members
+ * at the same point of their cycles share every launch.
  * Members with different launch shapes (chains per workgroup, wavefronts) are
  * advanced by one launch per shape.  Trajectories do not depend on the launch
  * shape or on the batch: a member advanced in a batch follows exactly the sweeps

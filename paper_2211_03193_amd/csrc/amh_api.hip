@@ -68,16 +68,14 @@ struct amh_ctx {
   unsigned int* err = nullptr;
   int64_t t = 0;
   double target = -INFINITY;
+  // shape of the context (chains and wavefronts per workgroup)
   int G = 1, W = 4;
-  size_t lds = 0;
   // sum of every table row's no-contact value (far_sum_kernel)
   double vfar = 0.0;
-  // launch shape of the localized-sweep kernel (wavefronts, LDS bytes)
+  // launch shape of the localized-sweep kernel (wavefronts; G chains per workgroup)
   int W_local = 4;
-  size_t lds_local = 0;
-  // launch shape of the global-sweep kernel (chains and wavefronts per workgroup, LDS)
+  // launch shape of the global-sweep kernel (chains and wavefronts per workgroup)
   int G_global = 1, W_global = 4;
-  size_t lds_global = 0;
   // trace
   int n_trace = 0;
   int trace_chain[4] = {-1, -1, -1, -1};
@@ -129,7 +127,7 @@ amh_status scratch_address(int dev, double** out) {
 namespace {
 
 // n_cu: compute units of the device (for the automatic launch shape).
-amh_status validate(const amh_config* c, int n_cu, int* G, int* W, size_t* lds) {
+amh_status validate(const amh_config* c, int n_cu, int* G, int* W) {
   if (!c) return sfail(AMH_E_INVAL, "config is NULL");
   if (c->L < 2 || c->L > 1024) return sfail(AMH_E_INVAL, "L=%d outside [2, 1024]", c->L);
   if (c->n_chains < 1) return sfail(AMH_E_INVAL, "n_chains=%d < 1", c->n_chains);
@@ -179,7 +177,6 @@ amh_status validate(const amh_config* c, int n_cu, int* G, int* W, size_t* lds) 
                 c->L, g, need, kMaxLds);
   *G = g;
   *W = w;
-  *lds = need;
   return AMH_OK;
 }
 
@@ -213,7 +210,7 @@ amh::ConfParams conf_base(const amh_ctx* x) {
 
 amh_status launch_conf(const amh::ConfParams& P, int B, hipStream_t st) {
   if (B <= 0) return AMH_OK;
-  const size_t lds = amh::conf_lds_bytes(P.L, kConfThreads / 64);
+  const size_t lds = amh::conf_lds_bytes(P.L);
   HIP_OK(hipFuncSetAttribute((const void*)amh::conf_energy_kernel,
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
   hipLaunchKernelGGL(amh::conf_energy_kernel, dim3(B), dim3(kConfThreads), lds, st, P);
@@ -283,6 +280,60 @@ amh_status read_err(amh_ctx* x, unsigned int* out) {
   HIP_OK(hipStreamSynchronize(x->stream));
   HIP_OK(hipMemcpy(out, x->err, sizeof(unsigned int), hipMemcpyDeviceToHost));
   return AMH_OK;
+}
+
+}  // namespace
+
+namespace {
+
+template <typename... Args>
+amh_status launch(const void* fn, dim3 grid, int threads, size_t lds, hipStream_t st, Args&&... args) {
+  HIP_OK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  void* a[] = {(void*)&args...};
+  HIP_OK(hipLaunchKernel(fn, grid, dim3(threads), a, lds, st));
+  return AMH_OK;
+}
+
+// Wavefronts a chain gets in a global-sweep workgroup of G chains and W wavefronts (a
+// power of two; wavefronts left over idle).
+int global_waves(int G, int W) {
+  int nw = 1;
+  while (2 * nw * G <= W && nw < 16) nw *= 2;
+  return nw;
+}
+
+const void* global_fn(int nw, bool batch) {
+  switch (nw) {
+    case 1: return batch ? (const void*)amh::global_batch_kernel<1> : (const void*)amh::global_kernel<1>;
+    case 2: return batch ? (const void*)amh::global_batch_kernel<2> : (const void*)amh::global_kernel<2>;
+    case 4: return batch ? (const void*)amh::global_batch_kernel<4> : (const void*)amh::global_kernel<4>;
+    case 8: return batch ? (const void*)amh::global_batch_kernel<8> : (const void*)amh::global_kernel<8>;
+    default: return batch ? (const void*)amh::global_batch_kernel<16> : (const void*)amh::global_kernel<16>;
+  }
+}
+
+const void* local_fn(int G, bool batch) {
+  switch (G) {
+    case 1: return batch ? (const void*)amh::local_batch_kernel<1> : (const void*)amh::local_kernel<1>;
+    case 2: return batch ? (const void*)amh::local_batch_kernel<2> : (const void*)amh::local_kernel<2>;
+    default: return batch ? (const void*)amh::local_batch_kernel<4> : (const void*)amh::local_kernel<4>;
+  }
+}
+
+// Wavefronts of a localized launch: kLocalWaves where their LDS fits, else W.
+int local_waves(int G, int L, int W) { return amh::local_lds_bytes(G, L, kLocalWaves) <= kMaxLds ? kLocalWaves : W; }
+
+size_t global_launch_lds(const amh_ctx* x) {
+  return amh::global_lds_bytes(x->G_global, x->cfg.L, global_waves(x->G_global, x->W_global));
+}
+
+// End of the run of sweeps that starts at t: sweeps of one kind (localized or global), up
+// to an anchor (after a sweep count that anchor_every divides) or `end`.
+int64_t run_end(const amh::SweepParams& P, int64_t t, int64_t end) {
+  const bool glob = amh::is_global(P, t);
+  int64_t e = t + 1;
+  while (e < end && e % P.anchor_every != 0 && amh::is_global(P, e) == glob) ++e;
+  return e;
 }
 
 }  // namespace
@@ -385,13 +436,12 @@ amh_status amh_init(const amh_config* cfg, const float* y_dev, const double* s0_
   if (!out) return sfail(AMH_E_INVAL, "out is NULL");
   *out = nullptr;
   int G = 0, W = 0;
-  size_t lds = 0;
   int dev = 0, n_cu = 0;
   const bool have_dev = hipGetDevice(&dev) == hipSuccess;
   if (!have_dev || hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
       n_cu < 1)
     n_cu = 256;
-  amh_status st = validate(cfg, n_cu, &G, &W, &lds);
+  amh_status st = validate(cfg, n_cu, &G, &W);
   if (st != AMH_OK) return st;
   if (!y_dev) return sfail(AMH_E_INVAL, "distogram table is NULL");
   if (!have_dev) return sfail(AMH_E_DEVICE, "no current HIP device");
@@ -403,22 +453,17 @@ amh_status amh_init(const amh_config* cfg, const float* y_dev, const double* s0_
   x->stream = reinterpret_cast<hipStream_t>(stream);
   x->G = G;
   x->W = W;
-  x->lds = lds;
   // localized sweeps run with kLocalWaves wavefronts (consecutive sweeps of a block
   // pipelined over more stages) where their LDS fits
-  x->W_local = amh::sweep_lds_bytes_local(G, cfg->L, kLocalWaves) <= kMaxLds ? kLocalWaves : W;
-  x->lds_local = amh::sweep_lds_bytes_local(G, cfg->L, x->W_local);
+  x->W_local = local_waves(G, cfg->L, W);
   // global sweeps of an automatically shaped context: two workgroups of two chains
-  // and four wavefronts per CU where their LDS fits, so that one workgroup runs
-  // while the other waits at a barrier
+  // and four wavefronts per CU, so that one workgroup runs while the other waits at a
+  // barrier
   x->G_global = G;
   x->W_global = W;
-  x->lds_global = lds;
-  if (cfg->chains_per_group == 0 && cfg->waves_per_group == 0 && G == 4 && W == 8 &&
-      2 * amh::sweep_lds_bytes(2, cfg->L, 4) <= kMaxLds) {
+  if (cfg->chains_per_group == 0 && cfg->waves_per_group == 0 && G == 4 && W == 8) {
     x->G_global = 2;
     x->W_global = 4;
-    x->lds_global = amh::sweep_lds_bytes(2, cfg->L, 4);
   }
   const int L = cfg->L, C = cfg->n_chains, n = 2 * L;
   const int64_t P = (int64_t)L * (L - 1) / 2;
@@ -490,37 +535,30 @@ amh_status amh_sweep(amh_ctx* x, int64_t n_sweeps) {
     return sfail(AMH_E_INVAL, "sweep %lld + %lld passes total_sweeps=%lld", (long long)x->t,
                 (long long)n_sweeps, (long long)x->cfg.total_sweeps);
   if (n_sweeps == 0) return AMH_OK;
-  const amh::SweepParams P0 = sweep_params(x, n_sweeps);
+  amh::SweepParams P = sweep_params(x, n_sweeps);
   const amh_config& c = x->cfg;
-  const dim3 grid((c.n_chains + x->G - 1) / x->G), block(64 * x->W);
-  const int wl = x->W_local;
-  const size_t lds_l = x->lds_local;
-  // one launch per run of sweeps of one kind (localized or global), in order on the
-  // stream; a launch boundary between two sweeps does not change any result
-  for (int64_t t = P0.t0; t < P0.t0 + P0.n_sweeps;) {
-    const bool glob = amh::is_global(P0, t);
-    int64_t e = t + 1;
-    while (e < P0.t0 + P0.n_sweeps && amh::is_global(P0, e) == glob) ++e;
-    amh::SweepParams P = P0;
+  // one launch per run of sweeps of one kind (localized or global) and one per anchor, in
+  // order on the stream; a launch boundary between two sweeps does not change any result
+  const int64_t end = x->t + n_sweeps;
+  for (int64_t t = x->t; t < end;) {
+    const bool glob = amh::is_global(P, t);
+    const int64_t e = run_end(P, t, end);
     P.t0 = t;
     P.n_sweeps = e - t;
-    const void* fn = nullptr;
-    switch (glob ? x->G_global : x->G) {
-      case 1: fn = glob ? (const void*)amh::sweep_kernel<1, amh::kSweepGlobal>
-                        : (const void*)amh::sweep_kernel<1, amh::kSweepLocal>; break;
-      case 2: fn = glob ? (const void*)amh::sweep_kernel<2, amh::kSweepGlobal>
-                        : (const void*)amh::sweep_kernel<2, amh::kSweepLocal>; break;
-      default: fn = glob ? (const void*)amh::sweep_kernel<4, amh::kSweepGlobal>
-                         : (const void*)amh::sweep_kernel<4, amh::kSweepLocal>; break;
+    const int G = glob ? x->G_global : x->G, nw = global_waves(x->G_global, x->W_global);
+    const dim3 grid((c.n_chains + G - 1) / G);
+    amh_status st = glob ? launch(global_fn(nw, false), grid, 64 * x->W_global,
+                                  amh::global_lds_bytes(G, c.L, nw), x->stream, P, G)
+                         : launch(local_fn(G, false), grid, 64 * x->W_local,
+                                  amh::local_lds_bytes(G, c.L, x->W_local), x->stream, P);
+    if (st == AMH_OK && e % c.anchor_every == 0) {
+      P.t0 = e;
+      st = launch((const void*)amh::anchor_kernel, dim3(c.n_chains), kConfThreads,
+                  amh::conf_lds_bytes(c.L), x->stream, P);
     }
-    const size_t lds = glob ? x->lds_global : lds_l;
-    const dim3 gg((c.n_chains + x->G_global - 1) / x->G_global);
-    HIP_OK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    void* args[] = {&P};
-    HIP_OK(hipLaunchKernel(fn, glob ? gg : grid, dim3(64 * (glob ? x->W_global : wl)), args, lds, x->stream));
+    if (st != AMH_OK) return st;
     t = e;
   }
-  HIP_OK(hipGetLastError());
   x->t += n_sweeps;
   return AMH_OK;
 }
@@ -671,7 +709,7 @@ amh_status amh_info(amh_ctx* x, int32_t* G, int32_t* W, int32_t* lds, int64_t* t
   if (!x) return sfail(AMH_E_INVAL, "ctx is NULL");
   if (G) *G = x->G;
   if (W) *W = x->W;
-  if (lds) *lds = (int32_t)x->lds;
+  if (lds) *lds = (int32_t)std::max(amh::local_lds_bytes(x->G, x->cfg.L, x->W_local), global_launch_lds(x));
   if (t) *t = x->t;
   return AMH_OK;
 }
@@ -681,10 +719,10 @@ amh_status amh_info_launches(amh_ctx* x, int32_t* local_G, int32_t* local_W, int
   if (!x) return sfail(AMH_E_INVAL, "ctx is NULL");
   if (local_G) *local_G = x->G;
   if (local_W) *local_W = x->W_local;
-  if (local_lds) *local_lds = (int32_t)x->lds_local;
+  if (local_lds) *local_lds = (int32_t)amh::local_lds_bytes(x->G, x->cfg.L, x->W_local);
   if (global_G) *global_G = x->G_global;
   if (global_W) *global_W = x->W_global;
-  if (global_lds) *global_lds = (int32_t)x->lds_global;
+  if (global_lds) *global_lds = (int32_t)global_launch_lds(x);
   return AMH_OK;
 }
 
@@ -752,13 +790,13 @@ amh_status amh_destroy(amh_ctx* x) {
 }  // extern "C"
 
 // ---------------------------------------------------------------------------
-// Batches: several contexts (proteins of different lengths) advanced by one launch
-// per launch shape.
+// Batches: several contexts (proteins of different lengths) advanced by shared launches,
+// one per launch shape and kind of sweep.
 
 namespace {
 
 constexpr int kRing = 8;   // pinned descriptor staging buffers in flight
-constexpr int kMaxRuns = 8;   // runs of one kind of sweep per call with split launches
+constexpr int kMaxRuns = 8;   // descriptor sets (one a launch) uploaded together
 // launch plans: 0 = each context's own shape, then uniform (chains per group, waves)
 constexpr int kPlans = 6;
 constexpr int kPlanShape[kPlans][2] = {{0, 0}, {1, 4}, {2, 4}, {2, 8}, {4, 4}, {4, 8}};
@@ -771,8 +809,8 @@ struct amh_batch {
   int plan = 0;
   struct Launch {
     int G = 1, W = 4;
-    size_t lds = 0;
-    size_t lds_local = 0;   // LDS of a localized-only launch with kLocalWaves wavefronts
+    int W_local = 4;   // wavefronts of a localized launch
+    size_t lds_local = 0, lds_global = 0, lds_anchor = 0;   // of the longest member
     int n_wg = 0;
     int2* d_map = nullptr;
   };
@@ -836,12 +874,12 @@ amh_status build_launches(amh_batch* b, int plan) {
     amh_batch::Launch l;
     l.G = shapes[s].first;
     l.W = shapes[s].second;
+    int longest = 2;
     std::vector<std::pair<double, int2>> items;
     for (size_t i = 0; i < b->m.size(); ++i) {
       if (shape_of[i] != (int)s) continue;
       const amh_ctx* x = b->m[i];
-      l.lds = std::max(l.lds, amh::sweep_lds_bytes(l.G, x->cfg.L, l.W));
-      l.lds_local = std::max(l.lds_local, amh::sweep_lds_bytes_local(l.G, x->cfg.L, kLocalWaves));
+      longest = std::max(longest, x->cfg.L);
       const int groups = (x->cfg.n_chains + l.G - 1) / l.G;
       for (int g = 0; g < groups; ++g) items.push_back({member_cost(x), make_int2((int)i, g)});
     }
@@ -850,6 +888,10 @@ amh_status build_launches(amh_batch* b, int plan) {
     std::vector<int2> map;
     for (auto& it : items) map.push_back(it.second);
     l.n_wg = (int)map.size();
+    l.W_local = local_waves(l.G, longest, l.W);
+    l.lds_local = amh::local_lds_bytes(l.G, longest, l.W_local);
+    l.lds_global = amh::global_lds_bytes(l.G, longest, global_waves(l.G, l.W));
+    l.lds_anchor = amh::conf_lds_bytes(longest);
     hipError_t e = hipMalloc(reinterpret_cast<void**>(&l.d_map), sizeof(int2) * map.size());
     if (e != hipSuccess) return sfail(AMH_E_NOMEM, "hipMalloc: %s", hipGetErrorString(e));
     b->launches.push_back(l);
@@ -859,23 +901,22 @@ amh_status build_launches(amh_batch* b, int plan) {
   return AMH_OK;
 }
 
-template <int G, int MODE>
-amh_status launch_batch(const amh_batch* b, const amh_batch::Launch& l, const amh::SweepParams* descs,
-                        int W, size_t lds) {
-  HIP_OK(hipFuncSetAttribute((const void*)amh::sweep_batch_kernel<G, MODE>,
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  hipLaunchKernelGGL((amh::sweep_batch_kernel<G, MODE>), dim3(l.n_wg), dim3(64 * W), lds, b->stream, descs,
-                     (const int2*)l.d_map);
-  HIP_OK(hipGetLastError());
-  return AMH_OK;
-}
+enum class Step { local, global, anchor };
 
-template <int MODE>
-amh_status launch_batch_mode(const amh_batch* b, const amh_batch::Launch& l, const amh::SweepParams* descs,
-                             int W, size_t lds) {
-  return l.G == 1 ? launch_batch<1, MODE>(b, l, descs, W, lds)
-         : l.G == 2 ? launch_batch<2, MODE>(b, l, descs, W, lds)
-                    : launch_batch<4, MODE>(b, l, descs, W, lds);
+// The launches of one step (one per shape) over the members' descriptors.
+amh_status launch_step(const amh_batch* b, Step kind, const amh::SweepParams* descs) {
+  for (const auto& l : b->launches) {
+    const int2* map = l.d_map;
+    const int G = l.G, nw = global_waves(l.G, l.W);
+    const amh_status st =
+        kind == Step::local ? launch(local_fn(G, true), dim3(l.n_wg), 64 * l.W_local, l.lds_local, b->stream, descs, map)
+        : kind == Step::global
+            ? launch(global_fn(nw, true), dim3(l.n_wg), 64 * l.W, l.lds_global, b->stream, descs, map, G)
+            : launch((const void*)amh::anchor_batch_kernel, dim3(l.n_wg, G), kConfThreads, l.lds_anchor, b->stream,
+                     descs, map, G);
+    if (st != AMH_OK) return st;
+  }
+  return AMH_OK;
 }
 
 }  // namespace
@@ -925,59 +966,74 @@ amh_status amh_batch_sweep_each(amh_batch* b, const int64_t* n_sweeps) {
   }
   if (most == 0) return AMH_OK;
   const size_t nm = b->m.size();
-  // Split launches (localized-only and global-only kernels, one launch per run of
-  // one kind) when every member advances by the same count through the same pattern
-  // of localized and global sweeps; else one launch of the kernel that runs any
-  // sweeps.  The results are the same either way.  Descriptors go up kMaxRuns runs
-  // at a time (stream order keeps an upload behind the launches that read the last).
-  std::vector<std::pair<int64_t, bool>> runs;   // (length, global)
-  bool split = true;
-  for (size_t i = 1; i < nm && split; ++i) split = n_sweeps[i] == n_sweeps[0];
-  if (split) {
-    std::vector<amh::SweepParams> P0(nm);
-    for (size_t i = 0; i < nm; ++i) P0[i] = sweep_params(b->m[i], n_sweeps[i]);
-    for (int64_t o = 0; o < most && split; ++o) {
-      const bool g = amh::is_global(P0[0], P0[0].t0 + o);
-      for (size_t i = 1; i < nm && split; ++i) split = amh::is_global(P0[i], P0[i].t0 + o) == g;
-      if (!split) break;
-      if (!runs.empty() && runs.back().second == g) ++runs.back().first;
-      else runs.emplace_back(1, g);
-    }
+  // Steps of one kind in turn: every member whose next run of sweeps is of that kind
+  // (localized or global, up to an anchor or its last sweep) takes part, the others pass
+  // through (n_sweeps = 0); an anchor step follows for the members that reached one.
+  // Members at the same point of their cycles share every step.  Descriptors go up
+  // kMaxRuns steps at a time (stream order keeps an upload behind the launches that read
+  // the last).
+  std::vector<int64_t> t(nm), end(nm), anchored(nm);
+  std::vector<amh::SweepParams> base(nm);
+  for (size_t i = 0; i < nm; ++i) {
+    base[i] = sweep_params(b->m[i], n_sweeps[i]);
+    t[i] = b->m[i]->t;
+    end[i] = t[i] + n_sweeps[i];
+    anchored[i] = t[i];
   }
-  for (const auto& l : b->launches) split = split && l.lds_local <= kMaxLds;
-  if (!split) runs.assign(1, std::make_pair(most, false));
-  int64_t off = 0;
-  for (size_t r0 = 0; r0 < runs.size(); r0 += kMaxRuns) {
-    const size_t nset = std::min(runs.size() - r0, (size_t)kMaxRuns);
+  std::vector<Step> steps;
+  auto upload_and_launch = [&]() -> amh_status {
+    if (steps.empty()) return AMH_OK;
     const int slot = b->ring;
-    if (b->ev_used[slot]) HIP_OK(hipEventSynchronize(b->ev[slot]));
-    for (size_t r = 0; r < nset; ++r) {
-      for (size_t i = 0; i < nm; ++i) {
-        amh::SweepParams P = sweep_params(b->m[i], n_sweeps[i]);
-        if (split) {
-          P.t0 += off;
-          P.n_sweeps = runs[r0 + r].first;
-        }
-        b->h_desc[slot][r * nm + i] = P;
-      }
-      off += runs[r0 + r].first;
-    }
-    HIP_OK(hipMemcpyAsync(b->d_desc, b->h_desc[slot], sizeof(amh::SweepParams) * nset * nm,
+    HIP_OK(hipMemcpyAsync(b->d_desc, b->h_desc[slot], sizeof(amh::SweepParams) * steps.size() * nm,
                           hipMemcpyHostToDevice, b->stream));
     HIP_OK(hipEventRecord(b->ev[slot], b->stream));
     b->ev_used[slot] = true;
     b->ring = (slot + 1) % kRing;
-    for (size_t r = 0; r < nset; ++r) {
-      const amh::SweepParams* descs = b->d_desc + r * nm;
-      for (const auto& l : b->launches) {
-        amh_status st = !split ? launch_batch_mode<amh::kSweepMixed>(b, l, descs, l.W, l.lds)
-                        : runs[r0 + r].second
-                            ? launch_batch_mode<amh::kSweepGlobal>(b, l, descs, l.W, l.lds)
-                            : launch_batch_mode<amh::kSweepLocal>(b, l, descs, kLocalWaves, l.lds_local);
-        if (st != AMH_OK) return st;
-      }
+    for (size_t r = 0; r < steps.size(); ++r) {
+      const amh_status st = launch_step(b, steps[r], b->d_desc + r * nm);
+      if (st != AMH_OK) return st;
     }
+    steps.clear();
+    return AMH_OK;
+  };
+  // one more step; fill(i, P) completes member i's descriptor and says whether it takes part
+  auto add_step = [&](Step kind, auto fill) -> amh_status {
+    if (steps.empty() && b->ev_used[b->ring]) HIP_OK(hipEventSynchronize(b->ev[b->ring]));
+    amh::SweepParams* d = b->h_desc[b->ring] + steps.size() * nm;
+    bool any = false;
+    for (size_t i = 0; i < nm; ++i) {
+      d[i] = base[i];
+      d[i].n_sweeps = 0;
+      any = fill(i, d[i]) || any;
+    }
+    if (!any) return AMH_OK;
+    steps.push_back(kind);
+    return steps.size() == (size_t)kMaxRuns ? upload_and_launch() : AMH_OK;
+  };
+  bool left = true;
+  for (bool glob = false; left; glob = !glob) {
+    amh_status st = add_step(glob ? Step::global : Step::local, [&](size_t i, amh::SweepParams& P) {
+      if (t[i] >= end[i] || amh::is_global(base[i], t[i]) != glob) return false;
+      P.t0 = t[i];
+      t[i] = run_end(base[i], t[i], end[i]);
+      P.n_sweeps = t[i] - P.t0;
+      return true;
+    });
+    // (a member that did not advance in this step stands at an anchor it has already made,
+    // or at its start)
+    if (st == AMH_OK)
+      st = add_step(Step::anchor, [&](size_t i, amh::SweepParams& P) {
+        if (t[i] == anchored[i] || t[i] % P.anchor_every != 0) return false;
+        P.t0 = anchored[i] = t[i];
+        P.n_sweeps = 1;
+        return true;
+      });
+    if (st != AMH_OK) return st;
+    left = false;
+    for (size_t i = 0; i < nm; ++i) left = left || t[i] < end[i];
   }
+  const amh_status st = upload_and_launch();
+  if (st != AMH_OK) return st;
   for (size_t i = 0; i < nm; ++i) b->m[i]->t += n_sweeps[i];
   return AMH_OK;
 }

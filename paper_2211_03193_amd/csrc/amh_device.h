@@ -126,10 +126,16 @@ __device__ __forceinline__ D3 apply_rot(const Rot& R, D3 x) {
   return D3{R.a[0] + v.x, R.a[1] + v.y, R.a[2] + v.z};
 }
 
+// Squared length in float32, the order of the fused operations written out: which product
+// the compiler would round on its own depends on the code around it, and a decision near
+// a tie on that bit.
+__device__ __forceinline__ float norm2(float dx, float dy, float dz) {
+  return fmaf(dz, dz, fmaf(dx, dx, dy * dy));
+}
+
 // float32 squared distance of two float64 points (difference taken in float64).
 __device__ __forceinline__ float dist2_64(D3 a, D3 b) {
-  const float dx = (float)(b.x - a.x), dy = (float)(b.y - a.y), dz = (float)(b.z - a.z);
-  return dx * dx + dy * dy + dz * dz;
+  return norm2((float)(b.x - a.x), (float)(b.y - a.y), (float)(b.z - a.z));
 }
 
 // ---------------------------------------------------------------------------
@@ -156,8 +162,8 @@ __device__ __forceinline__ void spline_pos(float d, const Spline32& S, int& b, f
 // Uniform Catmull-Rom cubic through (y0, y1, y2, y3) at fraction f of [y1, y2].
 __device__ __forceinline__ float catmull_rom(float y0, float y1, float y2, float y3, float f) {
   const float a1 = y2 - y0;
-  const float a2 = 2.0f * y0 - 5.0f * y1 + 4.0f * y2 - y3;
-  const float a3 = 3.0f * (y1 - y2) + y3 - y0;
+  const float a2 = fmaf(4.0f, y2, fmaf(2.0f, y0, -5.0f * y1)) - y3;   // (fused in this order everywhere)
+  const float a3 = fmaf(3.0f, y1 - y2, y3) - y0;
   return fmaf(0.5f * f, fmaf(f, fmaf(f, a3, a2), a1), y1);
 }
 

@@ -16,7 +16,7 @@ __device__ __forceinline__ const double* atom(const double* x64, int r, int a) {
 }
 
 // ---------------------------------------------------------------------------
-// Float64 NeRF of one chain by a whole wavefront, in parallel over the atoms
+// Float64 NeRF of one chain by a whole workgroup, in parallel over the atoms
 // (Parsons et al. 2005 placement; the parallel form of AlQuraishi's pNeRF).  Backbone
 // atom a_k (k >= 3: N, CA, C of residue k/3) is placed from a_{k-3}, a_{k-2}, a_{k-1}
 // in the frame (e1 = unit(a_{k-1} - a_{k-2}), n = unit((a_{k-2} - a_{k-3}) x e1),
@@ -27,11 +27,31 @@ __device__ __forceinline__ const double* atom(const double* x64, int r, int a) {
 //          [sin t sin x, -cos t sin x, cos x]],
 // which depends only on (t, x), so every frame is a prefix product of the rigid
 // transforms (R_k, l R_k e_1) (composition (R, u) o (R', u') = (R R', u + R u')).  The
-// wavefront takes the transforms 64 at a time (one per lane), scans them across the
-// lanes (Hillis-Steele, six steps) and applies the frame carried from the previous
-// 64; C-beta then follows per residue from its N, CA, C.  The rounding differs from
-// a serial build only at the last bits (about 1e-13 of the chain's extent).
-static __device__ void nerf_chain(const double* __restrict__ s, int L, double* __restrict__ x64, int lane) {
+// transforms go 64 to a block, one per lane, and each block is scanned across its
+// wavefront's lanes (Hillis-Steele, six steps), the blocks dealt to the wavefronts in
+// turn; one wavefront then carries the frame from block to block (one composition
+// each), and every atom follows from its block's frame; C-beta follows per residue from
+// its N, CA, C.  The scan is nearly all of the work (72 lane exchanges and six dependent
+// 3x3 products a block), so it is shared by the wavefronts; the values do not depend on
+// how many there are.  The rounding differs from a serial build only at the last bits
+// (about 1e-13 of the chain's extent).
+//
+// x64 [12L] and fr [nerf_scratch(L)] are in LDS, s [2L] anywhere; s is complete (a barrier
+// if the workgroup wrote it) and nobody uses fr; ends with a barrier of the workgroup.
+// A row of a 3x3 matrix times a vector, and the same plus an offset, with the order of the
+// fused operations written out: every kernel builds the same coordinates, bit for bit.
+__device__ __forceinline__ double row3(const double* m, double x, double y, double z) {
+  return fma(m[2], z, fma(m[0], x, m[1] * y));
+}
+__device__ __forceinline__ double row3(double o, const double* m, double x, double y, double z) {
+  return fma(m[2], z, fma(m[1], y, fma(m[0], x, o)));
+}
+
+__host__ __device__ inline int nerf_scratch(int L) { return 12 * ((3 * (L - 1) + 63) / 64); }
+
+__device__ inline void nerf_wg(const double* __restrict__ s, int L, double* __restrict__ x64,
+                               double* __restrict__ fr) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, W = blockDim.x >> 6;
   const double ct_cacn = cos(kAngCACN * kDeg), st_cacn = sin(kAngCACN * kDeg);
   const double ct_cnca = cos(kAngCNCA * kDeg), st_cnca = sin(kAngCNCA * kDeg);
   const double ct_ncac = cos(kAngNCAC * kDeg), st_ncac = sin(kAngNCAC * kDeg);
@@ -42,32 +62,22 @@ static __device__ void nerf_chain(const double* __restrict__ s, int L, double* _
   const double N0[3] = {0.0, 0.0, 0.0};
   const double CA0[3] = {kBondNCA, 0.0, 0.0};
   const double C0[3] = {kBondNCA - kBondCAC * ct_ncac, kBondCAC * st_ncac, 0.0};
-  if (lane < 9) atom(x64, 0, lane / 3)[lane % 3] = lane < 3 ? N0[lane] : lane < 6 ? CA0[lane - 3] : C0[lane - 6];
-  // frame of atom 3 (N_1): from N_0, CA_0, C_0, origin C_0 (uniform over the lanes)
-  double F[9], o[3];
-  {
-    double bx = C0[0] - CA0[0], by = C0[1] - CA0[1], bz = C0[2] - CA0[2];
-    const double ib = 1.0 / sqrt(bx * bx + by * by + bz * bz);
-    bx *= ib; by *= ib; bz *= ib;
-    const double ax = CA0[0] - N0[0], ay = CA0[1] - N0[1], az = CA0[2] - N0[2];
-    double nx = ay * bz - az * by, ny = az * bx - ax * bz, nz = ax * by - ay * bx;
-    const double in = 1.0 / sqrt(nx * nx + ny * ny + nz * nz);
-    nx *= in; ny *= in; nz *= in;
-    const double mx = ny * bz - nz * by, my = nz * bx - nx * bz, mz = nx * by - ny * bx;
-    F[0] = bx; F[1] = mx; F[2] = nx;
-    F[3] = by; F[4] = my; F[5] = ny;
-    F[6] = bz; F[7] = mz; F[8] = nz;
-    o[0] = C0[0]; o[1] = C0[1]; o[2] = C0[2];
-  }
-  const int nt = 3 * (L - 1);   // placed backbone atoms
-  for (int k0 = 0; k0 < nt; k0 += 64) {
-    const int j = k0 + lane, k = 3 + j, kind = k % 3, c = k / 3;
+  if (wave == 0 && lane < 9)
+    atom(x64, 0, lane / 3)[lane % 3] = lane < 3 ? N0[lane] : lane < 6 ? CA0[lane - 3] : C0[lane - 6];
+  const int nt = 3 * (L - 1), nblk = (nt + 63) >> 6;   // placed backbone atoms and their blocks
+  for (int blk = wave; blk < nblk; blk += W) {
+    const int k0 = 64 * blk, j = k0 + lane, k = 3 + j, kind = k % 3, c = k / 3;
     // this lane's transform (absent lanes: the identity)
     double ct = 1.0, st = 0.0, l = 0.0, cx = 1.0, sx = 0.0;
     if (j < nt) {
-      if (kind == 0) { ct = ct_cacn; st = st_cacn; l = kBondCN; sincos(s[2 * c - 1], &sx, &cx); }
-      else if (kind == 1) { ct = ct_cnca; st = st_cnca; l = kBondNCA; cx = co; sx = so; }
-      else { ct = ct_ncac; st = st_ncac; l = kBondCAC; sincos(s[2 * c], &sx, &cx); }
+      if (kind == 1) {
+        ct = ct_cnca; st = st_cnca; l = kBondNCA; cx = co; sx = so;
+      } else {
+        ct = kind == 0 ? ct_cacn : ct_ncac;
+        st = kind == 0 ? st_cacn : st_ncac;
+        l = kind == 0 ? kBondCN : kBondCAC;
+        sincos(s[kind == 0 ? 2 * c - 1 : 2 * c], &sx, &cx);
+      }
     }
     double R[9], u[3];
     if (j < nt) {
@@ -90,41 +100,82 @@ static __device__ void nerf_chain(const double* __restrict__ s, int L, double* _
 #pragma unroll
         for (int r = 0; r < 3; ++r) {
 #pragma unroll
-          for (int q = 0; q < 3; ++q) Rn[3 * r + q] = Rp[3 * r] * R[q] + Rp[3 * r + 1] * R[3 + q] + Rp[3 * r + 2] * R[6 + q];
-          un[r] = up[r] + Rp[3 * r] * u[0] + Rp[3 * r + 1] * u[1] + Rp[3 * r + 2] * u[2];
+          for (int q = 0; q < 3; ++q) Rn[3 * r + q] = row3(Rp + 3 * r, R[q], R[3 + q], R[6 + q]);
+          un[r] = row3(up[r], Rp + 3 * r, u[0], u[1], u[2]);
         }
 #pragma unroll
         for (int q = 0; q < 9; ++q) R[q] = Rn[q];
         u[0] = un[0]; u[1] = un[1]; u[2] = un[2];
       }
     }
-    // atom k = origin of the frame after this lane's transform
+    // the atom in its block's frame, and the block's transform
     if (j < nt) {
       double* x = atom(x64, c, kind);
-#pragma unroll
-      for (int r = 0; r < 3; ++r) x[r] = o[r] + F[3 * r] * u[0] + F[3 * r + 1] * u[1] + F[3 * r + 2] * u[2];
+      x[0] = u[0]; x[1] = u[1]; x[2] = u[2];
     }
-    // carry the frame past the last transform of these 64 (uniform)
-    const int last = nt - k0 < 64 ? nt - k0 - 1 : 63;
-    double Rl[9], ul[3];
+    if (lane == 63 || j == nt - 1) {
+      double* o = fr + 12 * blk;
 #pragma unroll
-    for (int q = 0; q < 9; ++q) Rl[q] = readlane_d(R[q], last);
-#pragma unroll
-    for (int q = 0; q < 3; ++q) ul[q] = readlane_d(u[q], last);
-    double Fn[9], on[3];
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-#pragma unroll
-      for (int q = 0; q < 3; ++q) Fn[3 * r + q] = F[3 * r] * Rl[q] + F[3 * r + 1] * Rl[3 + q] + F[3 * r + 2] * Rl[6 + q];
-      on[r] = o[r] + F[3 * r] * ul[0] + F[3 * r + 1] * ul[1] + F[3 * r + 2] * ul[2];
+      for (int q = 0; q < 9; ++q) o[q] = R[q];
+      o[9] = u[0]; o[10] = u[1]; o[11] = u[2];
     }
-#pragma unroll
-    for (int q = 0; q < 9; ++q) F[q] = Fn[q];
-    o[0] = on[0]; o[1] = on[1]; o[2] = on[2];
   }
-  wave_sync();
-  // C-beta of residue c from C_c, N_c, CA_c (one residue per lane)
-  for (int c = lane; c < L; c += 64) {
+  __syncthreads();
+  if (wave == 0) {
+    // frame of atom 3 (N_1): from N_0, CA_0, C_0, origin C_0 (uniform over the lanes)
+    double F[9], o[3];
+    double bx = C0[0] - CA0[0], by = C0[1] - CA0[1], bz = C0[2] - CA0[2];
+    const double ib = 1.0 / sqrt(bx * bx + by * by + bz * bz);
+    bx *= ib; by *= ib; bz *= ib;
+    const double ax = CA0[0] - N0[0], ay = CA0[1] - N0[1], az = CA0[2] - N0[2];
+    double nx = ay * bz - az * by, ny = az * bx - ax * bz, nz = ax * by - ay * bx;
+    const double in = 1.0 / sqrt(nx * nx + ny * ny + nz * nz);
+    nx *= in; ny *= in; nz *= in;
+    const double mx = ny * bz - nz * by, my = nz * bx - nx * bz, mz = nx * by - ny * bx;
+    F[0] = bx; F[1] = mx; F[2] = nx;
+    F[3] = by; F[4] = my; F[5] = ny;
+    F[6] = bz; F[7] = mz; F[8] = nz;
+    o[0] = C0[0]; o[1] = C0[1]; o[2] = C0[2];
+    double T[12], Tn[12];   // the block's transform and the next block's, read one ahead
+#pragma unroll
+    for (int q = 0; q < 12; ++q) T[q] = fr[q];
+    for (int blk = 0; blk < nblk; ++blk) {
+      if (blk + 1 < nblk) {
+#pragma unroll
+        for (int q = 0; q < 12; ++q) Tn[q] = fr[12 * (blk + 1) + q];
+      }
+      wave_sync();
+      if (lane == 0) {   // the block's frame takes the transform's place
+        double* w = fr + 12 * blk;
+#pragma unroll
+        for (int q = 0; q < 9; ++q) w[q] = F[q];
+        w[9] = o[0]; w[10] = o[1]; w[11] = o[2];
+      }
+      double Fn[9], on[3];
+#pragma unroll
+      for (int r = 0; r < 3; ++r) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) Fn[3 * r + q] = row3(F + 3 * r, T[q], T[3 + q], T[6 + q]);
+        on[r] = row3(o[r], F + 3 * r, T[9], T[10], T[11]);
+      }
+#pragma unroll
+      for (int q = 0; q < 9; ++q) F[q] = Fn[q];
+      o[0] = on[0]; o[1] = on[1]; o[2] = on[2];
+#pragma unroll
+      for (int q = 0; q < 12; ++q) T[q] = Tn[q];
+    }
+  }
+  __syncthreads();
+  for (int j = threadIdx.x; j < nt; j += blockDim.x) {
+    const double* F = fr + 12 * (j >> 6);
+    double* x = atom(x64, (3 + j) / 3, j % 3);
+    const double u0 = x[0], u1 = x[1], u2 = x[2];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) x[r] = row3(F[9 + r], F + 3 * r, u0, u1, u2);
+  }
+  __syncthreads();
+  // C-beta of residue c from C_c, N_c, CA_c (one residue per thread)
+  for (int c = threadIdx.x; c < L; c += blockDim.x) {
     const double* pN = atom(x64, c, 0);
     const double* pCA = atom(x64, c, 1);
     const double* pC = atom(x64, c, 2);
@@ -134,7 +185,7 @@ static __device__ void nerf_chain(const double* __restrict__ s, int L, double* _
     double* pB = atom(x64, c, 3);
     pB[0] = B[0]; pB[1] = B[1]; pB[2] = B[2];
   }
-  wave_sync();
+  __syncthreads();
 }
 
 }  // namespace amh

@@ -128,8 +128,8 @@ __device__ double value_grad(const double* __restrict__ s, int L, const float* _
   // the C-beta forces F_k accumulate as integers (multiples of 2^-44) in the first
   // three slots of ft[6k .. 6k+5]
   long long* facc = reinterpret_cast<long long*>(ft);
+  nerf_wg(s, L, x64, ft);   // (ft holds the NeRF's scratch: nerf_scratch(L) <= 6 (L + 1))
   for (int k = tid; k < L; k += T) facc[6 * k] = facc[6 * k + 1] = facc[6 * k + 2] = 0;
-  if (wave == 0) nerf_chain(s, L, x64, lane);
   __syncthreads();
   // forces: every pair i < j once, in tiles of 64 rows (block I) by 64 columns (block
   // J >= I) dealt to the wavefronts in turn.  Lane l holds row i = 64 I + l and at step

@@ -73,7 +73,8 @@ struct ConfParams {
 };
 
 size_t sweep_lds_bytes(int G, int L, int W);
-size_t sweep_lds_bytes_local(int G, int L, int W);
+size_t local_lds_bytes(int G, int L, int W);
+size_t global_lds_bytes(int G, int L, int NW);
 
 // Sweep t is global iff it is one of the last n_global sweeps of its cycle of
 // global_every sweeps (Algorithm 1's alternation, localized sweeps first).
@@ -81,14 +82,8 @@ __host__ __device__ inline bool is_global(const SweepParams& P, int64_t t) {
   return P.global_every > 0 && (int)((uint32_t)t % (uint32_t)P.global_every) >= P.global_every - P.n_global;
 }
 
-// kinds of sweep a sweep kernel instance runs
-constexpr int kSweepMixed = 0, kSweepLocal = 1, kSweepGlobal = 2;
-// virtual wavefronts of the float64 energy reduction (fixed, so that the energy
-// does not depend on the launch shape)
-constexpr int kVirtWaves = 8;
-inline size_t conf_lds_bytes(int L, int W) {
-  (void)W;
-  return 8 * (2 * (size_t)L + 12 * (size_t)L + 2 * (size_t)kVirtWaves + 2) + 16 * (size_t)((L + 7) / 8) + 32;
+inline size_t conf_lds_bytes(int L) {
+  return 8 * (14 * (size_t)L + 2 + 12 * ((3 * ((size_t)L - 1) + 63) / 64)) + 16 * (size_t)((L + 7) / 8);
 }
 
 __global__ void ingest_kernel(const float* y, int64_t P, int nb, int stride, float* out,
@@ -98,9 +93,17 @@ __global__ void far_sum_kernel(const float* table, int64_t P, int stride, int nb
 __global__ void philox_kernel(const uint32_t* ctr, int64_t n, uint32_t k0, uint32_t k1, uint32_t* out);
 __global__ void perturb_kernel(double* s, int64_t n_total, int n, uint32_t chain_offset, uint32_t tag,
                                uint32_t k0, uint32_t k1, double amplitude);
-template <int G, int MODE>
-__global__ void sweep_kernel(SweepParams P);
-template <int G, int MODE>
-__global__ void sweep_batch_kernel(const SweepParams* descs, const int2* map);
+__global__ void anchor_kernel(SweepParams P);
+__global__ void anchor_batch_kernel(const SweepParams* descs, const int2* map, int G);
+// localized sweeps: G chains per workgroup, any number of wavefronts (<= 12)
+template <int G>
+__global__ void local_kernel(SweepParams P);
+template <int G>
+__global__ void local_batch_kernel(const SweepParams* descs, const int2* map);
+// global sweeps: G chains per workgroup, NW wavefronts each (1, 2, 4, 8 or 16)
+template <int NW>
+__global__ void global_kernel(SweepParams P, int G);
+template <int NW>
+__global__ void global_batch_kernel(const SweepParams* descs, const int2* map, int G);
 
 }  // namespace amh
