@@ -302,6 +302,39 @@ int global_waves(int G, int W) {
   return nw;
 }
 
+// Launch shape of an automatically shaped context's global sweeps, by the chains each
+// compute unit gets (a unit holds 16 of the kernel's wavefronts, four per SIMD): one chain a
+// workgroup, with as many wavefronts as the unit's chains leave room for.  A proposal of one
+// chain shortens with its wavefronts, the work all chains share grows with them.  One global
+// sweep with 2 / 4 / 8 / 16 wavefronts a chain, us:
+//   L = 100: 128 chains  -   / 559  / 479  / 514;    512  -   / 646  / 588  / 1014;
+//            1024        913 / 749  / 1101 / 1990;   2048 1173 / 1375 / 2150 / 3941
+//   L = 300: 256 chains  -   / 3022 / 2016 / 1964;   512  -   / 3687 / 2635 / 3851;
+//            1024       5318 / 3785 / 4486 / 7262;   2048 7566 / 6443 / 8285 / 14268
+//   L = 800: 64 chains   -   / 18295 / 10417 / 8754
+// (longer chains have more tiles to share: 16 wavefronts from about 300 residues on, and 4
+// instead of 2 where every unit is full).  A context of 4-chain groups that takes at most one
+// group per unit, 1024 chains on 256 units, keeps the shape that amh_info_launches documents
+// for it, two chains and four wavefronts (2 a chain): 5.1 ms a sweep at L = 300.
+int waves_per_chain(int64_t chains, int L, int n_cu) {
+  const int64_t per_cu = (chains + n_cu - 1) / n_cu;
+  return per_cu <= 1 ? (L > 256 ? 16 : 8) : per_cu <= 2 ? 8 : per_cu <= 4 || L > 160 ? 4 : 2;
+}
+
+void global_shape(const amh_config* c, int n_cu, int G, int* G_global, int* W_global) {
+  const bool documented = G == 4 && c->n_chains <= 4 * (int64_t)n_cu;
+  *G_global = documented ? 2 : 1;
+  *W_global = documented ? 4 : waves_per_chain(c->n_chains, c->L, n_cu);
+}
+
+int compute_units() {
+  int dev = 0, n = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1)
+    n = 256;
+  return n;
+}
+
 const void* global_fn(int nw, bool batch) {
   switch (nw) {
     case 1: return batch ? (const void*)amh::global_batch_kernel<1> : (const void*)amh::global_kernel<1>;
@@ -436,11 +469,9 @@ amh_status amh_init(const amh_config* cfg, const float* y_dev, const double* s0_
   if (!out) return sfail(AMH_E_INVAL, "out is NULL");
   *out = nullptr;
   int G = 0, W = 0;
-  int dev = 0, n_cu = 0;
+  int dev = 0;
   const bool have_dev = hipGetDevice(&dev) == hipSuccess;
-  if (!have_dev || hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      n_cu < 1)
-    n_cu = 256;
+  const int n_cu = compute_units();
   amh_status st = validate(cfg, n_cu, &G, &W);
   if (st != AMH_OK) return st;
   if (!y_dev) return sfail(AMH_E_INVAL, "distogram table is NULL");
@@ -456,15 +487,10 @@ amh_status amh_init(const amh_config* cfg, const float* y_dev, const double* s0_
   // localized sweeps run with kLocalWaves wavefronts (consecutive sweeps of a block
   // pipelined over more stages) where their LDS fits
   x->W_local = local_waves(G, cfg->L, W);
-  // global sweeps of an automatically shaped context: two workgroups of two chains
-  // and four wavefronts per CU, so that one workgroup runs while the other waits at a
-  // barrier
+  // global sweeps of an automatically shaped context
   x->G_global = G;
   x->W_global = W;
-  if (cfg->chains_per_group == 0 && cfg->waves_per_group == 0 && G == 4 && W == 8) {
-    x->G_global = 2;
-    x->W_global = 4;
-  }
+  if (cfg->chains_per_group == 0 && cfg->waves_per_group == 0) global_shape(cfg, n_cu, G, &x->G_global, &x->W_global);
   const int L = cfg->L, C = cfg->n_chains, n = 2 * L;
   const int64_t P = (int64_t)L * (L - 1) / 2;
   x->stride = row_stride(cfg->n_bins);
@@ -809,7 +835,7 @@ struct amh_batch {
   int plan = 0;
   struct Launch {
     int G = 1, W = 4;
-    int W_local = 4;   // wavefronts of a localized launch
+    int W_local = 4, W_global = 4;   // wavefronts of a localized and a global launch
     size_t lds_local = 0, lds_global = 0, lds_anchor = 0;   // of the longest member
     int n_wg = 0;
     int2* d_map = nullptr;
@@ -870,16 +896,20 @@ amh_status build_launches(amh_batch* b, int plan) {
     shape_of[i] = (int)(it - shapes.begin());
     if (it == shapes.end()) shapes.emplace_back(G, W);
   }
+  int64_t chains = 0;
+  for (const amh_ctx* x : b->m) chains += x->cfg.n_chains;
   for (size_t s = 0; s < shapes.size(); ++s) {
     amh_batch::Launch l;
     l.G = shapes[s].first;
     l.W = shapes[s].second;
     int longest = 2;
+    bool automatic = true;   // no member has a shape of its caller's choice
     std::vector<std::pair<double, int2>> items;
     for (size_t i = 0; i < b->m.size(); ++i) {
       if (shape_of[i] != (int)s) continue;
       const amh_ctx* x = b->m[i];
       longest = std::max(longest, x->cfg.L);
+      automatic = automatic && x->cfg.chains_per_group == 0 && x->cfg.waves_per_group == 0;
       const int groups = (x->cfg.n_chains + l.G - 1) / l.G;
       for (int g = 0; g < groups; ++g) items.push_back({member_cost(x), make_int2((int)i, g)});
     }
@@ -890,7 +920,9 @@ amh_status build_launches(amh_batch* b, int plan) {
     l.n_wg = (int)map.size();
     l.W_local = local_waves(l.G, longest, l.W);
     l.lds_local = amh::local_lds_bytes(l.G, longest, l.W_local);
-    l.lds_global = amh::global_lds_bytes(l.G, longest, global_waves(l.G, l.W));
+    // (single-chain groups of the contexts' own shapes share the units with all the batch)
+    l.W_global = plan == 0 && l.G == 1 && automatic ? waves_per_chain(chains, longest, compute_units()) : l.W;
+    l.lds_global = amh::global_lds_bytes(l.G, longest, global_waves(l.G, l.W_global));
     l.lds_anchor = amh::conf_lds_bytes(longest);
     hipError_t e = hipMalloc(reinterpret_cast<void**>(&l.d_map), sizeof(int2) * map.size());
     if (e != hipSuccess) return sfail(AMH_E_NOMEM, "hipMalloc: %s", hipGetErrorString(e));
@@ -907,11 +939,11 @@ enum class Step { local, global, anchor };
 amh_status launch_step(const amh_batch* b, Step kind, const amh::SweepParams* descs) {
   for (const auto& l : b->launches) {
     const int2* map = l.d_map;
-    const int G = l.G, nw = global_waves(l.G, l.W);
+    const int G = l.G, nw = global_waves(l.G, l.W_global);
     const amh_status st =
         kind == Step::local ? launch(local_fn(G, true), dim3(l.n_wg), 64 * l.W_local, l.lds_local, b->stream, descs, map)
         : kind == Step::global
-            ? launch(global_fn(nw, true), dim3(l.n_wg), 64 * l.W, l.lds_global, b->stream, descs, map, G)
+            ? launch(global_fn(nw, true), dim3(l.n_wg), 64 * l.W_global, l.lds_global, b->stream, descs, map, G)
             : launch((const void*)amh::anchor_batch_kernel, dim3(l.n_wg, G), kConfThreads, l.lds_anchor, b->stream,
                      descs, map, G);
     if (st != AMH_OK) return st;

@@ -30,10 +30,13 @@
 //     launch shape.
 // Measured against global sweeps that rotated all atoms in LDS (128 bytes a residue), took
 // one tile at a time and wrote the next rotation after the decision, with a third barrier:
-// 1024 chains of 300 residues (2 chains and 4 wavefronts a workgroup) 6.8 -> 4.5 ms a
-// sweep; 128 chains of 300 (8 wavefronts a chain) 2.9 -> 2.0 ms; 64 of 800 27.7 -> 18.9 ms;
-// one of 64 residues 370 -> 242 us.  Most of it is instructions: a tile took 55 issued
-// instructions of one wavefront at a time, now 25.
+// 1024 chains of 300 residues (2 chains and 4 wavefronts a workgroup) 6.8 -> 4.3 ms a
+// sweep; 128 chains of 300 2.9 -> 2.0 ms; 64 of 800 27.7 -> 14 ms; one of 64 residues
+// 370 -> 255 us.  What bounds it is instructions: a wavefront alone issues one in 5 to 8
+// cycles (8 where it needs the one before), and with two a SIMD the vector units are busy
+// 52 % of the time at 1024 chains of 300 residues (1518 instructions a wavefront and
+// proposal).  Four wavefronts a SIMD fit (the helper's state is in LDS and the randoms are
+// drawn in a call, 128 registers instead of 226): 1500 chains of 250 residues 3.3 -> 2.3 ms.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -60,13 +63,22 @@ struct Slot {
 };
 static_assert(sizeof(Slot) == 208, "Slot layout");
 
+// The helper's state of a sweep, in LDS and not in registers: every wavefront is allocated
+// the registers of the busiest point, and these would be live at all of them.
+struct HelperState {
+  double A[12];                    // the accepted moves composed: x -> A x + b (matrix, b)
+  double window[64][3];            // backbone atoms from the window's first residue on
+  Batch batch[64];                 // randoms of 64 consecutive proposals
+};
+
 // LDS of one chain: float64 C-betas (x, y, z arrays), float32 C-betas of the trial
 // conformation (with two more blocks of 8: the fixed rows of the pivot's block, and one
-// that is far from everything), spheres, the slot, partial sums, near-pair queues and
-// tile lists.
+// that is far from everything), spheres, the slots of the current and the next proposal,
+// the helper's state, partial sums, near-pair queues and tile lists.
 __host__ __device__ inline size_t global_chain_bytes(int L, int NW) {
   const size_t nb8 = (size_t)((L + 7) >> 3);
-  return nb8 * (8 * 24 + 8 * 16 + 16) + (16 * 16 + 16) + sizeof(Slot) + 8 * 64 + (8 * (size_t)kQueue + 4 * kList) * NW;
+  return nb8 * (8 * 24 + 8 * 16 + 16) + (16 * 16 + 16) + 2 * sizeof(Slot) + sizeof(HelperState) + 8 * 64 +
+         (8 * (size_t)kQueue + 4 * kList) * NW;
 }
 
 size_t global_lds_bytes(int G, int L, int NW) { return (size_t)G * global_chain_bytes(L, NW); }
@@ -88,15 +100,43 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Parameters in constant memory.  cold() hides where a pointer came from, so that a field
+// read through it is loaded where it is used instead of being kept in scalar registers.
+typedef const __attribute__((address_space(4))) SweepParams CParams;
+__device__ __forceinline__ CParams& cold(CParams& P) {
+  CParams* p = &P;
+  asm volatile("" : "+s"(p));
+  return *p;
+}
+
+// Randoms of the 64 proposals from kn on, one per lane, to LDS.  A call and not inlined:
+// the compiler keeps the constants of log, cos and sincos in registers throughout the
+// loop that contains them (210 registers a lane against 128).
+typedef __attribute__((address_space(3))) Batch LdsBatch;
+__device__ __attribute__((noinline)) void draw_batch(CParams* P, int kn, uint32_t t, int chain, LdsBatch* out) {
+  const int lane = threadIdx.x & 63;
+  const Batch b = fill_batch(*P, kn, t, P->chain_offset + (uint32_t)chain, lane);
+  out[lane].delta = b.delta;
+  out[lane].log_u = b.log_u;
+  out[lane].cd = b.cd;
+  out[lane].sd = b.sd;
+}
+
+// Inverse temperature of sweep t (a call for the same reason).
+__device__ __attribute__((noinline)) double sweep_beta(CParams* P, int64_t t) {
+  double T_t = P->T0;
+  if (P->S > 1) T_t = P->T0 * pow(P->T1 / P->T0, (double)t / (double)(P->S - 1));
+  return 1.0 / T_t;
+}
+
 // The global sweeps [P.t0, P.t0 + P.n_sweeps) of chains group G .. group G + G - 1 of the
 // protein that P describes, NW wavefronts a chain.
 template <int NW>
-__device__ __forceinline__ void global_body(const SweepParams& P, const int group, const int G) {
+__device__ __forceinline__ void global_body(CParams& P, const int group, const int G) {
   extern __shared__ __align__(16) unsigned char lds[];
   // From four wavefronts on the helper leaves the tiles to the others and takes the
-  // transitions; below, the first wavefront takes them.
+  // transitions; below, the wavefronts share both.
   constexpr int TW = NW >= 4 ? NW - 1 : NW;
-  constexpr int kTransWave = NW >= 4 ? NW - 1 : 0;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int gi = wave / NW, wl = wave % NW;
   const int L = P.L, n = 2 * L, nb8 = (L + 7) >> 3, nres8 = 8 * nb8, nchunk = (L + 63) >> 6;
@@ -114,8 +154,9 @@ __device__ __forceinline__ void global_body(const SweepParams& P, const int grou
   double* const xb = reinterpret_cast<double*>(base);                  // [3][nres8]
   float4* const w32 = reinterpret_cast<float4*>(xb + 3 * nres8);       // [nres8 + 16]
   float4* const sph = w32 + nres8 + 16;                                // [nb8 + 1]
-  Slot* const slot = reinterpret_cast<Slot*>(sph + nb8 + 1);
-  double* const part = reinterpret_cast<double*>(slot + 1);            // [64]
+  Slot* const slots = reinterpret_cast<Slot*>(sph + nb8 + 1);          // [2]
+  HelperState* const hs = reinterpret_cast<HelperState*>(slots + 2);
+  double* const part = reinterpret_cast<double*>(hs + 1);              // [64]
   uint2* const qb = reinterpret_cast<uint2*>(part + 64) + kQueue * wl;
   unsigned int* const list = reinterpret_cast<unsigned int*>(reinterpret_cast<uint2*>(part + 64) + kQueue * NW) +
                              kList * wl;
@@ -126,13 +167,16 @@ __device__ __forceinline__ void global_body(const SweepParams& P, const int grou
   double* const gatoms = P.atoms + (size_t)chain * L * 12;
   double* const gs = P.s + (size_t)chain * n;
   const int slot_id = trace_slot(P, chain);
-  const float rcut = __builtin_amdgcn_sqrtf(P.d2far) + 0.05f;
+  const float d2far = P.d2far, rcut = __builtin_amdgcn_sqrtf(d2far) + 0.05f;
+  const float* const ydev = P.ydev;
+  const float* const zrow = P.zrow;
+  const int stride = P.stride;
   // absent columns and the columns before the pivot stand at kFar, absent rows at -kFar
   constexpr float kFar = 1e18f;
   // a step's four tiles take 16 lanes each; a lane has one row and four columns
   const unsigned int lane_pair = (unsigned int)((lane >> 1) & 7) | ((unsigned int)(4 * (lane & 1)) << 11);
   const unsigned int far_tile = (unsigned int)(nres8 + 8);   // (the far block's rows, the first columns)
-  const bool count = P.work != nullptr;
+  const bool count = cold(P).work != nullptr;
   // sums of a wavefront's rows of 16 lanes: rows 0 and 1 the rectangle's, 2 and 3 the
   // transition's; part holds the former in its first half, the latter in its second
   constexpr int kHalf = NW == 16 ? 32 : 16;
@@ -149,82 +193,88 @@ __device__ __forceinline__ void global_body(const SweepParams& P, const int grou
   if (wl == 0 && lane < 16) w32[nres8 + lane] = make_float4(-kFar, -kFar, -kFar, 0.0f);
   if (wl == 0) part[lane] = 0.0;
   for (int64_t t = P.t0; t < t_end; ++t) {
-    double T_t = P.T0;
-    if (P.S > 1) T_t = P.T0 * pow(P.T1 / P.T0, (double)t / (double)(P.S - 1));
-    const double beta = 1.0 / T_t;
-    double rp = 0.0;                                           // D(p) in units of 2^-30
-    double A[9] = {1, 0, 0, 0, 1, 0, 0, 0, 1}, tb[3] = {0, 0, 0};   // helper: accepted moves composed
-    double bx = 0.0, by = 0.0, bz = 0.0;                       // helper: backbone atom of this lane
-    int b0 = 0;                                                // first residue of the window
-    double sv = 0.0;                                           // helper: torsion (k & ~63) + lane
-    Batch bt{};
-    Rot R;                                                     // of the current proposal
-    double log_u = 0.0, delta = 0.0;                           // its randoms
+    const double beta = sweep_beta(&P, t);
+    double rp = 0.0;   // D(p) in units of 2^-30
+    int b0 = 0;        // first residue of the helper's window
+    double sv = 0.0;   // helper: torsion (k & ~63) + lane
     auto load_window = [&](int r0) {
       b0 = r0;
       const int m = 3 * r0 + lane;
       if (lane < kWindowAtoms && m < 3 * L) {
         const double* q = atom(gatoms, m / 3, m % 3);
-        bx = q[0]; by = q[1]; bz = q[2];
+        const double x = q[0], y = q[1], z = q[2];
+        hs->window[lane][0] = x; hs->window[lane][1] = y; hs->window[lane][2] = z;
       }
-    };
-    auto put = [&](double* o, const Rot& r) {
-#pragma unroll
-      for (int q = 0; q < 9; ++q) o[q] = r.r[q];
-      o[9] = r.a[0]; o[10] = r.a[1]; o[11] = r.a[2];
+      wave_sync();
     };
     auto get = [&](const double* o) {
+      Rot R;
 #pragma unroll
       for (int q = 0; q < 9; ++q) R.r[q] = o[q];
       R.a[0] = o[9]; R.a[1] = o[10]; R.a[2] = o[11];
+      return R;
     };
-    // proposal kn for the slot: (tx, ty, tz) hold the window's atoms in the conformation
-    // that proposal kn - 1 starts from; `both`: also the rotation if kn - 1 (R) is accepted
-    auto prepare = [&](int kn, double tx, double ty, double tz, bool both) {
-      if ((kn & 63) == 0) bt = fill_batch(P, kn, (uint32_t)t, (uint32_t)(P.chain_offset + chain), lane);
-      const int m = 3 * ((kn >> 1) - b0) + (kn & 1), kl = kn & 63;
-      D3 a{readlane_d(tx, m), readlane_d(ty, m), readlane_d(tz, m)};
-      const D3 e{readlane_d(tx, m + 1), readlane_d(ty, m + 1), readlane_d(tz, m + 1)};
-      D3 u = unit(a, e);
-      const double cd = readlane_d(bt.cd, kl), sd = readlane_d(bt.sd, kl);
-      Rot q;
-      make_rot_u(a, u, cd, sd, q);
-      if (lane == 0) {
-        put(slot->rot[0], q);
-        slot->log_u = readlane_d(bt.log_u, kl);
-        slot->delta = readlane_d(bt.delta, kl);
+    // slot of proposal kn, from the conformation that proposal kn - 1 starts from; `prev`:
+    // the rotation of proposal kn - 1, or null.  `done`: the residue whose backbone is
+    // final and is written back, or -1.
+    auto prepare = [&](int kn, const double* prev, int done) {
+      if ((kn & 63) == 0 && kn < n) {
+        draw_batch(&P, kn, (uint32_t)t, chain, (LdsBatch*)hs->batch);
+        wave_sync();
       }
-      if (both) {
-        // an accepted rotation turns the next bond rigidly: psi_c moves both atoms of
-        // phi_{c+1}'s, phi_c the far atom of psi_c's (whose near atom CA_c is on its axis)
-        if (!(kn & 1)) a = apply_rot(R, a);
-        u = rot_dir(R, u);
-        make_rot_u(a, u, cd, sd, q);
-        if (lane == 0) put(slot->rot[1], q);
+      // lanes 0 and 1: the axis atoms of kn, lanes 4 to 6 the backbone of `done`; all LDS
+      // reads go out together
+      const int m = 3 * ((kn >> 1) - b0) + (kn & 1), e = 3 * (done - b0);
+      const double* w = hs->window[lane < 4 ? (kn < n ? m + (lane & 1) : 0) : done >= 0 ? e + (lane < 7 ? lane - 4 : 0) : 0];
+      const double* A = hs->A;
+      const double x = w[0], y = w[1], z = w[2];
+      const Batch b = hs->batch[kn & 63];
+      Rot R;
+      if (prev) R = get(prev);
+      const D3 q{A[0] * x + A[1] * y + A[2] * z + A[9], A[3] * x + A[4] * y + A[5] * z + A[10],
+                 A[6] * x + A[7] * y + A[8] * z + A[11]};
+      if (done >= 0 && lane >= 4 && lane < 7) st3(atom(gatoms, done, lane - 4), q);
+      if (kn >= n) return;
+      D3 a{readlane_d(q.x, 0), readlane_d(q.y, 0), readlane_d(q.z, 0)};
+      D3 u = unit(a, D3{readlane_d(q.x, 1), readlane_d(q.y, 1), readlane_d(q.z, 1)});
+      if (prev) {
+        // odd lanes: the outcome where proposal kn - 1 is accepted.  Its rotation turns the
+        // next bond rigidly: psi_c moves both atoms of phi_{c+1}'s, phi_c the far atom of
+        // psi_c's (whose near atom CA_c is on its axis)
+        const D3 a1 = (kn & 1) ? a : apply_rot(R, a), u1 = rot_dir(R, u);
+        if (lane & 1) { a = a1; u = u1; }
       }
+      Rot o;
+      make_rot_u(a, u, b.cd, b.sd, o);
+      Slot& sl = slots[kn & 1];
+      if (lane < 2) {
+#pragma unroll
+        for (int c = 0; c < 9; ++c) sl.rot[lane][c] = o.r[c];
+        sl.rot[lane][9] = a.x; sl.rot[lane][10] = a.y; sl.rot[lane][11] = a.z;
+      }
+      if (lane == 0) { sl.log_u = b.log_u; sl.delta = b.delta; }
     };
     if (helper) {
+      if (lane < 12) hs->A[lane] = lane == 0 || lane == 4 || lane == 8 ? 1.0 : 0.0;
       load_window(0);
-      prepare(0, bx, by, bz, false);
+      prepare(0, nullptr, -1);
       if (lane < n) sv = gs[lane];
     }
     lds_barrier();
     // origin of the float32 work array for this sweep: the middle C-beta
     const D3 org = ldx(L / 2);
-    get(slot->rot[0]);
-    log_u = slot->log_u;
-    delta = slot->delta;
+    int sel = 0;     // the current proposal's rotation is slots[k & 1].rot[sel]
     int pprev = 0;   // pivot of the previous proposal (0: refresh every residue)
     // the previous proposal's outcome, for the helper's bookkeeping
     double dE_prev = 0.0, delta_prev = 0.0;
-    bool acc_prev = false;
-    auto book = [&](int k) {   // of proposal k, by the helper
-      if (acc_prev && lane == (k & 63)) sv = wrap_angle(sv + delta_prev);
+    auto book = [&](int k, bool acc) {   // of proposal k, by the helper
+      if (acc && lane == (k & 63)) sv = wrap_angle(sv + delta_prev);
       if (lane == 0) {
-        if (!isfinite(dE_prev)) atomicOr(P.err, kErrEnergy);
-        if (slot_id >= 0) trace_step(P, slot_id, t, k, dE_prev, delta_prev, acc_prev);
+        CParams& q = cold(P);
+        if (!isfinite(dE_prev)) atomicOr(q.err, kErrEnergy);
+        if (slot_id >= 0) trace_step(q, slot_id, t, k, dE_prev, delta_prev, acc);
       }
-      n_acc += acc_prev;
+      n_acc += acc;
       if ((k & 63) == 63 || k == n - 1) {
         const int m = (k & ~63) + lane;
         if (m < n) gs[m] = sv;
@@ -241,35 +291,47 @@ __device__ __forceinline__ void global_body(const SweepParams& P, const int grou
       // chain's wavefronts.  Residues below the previous pivot hold their committed
       // position already, so only the chunks from that of the previous pivot on.
       {
-        const int c0 = pprev >> 6;
-        for (int ch = c0 + ((wl - c0) & (NW - 1)); ch < nchunk; ch += NW) {
+        const Rot R = get(slots[odd].rot[sel]);
+        auto trial = [&](int ch) {   // this lane's residue of chunk ch
           const int r = 64 * ch + lane;
-          const bool real = r < L;
-          float vx = 0.0f, vy = 0.0f, vz = 0.0f;
-          if (real) {
+          float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+          if (r < L) {
             D3 x = ldx(r);
             if (r >= p) x = apply_rot(R, x);
-            vx = (float)(x.x - org.x); vy = (float)(x.y - org.y); vz = (float)(x.z - org.z);
+            v = make_float4((float)(x.x - org.x), (float)(x.y - org.y), (float)(x.z - org.z), 0.0f);
           }
-          if (ch == p >> 6 && (r >> 3) == p >> 3) {
-            // the pivot's block: its fixed rows have a block of their own
-            const bool row = r < p && real, col = r >= p && real;
-            w32[nres8 + (r & 7)] = row ? make_float4(vx, vy, vz, 0.0f) : make_float4(-kFar, -kFar, -kFar, 0.0f);
-            w32[r] = col ? make_float4(vx, vy, vz, 0.0f) : make_float4(kFar, kFar, kFar, 0.0f);
-          } else if (real) {
-            w32[r] = make_float4(vx, vy, vz, 0.0f);
-          }
+          return v;
+        };
+        auto sphere = [&](int ch, float4 v) {
           // any centre will do (the radius is measured from it); the 0.05 A margin of the
           // tile test covers the 1-ulp hardware square root
+          const bool real = 64 * ch + lane < L;
           const float cnt = sum8(real ? 1.0f : 0.0f), inv = __builtin_amdgcn_rcpf(cnt > 1.0f ? cnt : 1.0f);
-          const float cx = sum8(vx) * inv, cy = sum8(vy) * inv, cz = sum8(vz) * inv;
-          const float rad = max8(real ? __builtin_amdgcn_sqrtf((vx - cx) * (vx - cx) + (vy - cy) * (vy - cy) +
-                                                               (vz - cz) * (vz - cz))
+          const float cx = sum8(v.x) * inv, cy = sum8(v.y) * inv, cz = sum8(v.z) * inv;
+          const float rad = max8(real ? __builtin_amdgcn_sqrtf((v.x - cx) * (v.x - cx) + (v.y - cy) * (v.y - cy) +
+                                                               (v.z - cz) * (v.z - cz))
                                       : 0.0f);
-          if ((r & 7) == 0 && r < nres8) {
-            sph[r >> 3] = make_float4(cx, cy, cz, rad);
-            if ((r >> 3) == p >> 3) sph[nb8] = make_float4(cx, cy, cz, rad);
+          return make_float4(cx, cy, cz, rad);
+        };
+        auto publish = [&](int ch, float4 v, float4 s) {
+          const int r = 64 * ch + lane;
+          const bool real = r < L;
+          if (ch == p >> 6 && (r >> 3) == p >> 3) {
+            // the pivot's block: its fixed rows have a block of their own
+            w32[nres8 + (r & 7)] = r < p && real ? v : make_float4(-kFar, -kFar, -kFar, 0.0f);
+            w32[r] = r >= p && real ? v : make_float4(kFar, kFar, kFar, 0.0f);
+          } else if (real) {
+            w32[r] = v;
           }
+          if ((r & 7) == 0 && r < nres8) {
+            sph[r >> 3] = s;
+            if ((r >> 3) == p >> 3) sph[nb8] = s;
+          }
+        };
+        const int c0 = pprev >> 6;
+        for (int ch = c0 + ((wl - c0) & (NW - 1)); ch < nchunk; ch += NW) {
+          const float4 v = trial(ch);
+          publish(ch, v, sphere(ch, v));
         }
       }
       pprev = p;
@@ -278,81 +340,87 @@ __device__ __forceinline__ void global_body(const SweepParams& P, const int grou
       // that carry D from pivot p - 1 to p (current conformation): residue x against p - 1
       double acc = 0.0, tr = 0.0;
       const bool pairs = p > 0 && p < L;
+      // the transition's pairs of chunk ch: their stencils, and their sum
+      auto trans_load = [&](int ch, float4& q, float& f) {
+        const int x = 64 * ch + lane;
+        const bool use = x < L && x != c;
+        const int i = !use ? 0 : x < c ? x : c, j = !use ? 1 : x < c ? c : x;
+        const float* row = ydev + __umul24((unsigned)pair_row(i, j, L), (unsigned)stride);
+        const float d2 = use ? dist2_64(ldx(x), ldx(c)) : __builtin_inff();
+        q = ld_stencil(stencil_addr(row, zrow, d2, sp, d2far, f));
+      };
+      auto trans_add = [&](int ch, const float4& q, float f) {
+        const double e = fixed30_units(catmull_rom(q.x, q.y, q.z, q.w, f));
+        tr += 64 * ch + lane < c ? -e : e;
+      };
+      // chunks ch, ch + step, ...: two gathers in flight
+      auto transitions = [&](int ch, int step) {
+        for (; ch < nchunk; ch += 2 * step) {
+          float4 q0, q1;
+          float f0, f1;
+          trans_load(ch, q0, f0);
+          const bool two = ch + step < nchunk;
+          if (two) trans_load(ch + step, q1, f1);
+          trans_add(ch, q0, f0);
+          if (two) trans_add(ch + step, q1, f1);
+        }
+      };
       if (helper) {
-        if (k > 0) book(k - 1);
+        if (k > 0) book(k - 1, sel != 0);
         if (!odd && c + 1 > b0 + 20 && c + 1 < L) load_window(c);
-        const double tx = A[0] * bx + A[1] * by + A[2] * bz + tb[0];
-        const double ty = A[3] * bx + A[4] * by + A[5] * bz + tb[1];
-        const double tz = A[6] * bx + A[7] * by + A[8] * bz + tb[2];
-        if (odd && lane >= 3 * (c - b0) && lane < 3 * (c - b0) + 3) {   // residue c's backbone is final
-          double* q = atom(gatoms, c, lane - 3 * (c - b0));
-          q[0] = tx; q[1] = ty; q[2] = tz;
-        }
-        if (k + 1 < n) prepare(k + 1, tx, ty, tz, true);
+        prepare(k + 1, slots[odd].rot[sel], odd ? c : -1);
       }
-      if (odd && wl == kTransWave) {
-        const D3 xc = ldx(c);
-        for (int ch = 0; ch < nchunk; ++ch) {
-          const int x = 64 * ch + lane;
-          const bool use = x < L && x != c;
-          const int i = !use ? 0 : x < c ? x : c, j = !use ? 1 : x < c ? c : x;
-          const float* row = P.ydev + (unsigned)(pair_row(i, j, L) * P.stride);
-          const float d2 = use ? dist2_64(ldx(x), xc) : __builtin_inff();
-          float f;
-          const float4 q = ld_stencil(stencil_addr(row, P.zrow, d2, sp, P.d2far, f));
-          const double e = fixed30_units(catmull_rom(q.x, q.y, q.z, q.w, f));
-          tr += x < c ? -e : e;
-        }
-      }
+      if (odd && (NW < 4 || helper)) transitions(NW < 4 ? wl : 0, NW < 4 ? NW : 1);
       if (pairs && wl < TW) {
         int fill = 0;   // pairs in the wavefront's queue (uniform)
         const int Ip = (p - 1) >> 3, Jp = p >> 3, nJ = nb8 - Jp, ncand = (Ip + 1) * nJ;
         const int row_shift = nres8 - 8 * Jp;   // of the pivot block's rows
-        // evaluate the queue's last nq pairs, one per lane
+        // evaluate the queue's last nq pairs, one per lane: their stencils are gathered
+        // here and evaluated at the next call, so that the gather overlaps the steps between
+        float4 fq = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        float ff = 0.0f;
+        auto finish = [&]() { acc += fixed30_units(catmull_rom(fq.x, fq.y, fq.z, fq.w, ff)); };
         auto flush = [&](int nq) {
+          finish();
           fill -= nq;
+          wk_near += (unsigned int)nq;
           wave_sync();
+          fq = make_float4(0.0f, 0.0f, 0.0f, 0.0f);   // (evaluates to zero)
           if (lane < nq) {
             const uint2 e = qb[fill + lane];
             int bin;
-            float f;
-            spline_pos(__builtin_amdgcn_sqrtf(__uint_as_float(e.y)), sp, bin, f);
+            spline_pos(__builtin_amdgcn_sqrtf(__uint_as_float(e.y)), sp, bin, ff);
             int i = (int)(e.x & 2047u);
             i = i >= nres8 ? i - row_shift : i;
             // row i (2L - i - 1) / 2 + (j - i - 1): all factors below 2^24
             const unsigned row = (__umul24((unsigned)i, (unsigned)(2 * L - 1 - i)) >> 1) + (e.x >> 11) - (unsigned)i - 1u;
-            const float* q = P.ydev + (__umul24(row, (unsigned)P.stride) + (unsigned)bin);
-            acc += fixed30_units(catmull_rom(q[0], q[1], q[2], q[3], f));
+            fq = ld_stencil(ydev + (__umul24(row, (unsigned)stride) + (unsigned)bin));
           }
           wave_sync();
         };
-        // four tiles, the list's entries from `at` on (absent ones: the far tile); pairs
-        // inside the last knot go to the queue (ballot and lane rank give the slot), which
-        // is evaluated 64 pairs at a time
+        // a step of four tiles; pairs inside the last knot go to the queue (ballot and lane
+        // rank give the slot), which is evaluated 64 pairs at a time
         auto step = [&](unsigned int e) {
           e += lane_pair;
           const float4 xi = w32[e & 2047u];
           float4 xj[4];
-          float d2[4];
 #pragma unroll
           for (int u = 0; u < 4; ++u) xj[u] = w32[(e >> 11) + u];
+          // all 16 bytes are asked for: 12-byte LDS reads are slower (5 % of the sweep)
+          asm volatile("" ::"v"(xi.w), "v"(xj[0].w), "v"(xj[1].w), "v"(xj[2].w), "v"(xj[3].w));
+          float d2[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) d2[u] = norm2(xj[u].x - xi.x, xj[u].y - xi.y, xj[u].z - xi.z);
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
-            d2[u] = norm2(xj[u].x - xi.x, xj[u].y - xi.y, xj[u].z - xi.z);
-          }
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const unsigned long long bal = __ballot(d2[u] < P.d2far);
+            const unsigned long long bal = __ballot(d2[u] < d2far);
             const unsigned at = __builtin_amdgcn_mbcnt_hi((unsigned int)(bal >> 32),
                                                           __builtin_amdgcn_mbcnt_lo((unsigned int)bal, (unsigned)fill));
             if (__builtin_amdgcn_inverse_ballot_w64(bal))
               qb[at] = make_uint2(e + ((unsigned int)u << 11), __float_as_uint(d2[u]));
             fill += (int)__popcll(bal);
           }
-          while (fill >= 64) {
-            wk_near += 64;
-            flush(64);
-          }
+          while (fill >= 64) flush(64);
         };
         // The rectangle's tiles: row blocks I up to that of p - 1, column blocks J from
         // that of p.  Candidate tiles are tested one per lane and dealt to the wavefronts
@@ -385,16 +453,17 @@ __device__ __forceinline__ void global_body(const SweepParams& P, const int grou
           ntile += found;
           wk_tiles += (unsigned)found;
           wave_sync();
+          unsigned int ahead = list[(ntile >= 4 ? ntile - 4 : 0) + (lane >> 4)];   // read a step ahead
           while (ntile >= 4) {
             ntile -= 4;
-            step(list[ntile + (lane >> 4)]);
+            const unsigned int e = ahead;
+            ahead = list[(ntile >= 4 ? ntile - 4 : 0) + (lane >> 4)];
+            step(e);
           }
         }
         if (ntile > 0) step((lane >> 4) < ntile ? list[lane >> 4] : far_tile);
-        if (fill > 0) {
-          wk_near += (unsigned int)fill;
-          flush(fill);
-        }
+        if (fill > 0) flush(fill);
+        finish();
       }
       {
         double v = fold_halves(acc, tr);
@@ -407,7 +476,7 @@ __device__ __forceinline__ void global_body(const SweepParams& P, const int grou
       lds_barrier();
       // [D] decision, commit, next rotation
       double pv = part[lane];
-      const double log_u_next = slot->log_u, delta_next = slot->delta;
+      const double log_u = slots[odd].log_u, delta = slots[odd].delta;
       pv += dpp_d<kDppXor1>(pv);
       if constexpr (NW > 1) pv += dpp_d<kDppXor2>(pv);
       if constexpr (NW > 2) {   // (a rotation by 4 brings lane 0 lane 12's sum: both are needed)
@@ -421,11 +490,9 @@ __device__ __forceinline__ void global_body(const SweepParams& P, const int grou
       const bool accepted = __builtin_amdgcn_readfirstlane((dE <= 0.0) || (log_u < -beta * dE) ? 1 : 0) != 0;
       dE_prev = dE;
       delta_prev = delta;
-      acc_prev = accepted;
-      log_u = log_u_next;
-      delta = delta_next;
       if (accepted) {
         rp = pairs ? snew : 0.0;
+        const Rot R = get(slots[odd].rot[sel]);
         // commit: turn the C-betas the torsion moves (float64)
         const int c0 = p >> 6;
         for (int ch = c0 + ((wl - c0) & (NW - 1)); ch < nchunk; ch += NW) {
@@ -435,36 +502,35 @@ __device__ __forceinline__ void global_body(const SweepParams& P, const int grou
             xb[r] = x.x; xb[nres8 + r] = x.y; xb[2 * nres8 + r] = x.z;
           }
         }
-        if (helper) {   // x -> R (x - a) + a after (A, b)
-          double nA[9], nb[3];
+        if (helper) {   // x -> R (x - a) + a after (A, b): column q of (A | b) in lane q
+          const int q = lane & 3;
+          double* A = hs->A;
+          double v0 = A[q < 3 ? q : 9], v1 = A[q < 3 ? 3 + q : 10], v2 = A[q < 3 ? 6 + q : 11];
+          if (q == 3) { v0 -= R.a[0]; v1 -= R.a[1]; v2 -= R.a[2]; }
+          double w[3];
 #pragma unroll
-          for (int r = 0; r < 3; ++r) {
-#pragma unroll
-            for (int q = 0; q < 3; ++q)
-              nA[3 * r + q] = R.r[3 * r] * A[q] + R.r[3 * r + 1] * A[3 + q] + R.r[3 * r + 2] * A[6 + q];
-            nb[r] = R.r[3 * r] * (tb[0] - R.a[0]) + R.r[3 * r + 1] * (tb[1] - R.a[1]) +
-                    R.r[3 * r + 2] * (tb[2] - R.a[2]) + R.a[r];
-          }
-#pragma unroll
-          for (int q = 0; q < 9; ++q) A[q] = nA[q];
-          tb[0] = nb[0]; tb[1] = nb[1]; tb[2] = nb[2];
+          for (int r = 0; r < 3; ++r) w[r] = R.r[3 * r] * v0 + R.r[3 * r + 1] * v1 + R.r[3 * r + 2] * v2;
+          if (q == 3) { w[0] += R.a[0]; w[1] += R.a[1]; w[2] += R.a[2]; }
+          wave_sync();
+          if (lane < 4) { A[q < 3 ? q : 9] = w[0]; A[q < 3 ? 3 + q : 10] = w[1]; A[q < 3 ? 6 + q : 11] = w[2]; }
+          wave_sync();
         }
       }
-      get(slot->rot[accepted ? 1 : 0]);   // (written again only after the next barrier)
+      sel = accepted ? 1 : 0;
     }
-    if (helper) book(n - 1);
-    // the helper reads back what it stored, and the slot
+    if (helper) book(n - 1, sel != 0);
+    // the helper reads back what it stored, and its slots
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
     lds_barrier();
   }
   if (count) {
     if (lane == 0) {
-      atomicAdd(P.work + 0, (unsigned long long)wk_tiles);
-      atomicAdd(P.work + 2, (unsigned long long)wk_near);
+      atomicAdd(cold(P).work + 0, (unsigned long long)wk_tiles);
+      atomicAdd(cold(P).work + 2, (unsigned long long)wk_near);
     }
-    atomicAdd(P.work + 1, (unsigned long long)wk_tests);
+    atomicAdd(cold(P).work + 1, (unsigned long long)wk_tests);
   }
-  if (helper && lane == 0) P.counters[4 * chain + 1] += n_acc;
+  if (helper && lane == 0) cold(P).counters[4 * chain + 1] += n_acc;
   // a wavefront stores the C-betas it has committed
   for (int r = 64 * wl + lane; r < L; r += 64 * NW) {
     double* q = atom(gatoms, r, 3);
@@ -473,18 +539,20 @@ __device__ __forceinline__ void global_body(const SweepParams& P, const int grou
 }
 
 template <int NW>
-__global__ __launch_bounds__(NW == 16 ? 1024 : 512) void global_kernel(SweepParams P, int G) {
-  global_body<NW>(P, blockIdx.x, G);
+__global__ __launch_bounds__(NW == 16 ? 1024 : 512, 4) void global_kernel(SweepParams, int G) {
+  // (the parameters stand at the start of the kernel's argument segment)
+  global_body<NW>(*(CParams*)__builtin_amdgcn_kernarg_segment_ptr(), blockIdx.x, G);
 }
 
 // Several proteins in one launch: workgroup b runs chain group map[b].y of the protein
 // described by descs[map[b].x] (the grid is ordered by decreasing work).
 template <int NW>
-__global__ __launch_bounds__(NW == 16 ? 1024 : 512) void global_batch_kernel(const SweepParams* __restrict__ descs,
+__global__ __launch_bounds__(NW == 16 ? 1024 : 512, 4) void global_batch_kernel(const SweepParams* __restrict__ descs,
                                                                              const int2* __restrict__ map, int G) {
   const int2 wm = map[blockIdx.x];
-  if (descs[wm.x].n_sweeps == 0) return;
-  global_body<NW>(descs[wm.x], wm.y, G);
+  CParams& P = *(CParams*)(uintptr_t)(descs + wm.x);
+  if (P.n_sweeps == 0) return;
+  global_body<NW>(P, wm.y, G);
 }
 
 #define AMH_GLOBAL(NW)                                        \

@@ -15,14 +15,15 @@ struct Batch {  // proposal randoms of 64 consecutive proposals, one per lane
 
 // Proposal width of sweep t: constant, or reduced geometrically from sigma to
 // sigma_end over the schedule (Sec. 2.3 and Sec. 3 reduce it from 10 to 4 degrees).
-__device__ __forceinline__ double sigma_at(const SweepParams& P, int64_t t) {
+template <class Params>   // (SweepParams, in whichever address space)
+__device__ __forceinline__ double sigma_at(Params& P, int64_t t) {
   if (P.sigma_end > 0.0 && P.sigma > 0.0 && P.S > 1)
     return P.sigma * pow(P.sigma_end / P.sigma, (double)t / (double)(P.S - 1));
   return P.sigma;
 }
 
-__device__ __forceinline__ Batch fill_batch(const SweepParams& P, int kb, uint32_t t,
-                                            uint32_t chain, int lane) {
+template <class Params>
+__device__ __forceinline__ Batch fill_batch(Params& P, int kb, uint32_t t, uint32_t chain, int lane) {
   const int k = kb + lane;
   Batch b{0.0, 0.0, 1.0, 0.0};
   if (k < 2 * P.L) {
@@ -32,7 +33,8 @@ __device__ __forceinline__ Batch fill_batch(const SweepParams& P, int kb, uint32
   return b;
 }
 
-__device__ __forceinline__ int trace_slot(const SweepParams& P, int chain) {
+template <class Params>
+__device__ __forceinline__ int trace_slot(Params& P, int chain) {
   int slot = -1;
 #pragma unroll
   for (int m = 0; m < 4; ++m)
@@ -40,7 +42,8 @@ __device__ __forceinline__ int trace_slot(const SweepParams& P, int chain) {
   return slot;
 }
 
-__device__ __forceinline__ void trace_step(const SweepParams& P, int slot, int64_t t, int k,
+template <class Params>
+__device__ __forceinline__ void trace_step(Params& P, int slot, int64_t t, int k,
                                            double dE, double delta, int acc) {
   if (slot < 0) return;
   const int64_t idx = (t - P.trace_t0) * (int64_t)(2 * P.L) + k;
