@@ -70,7 +70,6 @@ __device__ __forceinline__ void st3(double* p, D3 v) { p[0] = v.x; p[1] = v.y; p
 struct Rot {
   double r[9];
   double a[3];
-  double log_u;  // acceptance log-uniform of the proposal the rotation belongs to
 };
 
 // 1/sqrt(x) for x > 0: the hardware estimate refined by two Newton steps (float64).
@@ -153,7 +152,7 @@ struct Spline32 {
 // [0, nb-1], b = min(floor t, nb-2), f = t - b (f = 1 at the far clamp).
 __device__ __forceinline__ void spline_pos(float d, const Spline32& S, int& b, float& f) {
   float t = fmaf(d, S.inv_w, -S.off);
-  t = fminf(fmaxf(t, 0.0f), S.tmax);
+  t = __builtin_amdgcn_fmed3f(t, 0.0f, S.tmax);   // (a NaN gives 0)
   const float bf = fminf(floorf(t), S.tmax - 1.0f);
   f = t - bf;
   b = (int)bf;
@@ -167,43 +166,9 @@ __device__ __forceinline__ float catmull_rom(float y0, float y1, float y2, float
   return fmaf(0.5f * f, fmaf(f, fmaf(f, a3, a2), a1), y1);
 }
 
-__device__ __forceinline__ float spline32(const float* __restrict__ row, float d, const Spline32& S) {
-  int b;
-  float f;
-  spline_pos(d, S, b, f);
-  const float* q = row + b;
-  return catmull_rom(q[0], q[1], q[2], q[3], f);
-}
-
-// Pair energy minus the pair's no-contact value, from a row of the deviation table:
-// exactly zero beyond the last knot (squared distance d2far), where the spline is flat.
-__device__ __forceinline__ float edev32(const float* __restrict__ dev_row, float d2, const Spline32& S,
-                                        float d2far) {
-  return d2 < d2far ? spline32(dev_row, __builtin_amdgcn_sqrtf(d2), S) : 0.0f;
-}
-
-// The same, split in two so that the loads can be issued well before the value is
-// needed: the stencil of a squared distance (zeros beyond the last knot, which
-// evaluate to exactly 0), then its evaluation.
-struct Stencil {
-  float y0, y1, y2, y3, f;
-};
-__device__ __forceinline__ Stencil fetch_dev(const float* __restrict__ dev_row, float d2,
-                                             const Spline32& S, float d2far) {
-  Stencil s{0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-  if (d2 < d2far) {
-    int b;
-    spline_pos(__builtin_amdgcn_sqrtf(d2), S, b, s.f);
-    const float* q = dev_row + b;
-    s.y0 = q[0]; s.y1 = q[1]; s.y2 = q[2]; s.y3 = q[3];
-  }
-  return s;
-}
-__device__ __forceinline__ float eval_dev(const Stencil& s) {
-  return catmull_rom(s.y0, s.y1, s.y2, s.y3, s.f);
-}
-
-// Branch-free form for several pairs in flight: the address of the stencil of a
+// Pair energy minus the pair's no-contact value is the spline of a row of the deviation
+// table, exactly zero beyond the last knot (squared distance d2far), where it is flat.
+// Branch-free for several pairs in flight: the address of the stencil of a
 // squared distance in `dev_row`, or of the same taps of the zero row beyond the last
 // knot (d2 = +inf marks an unused slot), and the fraction.  Loads from the returned
 // address can be issued for all slots before any is used.
@@ -313,14 +278,16 @@ __device__ __forceinline__ float readlane_f(float v, int lane) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }
 
-// Sum over the 64 lanes without LDS traffic: quad butterflies and row rotations by
-// DPP, then the four row totals in a fixed order; every lane gets the same value.
-__device__ __forceinline__ double wave_sum_dpp(double v) {
-  v += dpp_d<kDppXor1>(v);
-  v += dpp_d<kDppXor2>(v);
-  v += dpp_d<kDppRor4>(v);
-  v += dpp_d<kDppRor8>(v);
-  return (readlane_d(v, 0) + readlane_d(v, 16)) + (readlane_d(v, 32) + readlane_d(v, 48));
+typedef unsigned int uint2v __attribute__((ext_vector_type(2)));
+
+// a (lanes 0-31) and b (lanes 32-63) halves added across the wavefront: lane l < 32
+// gets a[l] + a[l + 32], lane l >= 32 gets b[l - 32] + b[l].
+__device__ __forceinline__ double fold_halves(double a, double b) {
+  const uint2v lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b),
+                                                     false, false);
+  const uint2v hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b),
+                                                     false, false);
+  return __hiloint2double((int)hi.x, (int)lo.x) + __hiloint2double((int)hi.y, (int)lo.y);
 }
 
 // Orders LDS traffic between the lanes of one wavefront.

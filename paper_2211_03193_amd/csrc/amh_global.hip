@@ -49,8 +49,6 @@
 
 namespace amh {
 
-typedef unsigned int uint2v __attribute__((ext_vector_type(2)));
-
 constexpr int kQueue = 320;       // near pairs a wavefront's queue holds (63 + four tiles at most)
 constexpr int kList = 68;         // surviving tiles a wavefront's list holds (3 + one per lane at most)
 constexpr int kWindowAtoms = 63;  // backbone atoms in the helper's window (21 residues)
@@ -83,30 +81,11 @@ __host__ __device__ inline size_t global_chain_bytes(int L, int NW) {
 
 size_t global_lds_bytes(int G, int L, int NW) { return (size_t)G * global_chain_bytes(L, NW); }
 
-// acc (lanes 0-31) and tr (lanes 32-63) halves added across the wavefront: lane l < 32
-// gets acc[l] + acc[l + 32], lane l >= 32 gets tr[l - 32] + tr[l].
-__device__ __forceinline__ double fold_halves(double acc, double tr) {
-  const uint2v lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(acc), (unsigned)__double2loint(tr),
-                                                     false, false);
-  const uint2v hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(acc), (unsigned)__double2hiint(tr),
-                                                     false, false);
-  return __hiloint2double((int)hi.x, (int)lo.x) + __hiloint2double((int)hi.y, (int)lo.y);
-}
-
 // Workgroup barrier that orders LDS only: loads and stores of global memory stay in flight.
 __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-// Parameters in constant memory.  cold() hides where a pointer came from, so that a field
-// read through it is loaded where it is used instead of being kept in scalar registers.
-typedef const __attribute__((address_space(4))) SweepParams CParams;
-__device__ __forceinline__ CParams& cold(CParams& P) {
-  CParams* p = &P;
-  asm volatile("" : "+s"(p));
-  return *p;
 }
 
 // Randoms of the 64 proposals from kn on, one per lane, to LDS.  A call and not inlined:
@@ -120,13 +99,6 @@ __device__ __attribute__((noinline)) void draw_batch(CParams* P, int kn, uint32_
   out[lane].log_u = b.log_u;
   out[lane].cd = b.cd;
   out[lane].sd = b.sd;
-}
-
-// Inverse temperature of sweep t (a call for the same reason).
-__device__ __attribute__((noinline)) double sweep_beta(CParams* P, int64_t t) {
-  double T_t = P->T0;
-  if (P->S > 1) T_t = P->T0 * pow(P->T1 / P->T0, (double)t / (double)(P->S - 1));
-  return 1.0 / T_t;
 }
 
 // The global sweeps [P.t0, P.t0 + P.n_sweeps) of chains group G .. group G + G - 1 of the

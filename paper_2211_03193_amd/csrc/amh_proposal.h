@@ -9,6 +9,15 @@
 
 namespace amh {
 
+// Parameters in constant memory.  cold() hides where a pointer came from, so that a field
+// read through it is loaded where it is used instead of being kept in scalar registers.
+typedef const __attribute__((address_space(4))) SweepParams CParams;
+__device__ __forceinline__ CParams& cold(CParams& P) {
+  CParams* p = &P;
+  asm volatile("" : "+s"(p));
+  return *p;
+}
+
 struct Batch {  // proposal randoms of 64 consecutive proposals, one per lane
   double delta, log_u, cd, sd;
 };
@@ -51,6 +60,14 @@ __device__ __forceinline__ void trace_step(Params& P, int slot, int64_t t, int k
   P.tr_dE[slot * P.trace_cap + idx] = dE;
   P.tr_delta[slot * P.trace_cap + idx] = delta;
   P.tr_acc[slot * P.trace_cap + idx] = (uint8_t)acc;
+}
+
+// Inverse temperature of sweep t (a call, not inlined: the compiler would keep the constants
+// of pow in registers throughout the loop over the sweeps).
+[[maybe_unused]] static __device__ __attribute__((noinline)) double sweep_beta(CParams* P, int64_t t) {
+  double T_t = P->T0;
+  if (P->S > 1) T_t = P->T0 * pow(P->T1 / P->T0, (double)t / (double)(P->S - 1));
+  return 1.0 / T_t;
 }
 
 }  // namespace amh
