@@ -170,7 +170,8 @@ amh_status amh_poll(amh_ctx* ctx);
 /* Launch shape chosen for the context (chains and wavefronts per workgroup: the batched
  * launches' own-shape plan; the LDS bytes of the larger of its localized and global
  * launches) and the current sweep index.  amh_sweep runs a range of sweeps as one launch
- * per run of consecutive sweeps of one kind, localized or global, and one per anchor;
+ * per run of consecutive sweeps of one kind, localized or global (two for a localized run
+ * whose last chains fill no whole round of the device), and one per anchor;
  * amh_info_launches gives their shapes. */
 amh_status amh_info(amh_ctx* ctx, int32_t* chains_per_group, int32_t* waves_per_group,
                     int32_t* lds_bytes, int64_t* t);
@@ -178,8 +179,8 @@ amh_status amh_info(amh_ctx* ctx, int32_t* chains_per_group, int32_t* waves_per_
 /* Launch shapes of amh_sweep's localized-sweep launches (consecutive localized sweeps
  * of a workgroup's chains are pipelined over its wavefronts) and global-sweep
  * launches (a workgroup's wavefronts are divided among its chains): chains and
- * wavefronts per workgroup and LDS bytes.  Any output pointer
- * may be NULL. */
+ * wavefronts per workgroup and LDS bytes (of the first of two localized launches).  Any
+ * output pointer may be NULL. */
 amh_status amh_info_launches(amh_ctx* ctx, int32_t* local_chains_per_group, int32_t* local_waves_per_group,
                              int32_t* local_lds_bytes, int32_t* global_chains_per_group,
                              int32_t* global_waves_per_group, int32_t* global_lds_bytes);

@@ -72,8 +72,10 @@ struct amh_ctx {
   int G = 1, W = 4;
   // sum of every table row's no-contact value (far_sum_kernel)
   double vfar = 0.0;
-  // launch shape of the localized-sweep kernel (wavefronts; G chains per workgroup)
-  int W_local = 4;
+  // launches of the localized-sweep kernel: chains [first, first + chains), G per workgroup
+  struct LocalPart { int first = 0, chains = 0, G = 1, W = 4; };
+  LocalPart local[2];
+  int n_local = 0;
   // launch shape of the global-sweep kernel (chains and wavefronts per workgroup)
   int G_global = 1, W_global = 4;
   // trace
@@ -356,6 +358,38 @@ const void* local_fn(int G, bool batch) {
 // Wavefronts of a localized launch: kLocalWaves where their LDS fits, else W.
 int local_waves(int G, int L, int W) { return amh::local_lds_bytes(G, L, kLocalWaves) <= kMaxLds ? kLocalWaves : W; }
 
+// Localized launches of a context.  A unit holds one workgroup of the localized kernel (12 of
+// its wavefronts), and takes 1 : 1.45 : 1.75 as long for one of 1 : 2 : 4 chains (L = 250, 9
+// sweeps: 1.12, 1.60, 1.95 ms; L = 100: 0.59, 0.85, 1.03 ms).  So an automatically shaped
+// context's chains go four to a workgroup (as LDS allows) while that fills every unit, and
+// what is left to the fewest that give each workgroup a unit.  Before, with 1, 2 and 4 chains
+// from 1, 512 and 1024 chains on throughout, L = 250: 476 chains 2.17 ms (two rounds), now
+// 1.60; 768 chains 3.11, now 1.92; 1500 chains 3.82, now 3.57.
+void local_parts(amh_ctx* x, int n_cu) {
+  const amh_config& c = x->cfg;
+  if (c.chains_per_group != 0 || c.waves_per_group != 0) {
+    x->local[0] = {0, c.n_chains, x->G, local_waves(x->G, c.L, x->W)};
+    x->n_local = 1;
+    return;
+  }
+  const auto part = [&](int first, int chains, int G) {
+    x->local[x->n_local++] = {first, chains, G, local_waves(G, c.L, x->W)};
+  };
+  int most = 4;
+  while (most > 1 && amh::local_lds_bytes(most, c.L, kLocalWaves) > kMaxLds) most >>= 1;
+  const int64_t round = (int64_t)most * n_cu;
+  const int whole = (int)(c.n_chains / round * round), rest = c.n_chains - whole;
+  int G = 1;
+  while (G < most && rest > (int64_t)G * n_cu) G *= 2;
+  x->n_local = 0;
+  if (whole > 0) part(0, whole, most);
+  if (rest > 0) part(whole, rest, G);
+}
+
+size_t local_launch_lds(const amh_ctx* x) {
+  return amh::local_lds_bytes(x->local[0].G, x->cfg.L, x->local[0].W);   // (the larger of two)
+}
+
 size_t global_launch_lds(const amh_ctx* x) {
   return amh::global_lds_bytes(x->G_global, x->cfg.L, global_waves(x->G_global, x->W_global));
 }
@@ -484,9 +518,7 @@ amh_status amh_init(const amh_config* cfg, const float* y_dev, const double* s0_
   x->stream = reinterpret_cast<hipStream_t>(stream);
   x->G = G;
   x->W = W;
-  // localized sweeps run with kLocalWaves wavefronts (consecutive sweeps of a block
-  // pipelined over more stages) where their LDS fits
-  x->W_local = local_waves(G, cfg->L, W);
+  local_parts(x, n_cu);
   // global sweeps of an automatically shaped context
   x->G_global = G;
   x->W_global = W;
@@ -571,12 +603,20 @@ amh_status amh_sweep(amh_ctx* x, int64_t n_sweeps) {
     const int64_t e = run_end(P, t, end);
     P.t0 = t;
     P.n_sweeps = e - t;
-    const int G = glob ? x->G_global : x->G, nw = global_waves(x->G_global, x->W_global);
-    const dim3 grid((c.n_chains + G - 1) / G);
-    amh_status st = glob ? launch(global_fn(nw, false), grid, 64 * x->W_global,
-                                  amh::global_lds_bytes(G, c.L, nw), x->stream, P, G)
-                         : launch(local_fn(G, false), grid, 64 * x->W_local,
-                                  amh::local_lds_bytes(G, c.L, x->W_local), x->stream, P);
+    amh_status st = AMH_OK;
+    if (glob) {
+      const int G = x->G_global, nw = global_waves(G, x->W_global);
+      st = launch(global_fn(nw, false), dim3((c.n_chains + G - 1) / G), 64 * x->W_global,
+                  amh::global_lds_bytes(G, c.L, nw), x->stream, P, G);
+    }
+    for (int i = 0; !glob && i < x->n_local && st == AMH_OK; ++i) {
+      const auto& l = x->local[i];
+      P.chain0 = l.first;
+      P.C = l.first + l.chains;
+      st = launch(local_fn(l.G, false), dim3((l.chains + l.G - 1) / l.G), 64 * l.W,
+                  amh::local_lds_bytes(l.G, c.L, l.W), x->stream, P);
+    }
+    P.C = c.n_chains;
     if (st == AMH_OK && e % c.anchor_every == 0) {
       P.t0 = e;
       st = launch((const void*)amh::anchor_kernel, dim3(c.n_chains), kConfThreads,
@@ -735,7 +775,7 @@ amh_status amh_info(amh_ctx* x, int32_t* G, int32_t* W, int32_t* lds, int64_t* t
   if (!x) return sfail(AMH_E_INVAL, "ctx is NULL");
   if (G) *G = x->G;
   if (W) *W = x->W;
-  if (lds) *lds = (int32_t)std::max(amh::local_lds_bytes(x->G, x->cfg.L, x->W_local), global_launch_lds(x));
+  if (lds) *lds = (int32_t)std::max(local_launch_lds(x), global_launch_lds(x));
   if (t) *t = x->t;
   return AMH_OK;
 }
@@ -743,9 +783,9 @@ amh_status amh_info(amh_ctx* x, int32_t* G, int32_t* W, int32_t* lds, int64_t* t
 amh_status amh_info_launches(amh_ctx* x, int32_t* local_G, int32_t* local_W, int32_t* local_lds,
                              int32_t* global_G, int32_t* global_W, int32_t* global_lds) {
   if (!x) return sfail(AMH_E_INVAL, "ctx is NULL");
-  if (local_G) *local_G = x->G;
-  if (local_W) *local_W = x->W_local;
-  if (local_lds) *local_lds = (int32_t)amh::local_lds_bytes(x->G, x->cfg.L, x->W_local);
+  if (local_G) *local_G = x->local[0].G;
+  if (local_W) *local_W = x->local[0].W;
+  if (local_lds) *local_lds = (int32_t)local_launch_lds(x);
   if (global_G) *global_G = x->G_global;
   if (global_W) *global_W = x->W_global;
   if (global_lds) *global_lds = (int32_t)global_launch_lds(x);

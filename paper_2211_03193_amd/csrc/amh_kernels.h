@@ -26,6 +26,7 @@ struct SweepParams {
   int n_cascade, cascade_hw[3];   // extra window half-widths taken in turn with half_window
   double sigma, sigma_end, T0, T1;  // sigma_end > 0: geometric decay of the proposal width
   int64_t S, t0, n_sweeps;
+  int chain0;         // first chain of a localized launch (its chains end before C)
   uint32_t key0, key1, chain_offset;
   int spin_limit;     // polls of a pipelined localized sweep's wait before it gives up
   double target;

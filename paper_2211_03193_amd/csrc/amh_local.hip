@@ -373,8 +373,8 @@ __device__ __forceinline__ void local_sweep(CParams& P, const Lds& S, int nact, 
   }
 }
 
-// The localized sweeps [P.t0, P.t0 + P.n_sweeps) of one workgroup: chains group G ..
-// group G + G - 1 of the protein that P describes.  Every wavefront runs all chains of
+// The localized sweeps [P.t0, P.t0 + P.n_sweeps) of one workgroup: the G chains from
+// P.chain0 + group G on, of the protein that P describes.  Every wavefront runs all chains of
 // the workgroup (64 / G lanes each); the W wavefronts run the consecutive sweeps in turn,
 // pipelined.
 template <int G>
@@ -383,7 +383,7 @@ __device__ __forceinline__ void local_body(CParams& P, const int group) {
   const int tid = threadIdx.x, T = blockDim.x, lane = tid & 63, W = T >> 6;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int L = P.L, n = 2 * L;
-  const int c0 = group * G;
+  const int c0 = P.chain0 + group * G;
   const int nact = P.C - c0 < G ? P.C - c0 : G;
   const Lds S{lds, L, G};
 

@@ -40,3 +40,29 @@ def test_localized_sweeps_at_deal_edges(L, d, cascade):
         if first is None:
             first = out
         assert all(np.array_equal(a, b) for a, b in zip(first, out)), (G, W)
+
+
+@pytest.mark.parametrize("C", [256, 257, 512, 513, 1025, 1281, 1540])
+def test_localized_launches_by_chain_count(C):
+    """Chain counts around the sizes where a context's localized launches change (1, 2 or 4
+    chains a workgroup, a second launch for the chains beyond whole rounds): the last chains
+    against the oracle, and every chain as in single-chain workgroups."""
+    w = sy.Workload(f"launches-C{C}", L=12, n_chains=C, total_sweeps=6, window_d=4, global_every=3, anchor_every=3,
+                    seed=0x3a0 + C, protein_seed=5, noise_seed=6)
+    s_ref, y = gu.protein(w)
+    rng = np.random.Generator(np.random.PCG64(C))
+    s0 = sy._wrap(s_ref[None] + 0.3 * rng.standard_normal((C, 2 * w.L)))
+    out = []
+    for G, W in ((0, 0), (1, 4)):
+        gu.say("localized launches", C, (G, W))
+        ctx = gu.context(w, y, s0=s0, chains_per_group=G, waves_per_group=W)
+        chains = [0, C - 2, C - 1]
+        tr = gu.traced_run(ctx, chains, 6)
+        st = ctx.get_state()
+        ctx.close()
+        for slot, chain in enumerate(chains):
+            rc, rep, s_end = gu.replay_chain(w, y, tr, slot, chain, s0[chain])
+            assert rc == 0 and rep["n_de_fail"] == 0 and rep["n_logic_fail"] == 0, ((G, W), rep)
+            assert np.abs(s_end - st["s"][chain].cpu().numpy()).max() <= 1e-12
+        out.append([st[k].cpu().numpy() for k in ("s", "v", "counters")])
+    assert all(np.array_equal(a, b) for a, b in zip(*out))
