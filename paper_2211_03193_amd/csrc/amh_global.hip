@@ -109,6 +109,7 @@ __device__ __forceinline__ void global_body(CParams& P, const int group, const i
   // From four wavefronts on the helper leaves the tiles to the others and takes the
   // transitions; below, the wavefronts share both.
   constexpr int TW = NW >= 4 ? NW - 1 : NW;
+  constexpr bool kWide = NW >= 8;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int gi = wave / NW, wl = wave % NW;
   const int L = P.L, n = 2 * L, nb8 = (L + 7) >> 3, nres8 = 8 * nb8, nchunk = (L + 63) >> 6;
@@ -338,11 +339,17 @@ __device__ __forceinline__ void global_body(CParams& P, const int group, const i
         }
       };
       if (helper) {
+        if (kWide) __builtin_amdgcn_s_setprio(3);
         if (k > 0) book(k - 1, sel != 0);
         if (!odd && c + 1 > b0 + 20 && c + 1 < L) load_window(c);
         prepare(k + 1, slots[odd].rot[sel], odd ? c : -1);
       }
-      if (odd && (NW < 4 || helper)) transitions(NW < 4 ? wl : 0, NW < 4 ? NW : 1);
+      const bool early = kWide && odd && wl < TW && wl < nchunk;
+      float4 tq;
+      float tf;
+      if (early) trans_load(wl, tq, tf);
+      if (kWide && helper) __builtin_amdgcn_s_setprio(0);
+      if (!kWide && odd && (NW < 4 || helper)) transitions(NW < 4 ? wl : 0, NW < 4 ? NW : 1);
       if (pairs && wl < TW) {
         int fill = 0;   // pairs in the wavefront's queue (uniform)
         const int Ip = (p - 1) >> 3, Jp = p >> 3, nJ = nb8 - Jp, ncand = (Ip + 1) * nJ;
@@ -436,6 +443,10 @@ __device__ __forceinline__ void global_body(CParams& P, const int group, const i
         if (ntile > 0) step((lane >> 4) < ntile ? list[lane >> 4] : far_tile);
         if (fill > 0) flush(fill);
         finish();
+      }
+      if (early) {
+        trans_add(wl, tq, tf);
+        if (wl + TW < nchunk) transitions(wl + TW, TW);
       }
       {
         double v = fold_halves(acc, tr);
