@@ -48,7 +48,6 @@ using amh::sfail;
 
 constexpr size_t kMaxLds = 160 * 1024;  // LDS per workgroup on gfx950
 constexpr int kLocalWaves = 12;          // wavefronts of a localized-only sweep launch
-constexpr int kConfThreads = 256;
 
 int row_stride(int nb) { return ((nb + 2) + 3) & ~3; }   // nb values + 2 ghosts, 16-byte rows
 
@@ -210,12 +209,31 @@ amh::ConfParams conf_base(const amh_ctx* x) {
   return P;
 }
 
+int compute_units() {
+  int dev = 0, n = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1)
+    n = 256;
+  return n;
+}
+
+// Threads of a conformation's workgroup (conformation, energy and anchor kernels): the 16
+// wavefronts that a unit holds are divided among its conformations (128 registers a lane).  With 4 wavefronts always
+// and now: energies of one conformation of 300 residues 71 -> 42 us, 256 of them 100 -> 69,
+// 64 of 600 228 -> 122; 1024 of 300 have 4 still.  Coordinates alone take 4: 16 are no faster
+// (L = 300: 1 conformation 29 against 27 us, 256 34 against 40).
+int conf_threads(int64_t B) {
+  const int64_t per_cu = (B + compute_units() - 1) / compute_units();
+  return per_cu <= 1 ? 1024 : per_cu <= 2 ? 512 : 256;
+}
+
 amh_status launch_conf(const amh::ConfParams& P, int B, hipStream_t st) {
   if (B <= 0) return AMH_OK;
-  const size_t lds = amh::conf_lds_bytes(P.L);
+  const int threads = P.table ? conf_threads(B) : 256;
+  const size_t lds = amh::conf_lds_bytes(P.L, threads, P.table != nullptr);
   HIP_OK(hipFuncSetAttribute((const void*)amh::conf_energy_kernel,
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  hipLaunchKernelGGL(amh::conf_energy_kernel, dim3(B), dim3(kConfThreads), lds, st, P);
+  hipLaunchKernelGGL(amh::conf_energy_kernel, dim3(B), dim3(threads), lds, st, P);
   HIP_OK(hipGetLastError());
   return AMH_OK;
 }
@@ -327,14 +345,6 @@ void global_shape(const amh_config* c, int n_cu, int G, int* G_global, int* W_gl
   const bool documented = G == 4 && c->n_chains <= 4 * (int64_t)n_cu;
   *G_global = documented ? 2 : 1;
   *W_global = documented ? 4 : waves_per_chain(c->n_chains, c->L, n_cu);
-}
-
-int compute_units() {
-  int dev = 0, n = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1)
-    n = 256;
-  return n;
 }
 
 const void* global_fn(int nw, bool batch) {
@@ -619,8 +629,8 @@ amh_status amh_sweep(amh_ctx* x, int64_t n_sweeps) {
     P.C = c.n_chains;
     if (st == AMH_OK && e % c.anchor_every == 0) {
       P.t0 = e;
-      st = launch((const void*)amh::anchor_kernel, dim3(c.n_chains), kConfThreads,
-                  amh::conf_lds_bytes(c.L), x->stream, P);
+      st = launch((const void*)amh::anchor_kernel, dim3(c.n_chains), conf_threads(c.n_chains),
+                  amh::conf_lds_bytes(c.L, conf_threads(c.n_chains), true), x->stream, P);
     }
     if (st != AMH_OK) return st;
     t = e;
@@ -877,6 +887,7 @@ struct amh_batch {
     int G = 1, W = 4;
     int W_local = 4, W_global = 4;   // wavefronts of a localized and a global launch
     size_t lds_local = 0, lds_global = 0, lds_anchor = 0;   // of the longest member
+    int anchor_threads = 256;
     int n_wg = 0;
     int2* d_map = nullptr;
   };
@@ -963,7 +974,8 @@ amh_status build_launches(amh_batch* b, int plan) {
     // (single-chain groups of the contexts' own shapes share the units with all the batch)
     l.W_global = plan == 0 && l.G == 1 && automatic ? waves_per_chain(chains, longest, compute_units()) : l.W;
     l.lds_global = amh::global_lds_bytes(l.G, longest, global_waves(l.G, l.W_global));
-    l.lds_anchor = amh::conf_lds_bytes(longest);
+    l.anchor_threads = conf_threads((int64_t)l.n_wg * l.G);
+    l.lds_anchor = amh::conf_lds_bytes(longest, l.anchor_threads, true);
     hipError_t e = hipMalloc(reinterpret_cast<void**>(&l.d_map), sizeof(int2) * map.size());
     if (e != hipSuccess) return sfail(AMH_E_NOMEM, "hipMalloc: %s", hipGetErrorString(e));
     b->launches.push_back(l);
@@ -984,7 +996,7 @@ amh_status launch_step(const amh_batch* b, Step kind, const amh::SweepParams* de
         kind == Step::local ? launch(local_fn(G, true), dim3(l.n_wg), 64 * l.W_local, l.lds_local, b->stream, descs, map)
         : kind == Step::global
             ? launch(global_fn(nw, true), dim3(l.n_wg), 64 * l.W_global, l.lds_global, b->stream, descs, map, G)
-            : launch((const void*)amh::anchor_batch_kernel, dim3(l.n_wg, G), kConfThreads, l.lds_anchor, b->stream,
+            : launch((const void*)amh::anchor_batch_kernel, dim3(l.n_wg, G), l.anchor_threads, l.lds_anchor, b->stream,
                      descs, map, G);
     if (st != AMH_OK) return st;
   }

@@ -83,8 +83,15 @@ __host__ __device__ inline bool is_global(const SweepParams& P, int64_t t) {
   return P.global_every > 0 && (int)((uint32_t)t % (uint32_t)P.global_every) >= P.global_every - P.n_global;
 }
 
-inline size_t conf_lds_bytes(int L) {
-  return 8 * (14 * (size_t)L + 2 + 12 * ((3 * ((size_t)L - 1) + 63) / 64)) + 16 * (size_t)((L + 7) / 8);
+// A wavefront's pairs inside the last knot, waiting for their energies.
+struct EnergyQueue {
+  double d2[128];           // (63 and a tile at most)
+  unsigned int code[128];   // i << 10 | j
+};
+
+inline size_t conf_lds_bytes(int L, int threads, bool energy) {
+  const size_t frames = 8 * 12 * ((3 * ((size_t)L - 1) + 63) / 64), queues = energy ? sizeof(EnergyQueue) * (threads / 64) : 0;
+  return 8 * (14 * (size_t)L + 2) + 16 * (size_t)((L + 7) / 8) + (frames > queues ? frames : queues);
 }
 
 __global__ void ingest_kernel(const float* y, int64_t P, int nb, int stride, float* out,
