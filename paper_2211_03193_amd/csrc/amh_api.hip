@@ -227,6 +227,30 @@ int conf_threads(int64_t B) {
   return per_cu <= 1 ? 1024 : per_cu <= 2 ? 512 : 256;
 }
 
+// Shape of a conformation's workgroup in the gradient and L-BFGS kernels: threads, of which a
+// unit holds 512 (256 registers a lane: 16 wavefronts of 128 are slower by a quarter), and
+// pairs a wavefront's list holds, as the LDS of the workgroups a unit is to hold allows.  One
+// conformation a unit takes all 512 threads (one of 300 residues 113 us with 256, 86 with 512);
+// more take 256, and from three a unit on 128 where there are three tiles at most (1024 of 64
+// residues 101 us with 256, 62 with 128).  `least`: threads the kernel needs, `extra`: its LDS
+// beyond the gradient's.
+struct GradShape { int threads, cap; size_t lds; };
+
+GradShape grad_shape(int L, int64_t B, int least, size_t extra) {
+  const int n_cu = compute_units();
+  GradShape s{B <= n_cu ? 512 : B > 2 * (int64_t)n_cu && L <= 128 ? 128 : 256, 0, 0};
+  if (s.threads < least) s.threads = least;
+  // (the kernels' own 256 bytes are the barrier votes')
+  const auto bytes = [&](int cap) { return amh::grad_lds_bytes(L, s.threads / 64, cap) + extra + 256; };
+  if (s.threads == 512 && bytes(512) > kMaxLds) s.threads = 256;
+  size_t room = kMaxLds / (512 / s.threads);   // of a workgroup, as many on a unit as it holds
+  if (bytes(256) > room) room = kMaxLds;
+  s.cap = 64;
+  while (s.cap < 2048 && bytes(s.cap + 8) <= room) s.cap += 8;
+  s.lds = bytes(s.cap) - 256;
+  return s;
+}
+
 amh_status launch_conf(const amh::ConfParams& P, int B, hipStream_t st) {
   if (B <= 0) return AMH_OK;
   const int threads = P.table ? conf_threads(B) : 256;
@@ -467,6 +491,7 @@ amh_status minimize_impl(amh_ctx* x, double* s_dev, int32_t B, const amh_lbfgs_o
   P.nb = x->cfg.n_bins;
   P.d_min = x->cfg.d_min;
   P.bin_w = x->cfg.bin_w;
+  P.vfar = x->vfar;
   P.n_iter = o->n_iter;
   P.m = o->m;
   P.nonmonotone = o->nonmonotone;
@@ -486,11 +511,13 @@ amh_status minimize_impl(amh_ctx* x, double* s_dev, int32_t B, const amh_lbfgs_o
     P.v_state = x->v;
     P.s_best = x->s_best;
   }
-  const size_t lds = amh::lbfgs_lds_bytes(L, amh::kGradThreads / 64, o->m, o->nonmonotone);
+  const GradShape shape = grad_shape(L, B, amh::kReduceThreads, amh::lbfgs_lds_bytes(L, 0, 0, o->m, o->nonmonotone) - amh::grad_lds_bytes(L, 0, 0));
+  const size_t lds = shape.lds;
+  P.cap = shape.cap;
   if (lds > kMaxLds) return sfail(AMH_E_INVAL, "L=%d needs %zu bytes of LDS for L-BFGS", L, lds);
   HIP_OK(hipFuncSetAttribute((const void*)amh::lbfgs_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                              (int)lds));
-  hipLaunchKernelGGL(amh::lbfgs_kernel, dim3(B), dim3(amh::kGradThreads), lds, x->stream, P);
+  hipLaunchKernelGGL(amh::lbfgs_kernel, dim3(B), dim3(shape.threads), lds, x->stream, P);
   HIP_OK(hipGetLastError());
   if (!s_dev) {
     amh::ConfParams cp{};
@@ -830,14 +857,17 @@ amh_status amh_grad(amh_ctx* x, const double* s_dev, int32_t B, double* V_out_de
   P.nb = x->cfg.n_bins;
   P.d_min = x->cfg.d_min;
   P.bin_w = x->cfg.bin_w;
+  P.vfar = x->vfar;
   P.V = V_out_dev;
   P.g = g_out_dev;
   P.err = x->err;
-  const size_t lds = amh::grad_lds_bytes(P.L, amh::kGradThreads / 64);
+  const GradShape shape = grad_shape(P.L, B, 64, 0);
+  const size_t lds = shape.lds;
+  P.cap = shape.cap;
   if (lds > kMaxLds) return sfail(AMH_E_INVAL, "L=%d needs %zu bytes of LDS for the gradient", P.L, lds);
   HIP_OK(hipFuncSetAttribute((const void*)amh::grad_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                              (int)lds));
-  hipLaunchKernelGGL(amh::grad_kernel, dim3(B), dim3(amh::kGradThreads), lds, x->stream, P);
+  hipLaunchKernelGGL(amh::grad_kernel, dim3(B), dim3(shape.threads), lds, x->stream, P);
   HIP_OK(hipGetLastError());
   return AMH_OK;
 }

@@ -188,4 +188,26 @@ __device__ inline void nerf_wg(const double* __restrict__ s, int L, double* __re
   __syncthreads();
 }
 
+// Bounding spheres (centroid, radius; float32) of the C-betas of every block of 8 residues,
+// by the workgroup: a block in 8 aligned lanes of one wavefront.  x64 is complete; the
+// caller's next barrier publishes sph.
+__device__ __forceinline__ void block_spheres(const double* __restrict__ x64, int L, float4* __restrict__ sph) {
+  const int nres8 = 8 * ((L + 7) >> 3);
+  for (int r0 = 0; r0 < nres8; r0 += blockDim.x) {
+    const int r = r0 + threadIdx.x;
+    const bool real = r < L;
+    float vx = 0.0f, vy = 0.0f, vz = 0.0f;
+    if (real) {
+      const double* q = atom(x64, r, 3);
+      vx = (float)q[0]; vy = (float)q[1]; vz = (float)q[2];
+    }
+    const float cnt = sum8(real ? 1.0f : 0.0f), inv = __builtin_amdgcn_rcpf(cnt > 1.0f ? cnt : 1.0f);
+    const float cx = sum8(vx) * inv, cy = sum8(vy) * inv, cz = sum8(vz) * inv;
+    const float rad = max8(real ? __builtin_amdgcn_sqrtf((vx - cx) * (vx - cx) + (vy - cy) * (vy - cy) +
+                                                         (vz - cz) * (vz - cz))
+                                : 0.0f);
+    if (r < nres8 && (r & 7) == 0) sph[r >> 3] = make_float4(cx, cy, cz, rad);
+  }
+}
+
 }  // namespace amh

@@ -10,7 +10,7 @@
 namespace amh {
 
 constexpr unsigned int kErrGradEnergy = kErrEnergy;
-constexpr int kGradThreads = 256;
+constexpr int kReduceThreads = 256;   // of a workgroup, that sum over a chain's vectors
 constexpr int kLbfgsMaxHistory = 64;
 constexpr int kLbfgsMaxNonmonotone = 64;
 // Fixed L-BFGS workspace of amh_minimize_noalloc: 8 Mi doubles (64 MiB) per device,
@@ -24,6 +24,8 @@ struct GradParams {
   const float* table;   // padded -ln p rows
   int stride, nb;
   double d_min, bin_w;
+  double vfar;          // sum of every row's no-contact value
+  int cap;              // pairs a wavefront's list holds
   double* V;            // [B] or null
   double* g;            // [B][2L] or null
   unsigned int* err;
@@ -35,6 +37,8 @@ struct LbfgsParams {
   const float* table;
   int stride, nb;
   double d_min, bin_w;
+  double vfar;          // sum of every row's no-contact value
+  int cap;              // pairs a wavefront's list holds
   int n_iter, m, nonmonotone, max_ls;
   double c1, shrink, gtol, step0;
   double* work;         // [B][(5 + 2m) 2L]
@@ -48,11 +52,14 @@ struct LbfgsParams {
   unsigned int* err;
 };
 
-inline size_t grad_lds_bytes(int L, int W) {
-  return 8 * (12 * (size_t)L + 6 * ((size_t)L + 1) + 3 * (size_t)W);
+// A wavefront's list of cap pairs (a multiple of 8, 64 at least).
+__host__ __device__ inline size_t grad_pair_bytes(int cap) { return 10 * (size_t)cap + 640; }
+inline size_t grad_lds_bytes(int L, int W, int cap) {
+  return 8 * (12 * (size_t)L + 6 * ((size_t)L + 1) + 3 * (kReduceThreads / 64)) + 16 * (size_t)((L + 7) / 8) +
+         W * grad_pair_bytes(cap);
 }
-inline size_t lbfgs_lds_bytes(int L, int W, int m, int M) {
-  return grad_lds_bytes(L, W) + 8 * (2 * (size_t)m + (size_t)M);
+inline size_t lbfgs_lds_bytes(int L, int W, int cap, int m, int M) {
+  return grad_lds_bytes(L, W, cap) + 8 * (2 * (size_t)m + (size_t)M);
 }
 inline size_t lbfgs_work_doubles(int L, int m) { return (5 + 2 * (size_t)m) * 2 * (size_t)L; }
 

@@ -34,22 +34,24 @@ namespace amh {
 // t is the position in bin widths from the first centre; the four taps row[b .. b+3]
 // are gathered beforehand at b = stencil_base(t): b = 0 below the first knot (q1 =
 // row[1] is the value there) and for a NaN position, b = nb - 3 at or beyond the last
-// knot (q3 = row[nb]), else the interval of t.
+// knot (q3 = row[nb]), else the interval of t.  The order of the fused operations is
+// written out, here and where the forces are formed: a minimisation multiplies their last
+// bits by 10^2 to 10^3 an iteration.
 __device__ __forceinline__ int stencil_base(double t, int nb) {
   return !(t > 0.0) ? 0 : t >= (double)(nb - 1) ? nb - 3 : (int)floor(t);
 }
 
 __device__ __forceinline__ void spline64_ed(double q0, double q1, double q2, double q3, double t, int b,
                                             int nb, double inv_w, double& E, double& dE) {
-  if (t != t) { E = t; dE = t; return; }   // a NaN distance: V turns NaN
-  if (t <= 0.0) { E = q1; dE = 0.0; return; }
-  if (t >= (double)(nb - 1)) { E = q3; dE = 0.0; return; }
   const double f = t - (double)b;
-  const double a1 = -q0 + q2;
-  const double a2 = 2.0 * q0 - 5.0 * q1 + 4.0 * q2 - q3;
-  const double a3 = -q0 + 3.0 * q1 - 3.0 * q2 + q3;
-  E = 0.5 * (2.0 * q1 + a1 * f + a2 * f * f + a3 * f * f * f);
-  dE = 0.5 * (a1 + 2.0 * a2 * f + 3.0 * a3 * f * f) * inv_w;
+  const double a1 = q2 - q0;
+  const double a2 = fma(4.0, q2, fma(2.0, q0, -5.0 * q1)) - q3;
+  const double a3 = fma(-3.0, q2, fma(3.0, q1, -q0)) + q3;
+  E = 0.5 * fma(f, f * (f * a3), fma(f, f * a2, fma(2.0, q1, f * a1)));
+  dE = 0.5 * fma(f, f * (3.0 * a3), fma(f, a2 + a2, a1)) * inv_w;
+  if (t <= 0.0) { E = q1; dE = 0.0; }
+  if (t >= (double)(nb - 1)) { E = q3; dE = 0.0; }
+  if (t != t) { E = t; dE = t; }   // a NaN distance: V turns NaN
 }
 
 typedef __attribute__((address_space(1))) const float gfloat;
@@ -78,13 +80,15 @@ __device__ __forceinline__ double wave_allmax(double v) {
 }
 
 // Block-wide reductions; every thread returns the same value, summed in a fixed
-// order (per-thread strided partials, the lane butterfly, the waves in order).
-// `red` holds 3 W doubles.  Each call begins and ends with a barrier.
+// order (strided partials of the first kReduceThreads threads, the lane butterfly, their
+// waves in order), which does not depend on the workgroup's size.
+// `red` holds 3 kReduceThreads / 64 doubles.  Each call begins and ends with a barrier.
 __device__ void block_sum3(double& a, double& b, double& c, double* red) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, W = blockDim.x >> 6;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  constexpr int W = kReduceThreads / 64;
   a = wave_allsum(a); b = wave_allsum(b); c = wave_allsum(c);
   __syncthreads();
-  if (lane == 0) { red[3 * wave] = a; red[3 * wave + 1] = b; red[3 * wave + 2] = c; }
+  if (lane == 0 && wave < W) { red[3 * wave] = a; red[3 * wave + 1] = b; red[3 * wave + 2] = c; }
   __syncthreads();
   a = 0.0; b = 0.0; c = 0.0;
   for (int v = 0; v < W; ++v) { a += red[3 * v]; b += red[3 * v + 1]; c += red[3 * v + 2]; }
@@ -94,18 +98,21 @@ __device__ void block_sum3(double& a, double& b, double& c, double* red) {
 __device__ double block_dot(const double* __restrict__ x, const double* __restrict__ y, int n,
                             double* red) {
   double a = 0.0, b = 0.0, c = 0.0;
-  for (int e = threadIdx.x; e < n; e += blockDim.x) a += x[e] * y[e];
+  if (threadIdx.x < kReduceThreads)
+    for (int e = threadIdx.x; e < n; e += kReduceThreads) a += x[e] * y[e];
   block_sum3(a, b, c, red);
   return a;
 }
 
 __device__ double block_maxabs(const double* __restrict__ x, int n, double* red) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, W = blockDim.x >> 6;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  constexpr int W = kReduceThreads / 64;
   double m = 0.0;
-  for (int e = threadIdx.x; e < n; e += blockDim.x) m = fmax(m, fabs(x[e]));
+  if (threadIdx.x < kReduceThreads)
+    for (int e = threadIdx.x; e < n; e += kReduceThreads) m = fmax(m, fabs(x[e]));
   m = wave_allmax(m);
   __syncthreads();
-  if (lane == 0) red[wave] = m;
+  if (lane == 0 && wave < W) red[wave] = m;
   __syncthreads();
   m = 0.0;
   for (int v = 0; v < W; ++v) m = fmax(m, red[v]);
@@ -114,14 +121,36 @@ __device__ double block_maxabs(const double* __restrict__ x, int n, double* red)
 }
 
 // V(s) and, if g != null, dV/ds of one conformation, by the whole workgroup.
-// x64 [12 L] and ft [6 (L + 1)] are LDS scratch, red [3 W] the reduction slots.
+// x64 [12 L], ft [6 (L + 1)], sph [(L + 7) / 8] and pairs [wavefronts] (of grad_pair_bytes(cap)
+// bytes each) are LDS scratch, vacc three LDS words.
 // Returns V in every thread; g is complete after the closing barrier.
+//
+// Only pairs inside the last knot have a force and an energy other than their row's
+// no-contact value (whose sum is vfar): a few in a hundred of a folded chain's.  They are
+// taken by tiles of 64 rows by 64 columns, which the wavefronts draw in turn from the diagonal
+// (where most of them are) outwards, a row and a column of the tile per lane:
+//   * every lane marks its row's pairs inside the last knot (blocks of 8 columns that the
+//     bounding spheres rule out for all lanes are passed over); the ballots are the columns'
+//     marks;
+//   * the pairs are listed row by row and evaluated 64 at a time, dE/dd / d going to LDS;
+//   * every lane adds the forces of its row and then of its column, each in the order
+//     u = (j - i) mod 64.  A list that its LDS does not hold is taken in ranges of u.
+// A tile's forces on a residue and a pair's energy, rounded to multiples of 2^-44, are added as
+// integers (the energy's whole numbers and fractions apart, which bounds neither): the totals do not depend on the order of the tiles or on the launch shape.
+// At 512 conformations of 400 residues (two workgroups of 4 wavefronts a unit, one pair in six
+// inside the last knot) the time goes to the sums (27 %), the marks (20 %), the coordinates
+// (19 %) and the evaluations (17 %): vector instructions, at two wavefronts a SIMD.  Evaluating
+// all pairs, absent and far ones too, one a lane and step: 291 us, now 244; 64 of 800 630, now
+// 291; one of 300 146, now 86; 1024 of 300 355, now 294; 128 of 200 minimised for 20
+// iterations 4.4 ms, now 2.2.
 __device__ double value_grad(const double* __restrict__ s, int L, const float* __restrict__ table,
-                             int stride, int nb, double d_min, double w, double* x64, double* ft,
-                             double* red, double* __restrict__ g) {
-  const int tid = threadIdx.x, T = blockDim.x, lane = tid & 63, wave = tid >> 6, W = T >> 6;
+                             int stride, int nb, double d_min, double w, double vfar, double* x64, double* ft,
+                             float4* sph, unsigned char* pairs, int cap, long long* vacc,
+                             double* __restrict__ g) {
+  const int tid = threadIdx.x, T = blockDim.x, lane = tid & 63, wave = tid >> 6;
   const double dfar = d_min + w * ((double)nb - 0.5), d2far = dfar * dfar;   // the last knot
-  const double inv_w = 1.0 / w;
+  const double inv_w = 1.0 / w, first = d_min + 0.5 * w;
+  const float rcut = (float)dfar + 0.05f;   // (0.05 A: far above float32 rounding)
   // the table through a global-memory pointer, so that its gathers wait only on their own
   // counter and not on the LDS traffic of the same steps
   const gfloat* gtable = (const gfloat*)table;
@@ -130,92 +159,189 @@ __device__ double value_grad(const double* __restrict__ s, int L, const float* _
   long long* facc = reinterpret_cast<long long*>(ft);
   nerf_wg(s, L, x64, ft);   // (ft holds the NeRF's scratch: nerf_scratch(L) <= 6 (L + 1))
   for (int k = tid; k < L; k += T) facc[6 * k] = facc[6 * k + 1] = facc[6 * k + 2] = 0;
+  if (tid == 0) vacc[0] = vacc[1] = vacc[2] = 0;
+  block_spheres(x64, L, sph);
   __syncthreads();
-  // forces: every pair i < j once, in tiles of 64 rows (block I) by 64 columns (block
-  // J >= I) dealt to the wavefronts in turn.  Lane l holds row i = 64 I + l and at step
-  // u the column j = 64 J + ((l + u) & 63); the row's force accumulates in registers,
-  // and each column's travels with it (every step a lane takes the column sum of the
-  // lane above), so that after 64 steps lane l holds column 64 J + l's.  The tile's
-  // row and column sums, rounded to multiples of 2^-44, are added as integers: the
-  // totals do not depend on the order in which the wavefronts add them.
-  double vs = 0.0, vc = 0.0;
-  bool wide = false;   // a tile sum beyond the integer range (or NaN): V is returned NaN
+  bool wide = false;   // an item's sum beyond the integer range (or NaN): V is returned NaN
   const int nb64 = (L + 63) >> 6, ntile = nb64 * (nb64 + 1) / 2;
+  // this wavefront's list of a tile's pairs: dE/dd / d, the marks and list positions of its
+  // rows, and the pairs themselves (row | u << 6)
+  unsigned char* const scratch = pairs + grad_pair_bytes(cap) * wave;
+  double* const qs = reinterpret_cast<double*>(scratch);
+  unsigned long long* const marks = reinterpret_cast<unsigned long long*>(qs + cap);
+  unsigned short* const base = reinterpret_cast<unsigned short*>(marks + 64);
+  unsigned short* const code = base + 64;
+  auto dist2 = [&](double ex, double ey, double ez) { return fma(ez, ez, fma(ex, ex, ey * ey)); };
   // retire every memory operation before the tiles (the NeRF's spill stores among them),
-  // so that inside the tiles only the table gathers are counted and each step waits for
-  // the gather of the pair it evaluates, not for the one issued for the next step
+  // so that inside them only the table gathers are counted and each step waits for
+  // the gather of the pairs it evaluates, not for the one issued for the next step
   __builtin_amdgcn_s_waitcnt(0);
-  for (int tile = wave; tile < ntile; tile += W) {
-    int I = 0, rem = tile;
-    while (rem >= nb64 - I) { rem -= nb64 - I; ++I; }
-    const int J = I + rem, i = 64 * I + lane;
-    const double* xi = atom(x64, i < L ? i : 0, 3);
-    const double ix = xi[0], iy = xi[1], iz = xi[2];
-    double rx = 0.0, ry = 0.0, rz = 0.0, cx = 0.0, cy = 0.0, cz = 0.0;
-    // step u's partner, distance, stencil base and taps; issued one step ahead of its
-    // evaluation so that the table gather overlaps the previous pair (an absent pair
-    // reads row 0, a far one the taps ending at its no-contact value)
-    struct Pair {
-      double ex, ey, ez, inv_d, t;
-      int b;
-      bool real, near;
-      float q0, q1, q2, q3;
-    };
-    auto prep = [&](int u) {
-      Pair a;
-      const int j = 64 * J + ((lane + u) & 63);
-      a.real = i < j && j < L;
-      const double* xj = atom(x64, a.real ? j : 0, 3);
-      a.ex = xj[0] - ix; a.ey = xj[1] - iy; a.ez = xj[2] - iz;
-      const double d2 = a.ex * a.ex + a.ey * a.ey + a.ez * a.ez;
-      a.near = a.real && !(d2 >= d2far);   // a NaN distance is evaluated, so V turns NaN
-      // distance through the hardware reciprocal square root and two Newton steps
-      a.inv_d = a.near && d2 > 0.0 ? rsqrt64(d2) : 0.0;
-      a.t = a.near ? (d2 * a.inv_d - (d_min + 0.5 * w)) * inv_w : (double)nb;
-      a.b = stencil_base(a.t, nb);
-      const gfloat* row = gtable + (size_t)(a.real ? pair_row(i, j, L) : 0) * stride + a.b;
-      a.q0 = row[0]; a.q1 = row[1]; a.q2 = row[2]; a.q3 = row[3];
-      return a;
-    };
-    auto eval = [&](const Pair& a) {
-      if (a.real) {
-        double E = (double)a.q3, dE = 0.0;   // beyond the last knot: the no-contact value
-        if (a.near)
-          spline64_ed((double)a.q0, (double)a.q1, (double)a.q2, (double)a.q3, a.t, a.b, nb, inv_w, E, dE);
-        neumaier_add(vs, vc, E);
-        if (a.inv_d > 0.0) {   // dV/dx_j = +q e, dV/dx_i = -q e
-          const double q = dE * a.inv_d, qx = q * a.ex, qy = q * a.ey, qz = q * a.ez;
-          cx += qx; cy += qy; cz += qz;
-          rx -= qx; ry -= qy; rz -= qz;
+  for (;;) {
+    int tile = 0;
+    if (lane == 0) tile = (int)__hip_atomic_fetch_add((__attribute__((address_space(3))) int*)(vacc + 1), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    tile = __builtin_amdgcn_readfirstlane(tile);
+    if (tile >= ntile) break;
+    int off = 0, I = tile;   // J - I, I
+    while (I >= nb64 - off) { I -= nb64 - off; ++off; }
+    const int i0 = 64 * I, j0 = 64 * (I + off), i = i0 + lane, j = j0 + lane;
+    const double* xp = atom(x64, i < L ? i : 0, 3);
+    // (absent rows stand far off; absent columns and those up to the row drop out of the marks)
+    const double ix = i < L ? xp[0] : 1e300, iy = xp[1], iz = xp[2];
+    const float4 si = sph[i < L ? i >> 3 : 0];
+    unsigned long long near = 0;       // of row i, by column
+    unsigned long long column = 0;     // of column j, by row
+    for (int q = 0; q < 64 && j0 + q < L; q += 8) {
+      const float4 sq = sph[(j0 + q) >> 3];
+      const float dx = si.x - sq.x, dy = si.y - sq.y, dz = si.z - sq.z, lim = rcut + si.w + sq.w;
+      if (__ballot(i < L && !(dx * dx + dy * dy + dz * dz > lim * lim)) == 0) continue;
+      unsigned int mine = 0;
+      unsigned long long rows = 0;
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {   // (NaN distances are evaluated, so V turns NaN)
+        const double* x = atom(x64, j0 + q + r < L ? j0 + q + r : 0, 3);
+        const bool use = !(dist2(x[0] - ix, x[1] - iy, x[2] - iz) >= d2far);
+        const unsigned long long bal = __ballot(use);
+        mine |= use ? 1u << r : 0u;
+        if ((lane & 7) == r) rows = bal;
+      }
+      near |= (unsigned long long)mine << q;
+      if ((lane >> 3) == (q >> 3)) column = rows;
+    }
+    if (j0 + 64 > L) near &= (1ull << (L - j0)) - 1;
+    if (j >= L) column = 0;
+    if (off == 0) {
+      near &= ~1ull << lane;
+      column &= (1ull << lane) - 1;
+    }
+    if (__ballot(near != 0) == 0) continue;
+    // the marks by the step u
+    const unsigned long long rev = __brevll(column);
+    const int by = (lane + 1) & 63;
+    const unsigned long long row = near >> lane | near << ((64 - lane) & 63), col = rev << by | rev >> ((64 - by) & 63);
+    xp = atom(x64, j < L ? j : 0, 3);
+    const double jx = xp[0], jy = xp[1], jz = xp[2];
+    double rx = 0.0, ry = 0.0, rz = 0.0, cx = 0.0, cy = 0.0, cz = 0.0, whole = 0.0, part = 0.0;
+    for (int u0 = 0, width = 64; u0 < 64; u0 += width, width = 64 - u0) {
+      unsigned long long range, m;   // steps [u0, u0 + width), as many as the list holds
+      int at, count;                 // the row's first pair in the list, all pairs
+      for (;;) {
+        range = (width == 64 ? ~0ull : (1ull << width) - 1) << u0;
+        m = row & range;
+        const int n = (int)__popcll(m);
+        at = count = 0;
+#pragma unroll
+        for (int b = 0; b < 7; ++b) {
+          const unsigned long long bal = __ballot((n >> b) & 1);
+          at += (int)__builtin_amdgcn_mbcnt_hi((unsigned)(bal >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0)) << b;
+          count += (int)__popcll(bal) << b;
+        }
+        if (count <= cap) break;
+        const int fit = width * cap / count;   // (one step has 64 pairs at most)
+        width = fit < 1 ? 1 : fit;
+      }
+      if (count == 0) continue;
+      marks[lane] = m;
+      base[lane] = (unsigned short)at;
+      {
+        int k = at;
+        for (unsigned long long left = m; left != 0; left &= left - 1)
+          code[k++] = (unsigned short)(lane | (__builtin_ctzll(left) << 6));
+      }
+      wave_sync();
+      // 64 pairs: ends, distance, stencil base and taps, issued one step ahead of their
+      // evaluation so that the table gather overlaps the previous step
+      struct Pair {
+        double inv_d, t;
+        int b;
+        bool use;
+        float q0, q1, q2, q3, qn;
+      };
+      auto prep = [&](int k) {
+        Pair a;
+        a.use = k < count;
+        const int cd = a.use ? code[k] : 0;
+        const int pi = i0 + (cd & 63), pj = a.use ? j0 + (((cd & 63) + (cd >> 6)) & 63) : 0;
+        const double* xa = atom(x64, pi, 3);
+        const double* xb = atom(x64, pj, 3);
+        const double d2 = dist2(xb[0] - xa[0], xb[1] - xa[1], xb[2] - xa[2]);
+        // distance through the hardware reciprocal square root and two Newton steps
+        a.inv_d = a.use && d2 > 0.0 ? rsqrt64(d2) : 0.0;
+        a.t = fma(d2, a.inv_d, -first) * inv_w;
+        a.b = stencil_base(a.t, nb);
+        const gfloat* r = gtable + (size_t)(a.use ? pair_row(pi, pj, L) : 0) * stride;
+        a.q0 = r[a.b]; a.q1 = r[a.b + 1]; a.q2 = r[a.b + 2]; a.q3 = r[a.b + 3];
+        a.qn = r[nb];
+        return a;
+      };
+      auto eval = [&](const Pair& a, int k) {
+        if (!a.use) return;
+        double E, dE;
+        spline64_ed((double)a.q0, (double)a.q1, (double)a.q2, (double)a.q3, a.t, a.b, nb, inv_w, E, dE);
+        const double e = E - (double)a.qn, n = rint(e);   // (sums of integers below 2^53)
+        whole += n;
+        part += rint((e - n) * 0x1p44);
+        qs[k] = a.inv_d > 0.0 ? dE * a.inv_d : 0.0;
+      };
+      // two records in turn, so that no gathered value is copied
+      Pair A = prep(lane);
+      for (int k = lane;; k += 128) {
+        const Pair B = prep(k + 64);
+        eval(A, k);
+        if (k - lane + 64 >= count) break;
+        A = prep(k + 128);
+        eval(B, k + 64);
+        if (k - lane + 128 >= count) break;
+      }
+      wave_sync();
+      // dV/dx_j = +q (x_j - x_i), dV/dx_i = -q (x_j - x_i)
+      // (two a step, so that their reads overlap; an absent one adds zero)
+      {
+        int k = at;
+        for (unsigned long long left = m; left != 0;) {
+          const int ua = __builtin_ctzll(left);
+          left &= left - 1;
+          const bool two = left != 0;
+          const int ub = two ? __builtin_ctzll(left) : ua;
+          left &= left - 1;
+          const double* xa = atom(x64, j0 + ((lane + ua) & 63), 3);
+          const double* xb = atom(x64, j0 + ((lane + ub) & 63), 3);
+          const double qa = -qs[k], qb = two ? -qs[k + 1] : 0.0;
+          rx = fma(xa[0] - ix, qa, rx); ry = fma(xa[1] - iy, qa, ry); rz = fma(xa[2] - iz, qa, rz);
+          rx = fma(xb[0] - ix, qb, rx); ry = fma(xb[1] - iy, qb, ry); rz = fma(xb[2] - iz, qb, rz);
+          k += 2;
         }
       }
-      const int up = (lane + 1) & 63;
-      cx = __shfl(cx, up, 64); cy = __shfl(cy, up, 64); cz = __shfl(cz, up, 64);
-    };
-    // two records in turn, so that no gathered value is copied (u = 64 prepares a pair
-    // that is not evaluated)
-    Pair A = prep(0);
-    for (int u = 0; u < 64; u += 2) {
-      const Pair B = prep(u + 1);
-      eval(A);
-      A = prep(u + 2);
-      eval(B);
+      for (unsigned long long left = col & range; left != 0;) {
+        const int ua = __builtin_ctzll(left), ra = (lane - ua) & 63;
+        left &= left - 1;
+        const bool two = left != 0;
+        const int ub = two ? __builtin_ctzll(left) : ua, rb = (lane - ub) & 63;
+        left &= left - 1;
+        const double* xa = atom(x64, i0 + ra, 3);
+        const double* xb = atom(x64, i0 + rb, 3);
+        const double qa = qs[base[ra] + (int)__popcll(marks[ra] & ((1ull << ua) - 1))];
+        const double qv = qs[base[rb] + (int)__popcll(marks[rb] & ((1ull << ub) - 1))], qb = two ? qv : 0.0;
+        cx = fma(jx - xa[0], qa, cx); cy = fma(jy - xa[1], qa, cy); cz = fma(jz - xa[2], qa, cz);
+        cx = fma(jx - xb[0], qb, cx); cy = fma(jy - xb[1], qb, cy); cz = fma(jz - xb[2], qb, cz);
+      }
+      wave_sync();
     }
     const double lim = 0x1p13;   // |tile sum| < 2^13: a residue's total stays below 2^19
     wide = wide || !(fabs(rx) < lim && fabs(ry) < lim && fabs(rz) < lim && fabs(cx) < lim &&
-                     fabs(cy) < lim && fabs(cz) < lim);
+                     fabs(cy) < lim && fabs(cz) < lim && fabs(whole) < 0x1p53);
     if (!wide) {
-      if (i < L) {
+      if (row != 0) {
         lds_add(facc + 6 * i, fixed44(rx));
         lds_add(facc + 6 * i + 1, fixed44(ry));
         lds_add(facc + 6 * i + 2, fixed44(rz));
       }
-      const int jc = 64 * J + lane;
-      if (jc < L) {
-        lds_add(facc + 6 * jc, fixed44(cx));
-        lds_add(facc + 6 * jc + 1, fixed44(cy));
-        lds_add(facc + 6 * jc + 2, fixed44(cz));
+      if (col != 0) {
+        lds_add(facc + 6 * j, fixed44(cx));
+        lds_add(facc + 6 * j + 1, fixed44(cy));
+        lds_add(facc + 6 * j + 2, fixed44(cz));
       }
+      lds_add(vacc, (long long)whole);
+      lds_add(vacc + 2, (long long)part);
     }
   }
   __syncthreads();
@@ -231,16 +357,36 @@ __device__ double value_grad(const double* __restrict__ s, int L, const float* _
     o[4] = kz * fx - kx * fz;
     o[5] = kx * fy - ky * fx;
   }
-  if (wide) vs = __builtin_nan("");
-  double V = vs + vc, z1 = 0.0, z2 = 0.0;
-  block_sum3(V, z1, z2, red);   // also the barrier that publishes ft
-  // suffix sums S_p, T_p (six components, one lane each, in chain order)
+  wide = __syncthreads_or(wide);   // (also the barrier that publishes ft)
+  const double V = wide ? __builtin_nan("") : vfar + ((double)vacc[0] + (double)vacc[2] * 0x1p-44);
+  // suffix sums S_p, T_p (six components, one lane each, in chain order; eight residues
+  // are read ahead of the additions, which alone are a chain)
   if (wave == 0 && lane < 6) {
     double acc = 0.0;
-    ft[6 * L + lane] = 0.0;
-    for (int j = L - 1; j >= 0; --j) {
-      acc += ft[6 * j + lane];
-      ft[6 * j + lane] = acc;
+    double* f = ft + lane;
+    f[6 * L] = 0.0;
+    int j = L;
+    double v[8], next[8];
+    auto read = [&](double* o, int k) {   // residues k + 7 down to k
+      const double* p = f + 6 * (k > 0 ? k : 0);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) o[q] = p[42 - 6 * q];
+    };
+    if (j >= 8) read(next, j - 8);
+    for (; j >= 8; j -= 8) {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v[q] = next[q];
+      read(next, j - 16);
+      double* const p = f + 6 * (j - 8);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        acc += v[q];
+        p[42 - 6 * q] = acc;
+      }
+    }
+    for (; j > 0; --j) {
+      acc += f[6 * (j - 1)];
+      f[6 * (j - 1)] = acc;
     }
   }
   __syncthreads();
@@ -269,19 +415,21 @@ __device__ double value_grad(const double* __restrict__ s, int L, const float* _
 
 // ---------------------------------------------------------------------------
 // Both kernels are held to two wavefronts per SIMD (at most 256 registers a lane).
-// Left free, the compiler gives the parallel NeRF scan, which one wavefront runs once
-// per evaluation, 271 registers and every kernel one wavefront per SIMD; under the
-// cap it spills a little inside that scan, and two workgroups share each CU (the
-// most their LDS allows at 400 residues), hiding the force pass's table gathers.
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) grad_kernel(GradParams P) {
+// Left free, the compiler gives the NeRF scan 271 registers and every kernel one wavefront
+// per SIMD; under the cap it spills a little inside that scan, and two workgroups of four
+// wavefronts share each CU (the most their LDS allows at 400 residues).
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) grad_kernel(GradParams P) {
   extern __shared__ __align__(16) unsigned char lds[];
   const int L = P.L;
   double* x64 = reinterpret_cast<double*>(lds);
   double* ft = x64 + 12 * L;
-  double* red = ft + 6 * (L + 1);
+  float4* sph = reinterpret_cast<float4*>(ft + 6 * (L + 1));
+  unsigned char* pairs = reinterpret_cast<unsigned char*>(sph + ((L + 7) >> 3));
+  double* red = reinterpret_cast<double*>(pairs + (blockDim.x >> 6) * grad_pair_bytes(P.cap));
   const int b = blockIdx.x;
   const double V = value_grad(P.s + (size_t)b * 2 * L, L, P.table, P.stride, P.nb, P.d_min,
-                              P.bin_w, x64, ft, red, P.g ? P.g + (size_t)b * 2 * L : nullptr);
+                              P.bin_w, P.vfar, x64, ft, sph, pairs, P.cap, reinterpret_cast<long long*>(red),
+                              P.g ? P.g + (size_t)b * 2 * L : nullptr);
   if (threadIdx.x == 0) {
     if (!isfinite(V)) atomicOr(P.err, kErrGradEnergy);
     if (P.V) P.V[b] = V;
@@ -291,14 +439,16 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) g
 // ---------------------------------------------------------------------------
 // One chain's L-BFGS.  Workspace rows (n = 2L doubles each): x, g, d, xn, gn, then
 // the curvature pairs S[m], Y[m] kept as a ring (oldest at `head`).
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) lbfgs_kernel(LbfgsParams P) {
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) lbfgs_kernel(LbfgsParams P) {
   extern __shared__ __align__(16) unsigned char lds[];
-  const int L = P.L, n = 2 * L, tid = threadIdx.x, T = blockDim.x, W = T >> 6;
+  const int L = P.L, n = 2 * L, tid = threadIdx.x, T = blockDim.x;
   const int m = P.m, M = P.nonmonotone;
   double* x64 = reinterpret_cast<double*>(lds);
   double* ft = x64 + 12 * L;
-  double* red = ft + 6 * (L + 1);
-  double* rho = red + 3 * W;     // [m]
+  float4* sph = reinterpret_cast<float4*>(ft + 6 * (L + 1));
+  unsigned char* pairs = reinterpret_cast<unsigned char*>(sph + ((L + 7) >> 3));
+  double* red = reinterpret_cast<double*>(pairs + (blockDim.x >> 6) * grad_pair_bytes(P.cap));
+  double* rho = red + 3 * kReduceThreads / 64;   // [m]
   double* alp = rho + m;         // [m]
   double* fh = alp + m;          // [M]
   const int b = blockIdx.x;
@@ -319,7 +469,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) l
     if (xtr) xtr[e] = sb[e];
   }
   __syncthreads();
-  double f = value_grad(x, L, P.table, P.stride, P.nb, P.d_min, P.bin_w, x64, ft, red, g);
+  double f = value_grad(x, L, P.table, P.stride, P.nb, P.d_min, P.bin_w, P.vfar, x64, ft, sph, pairs, P.cap, reinterpret_cast<long long*>(red), g);
   if (trace && tid == 0) trace[0] = f;
   if (tid == 0) fh[0] = f;
   int k = 0, head = 0, nf = 1, it = 0, status = 1;
@@ -331,7 +481,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) l
     if (k > 0) {
       const int r = (head + k - 1) % m;
       double sy = 0.0, yy = 0.0, z = 0.0;
-      for (int e = tid; e < n; e += T) {
+      for (int e = tid; e < n && tid < kReduceThreads; e += kReduceThreads) {
         const double ye = Yh[(size_t)r * n + e];
         sy += Sh[(size_t)r * n + e] * ye;
         yy += ye * ye;
@@ -380,14 +530,14 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) l
     for (int ls = 0; ls < P.max_ls; ++ls) {
       for (int e = tid; e < n; e += T) xn[e] = x[e] + alpha * d[e];
       __syncthreads();
-      fnew = value_grad(xn, L, P.table, P.stride, P.nb, P.d_min, P.bin_w, x64, ft, red, gn);
+      fnew = value_grad(xn, L, P.table, P.stride, P.nb, P.d_min, P.bin_w, P.vfar, x64, ft, sph, pairs, P.cap, reinterpret_cast<long long*>(red), gn);
       if (fnew <= fref + P.c1 * alpha * gd) { ok = true; break; }
       alpha *= P.shrink;
     }
     if (!ok) { status = 2; break; }
     // curvature pair, kept only when s.y is clearly positive
     double sy = 0.0, ss = 0.0, yy = 0.0;
-    for (int e = tid; e < n; e += T) {
+    for (int e = tid; e < n && tid < kReduceThreads; e += kReduceThreads) {
       const double se = xn[e] - x[e], ye = gn[e] - g[e];
       sy += se * ye; ss += se * se; yy += ye * ye;
     }

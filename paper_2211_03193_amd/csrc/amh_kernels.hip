@@ -114,24 +114,9 @@ __device__ double energy64(const float* __restrict__ table, int stride, int nb, 
   const double dfar = d_min + w * ((double)nb - 0.5), d2far = dfar * dfar;   // the last knot
   const double inv_w = 1.0 / w;
   const float rcut = (float)dfar + 0.05f;
-  const int nb8 = (L + 7) >> 3, nres8 = 8 * nb8;
+  const int nb8 = (L + 7) >> 3;
   if (tid == 0) *acc = 0;
-  // spheres: the 8 residues of a block in 8 aligned lanes of one wavefront
-  for (int e0 = 0; e0 < nres8; e0 += T) {
-    const int r = e0 + tid;
-    const bool real = r < L;
-    float vx = 0.0f, vy = 0.0f, vz = 0.0f;
-    if (real) {
-      const double* q = atom(x, r, 3);
-      vx = (float)q[0]; vy = (float)q[1]; vz = (float)q[2];
-    }
-    const float cnt = sum8(real ? 1.0f : 0.0f), inv = __builtin_amdgcn_rcpf(cnt > 1.0f ? cnt : 1.0f);
-    const float cx = sum8(vx) * inv, cy = sum8(vy) * inv, cz = sum8(vz) * inv;
-    const float rad = max8(real ? __builtin_amdgcn_sqrtf((vx - cx) * (vx - cx) + (vy - cy) * (vy - cy) +
-                                                         (vz - cz) * (vz - cz))
-                                : 0.0f);
-    if (r < nres8 && (r & 7) == 0) sph[r >> 3] = make_float4(cx, cy, cz, rad);
-  }
+  block_spheres(x, L, sph);
   __syncthreads();
   long long part = 0;
   int fill = 0;   // pairs in the wavefront's queue (uniform)
