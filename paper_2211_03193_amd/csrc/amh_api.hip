@@ -56,6 +56,7 @@ int row_stride(int nb) { return ((nb + 2) + 3) & ~3; }   // nb values + 2 ghosts
 struct amh_ctx {
   amh_config cfg{};
   hipStream_t stream = nullptr;
+  unsigned char* slab = nullptr;   // the arrays below, in one allocation
   float* table = nullptr;
   float* ydev = nullptr;
   int stride = 0;
@@ -183,8 +184,7 @@ amh_status validate(const amh_config* c, int n_cu, int* G, int* W) {
 
 void free_ctx(amh_ctx* x) {
   if (!x) return;
-  (void)hipFree(x->table); (void)hipFree(x->ydev); (void)hipFree(x->s); (void)hipFree(x->s_best); (void)hipFree(x->atoms);
-  (void)hipFree(x->v); (void)hipFree(x->counters); (void)hipFree(x->err);
+  (void)hipFree(x->slab);
   (void)hipFree(x->work);
   delete x;
 }
@@ -218,8 +218,8 @@ int compute_units() {
 }
 
 // Threads of a conformation's workgroup (conformation, energy and anchor kernels): the 16
-// wavefronts that a unit holds are divided among its conformations (128 registers a lane).  With 4 wavefronts always
-// and now: energies of one conformation of 300 residues 71 -> 42 us, 256 of them 100 -> 69,
+// wavefronts that a unit holds are divided among its conformations (128 registers a lane).
+// With 4 wavefronts always and now: energies of one conformation of 300 residues 71 -> 42 us, 256 of them 100 -> 69,
 // 64 of 600 228 -> 122; 1024 of 300 have 4 still.  Coordinates alone take 4: 16 are no faster
 // (L = 300: 1 conformation 29 against 27 us, 256 34 against 40).
 int conf_threads(int64_t B) {
@@ -351,15 +351,16 @@ int global_waves(int G, int W) {
 // workgroup, with as many wavefronts as the unit's chains leave room for.  A proposal of one
 // chain shortens with its wavefronts, the work all chains share grows with them.  One global
 // sweep with 2 / 4 / 8 / 16 wavefronts a chain, us:
-//   L = 100: 128 chains  -   / 559  / 479  / 514;    512  -   / 646  / 588  / 1014;
-//            1024        913 / 749  / 1101 / 1990;   2048 1173 / 1375 / 2150 / 3941
-//   L = 300: 256 chains  -   / 3022 / 2016 / 1964;   512  -   / 3687 / 2635 / 3851;
-//            1024       5318 / 3785 / 4486 / 7262;   2048 7566 / 6443 / 8285 / 14268
-//   L = 800: 64 chains   -   / 18295 / 10417 / 8754
-// (longer chains have more tiles to share: 16 wavefronts from about 300 residues on, and 4
-// instead of 2 where every unit is full).  A context of 4-chain groups that takes at most one
+//   L = 100: 128 chains  -   / 551  / 458  / -;    512  -   / 629  / 589  / -;
+//            1024        887 / 748  / 1088 / -;   2048 1131 / 1389 / 2070 / -
+//   L = 300: 256 chains  -   / 2964 / 1887 / 1747;  512  -   / 3571 / 2521 / -;
+//            1024       5127 / 3654 / 4049 / -;   2048 7232 / 6192 / 7536 / -
+//   L = 800: 64 chains   -   / 12313 / 7321 / 5801
+// (16 for longer chains, which have more tiles to share, and where a unit has one chain; at
+// 100 residues and 512 chains on they took 1.7 times as long as 8.  4 instead of 2 for longer
+// chains where every unit is full).  A context of 4-chain groups that takes at most one
 // group per unit, 1024 chains on 256 units, keeps the shape that amh_info_launches documents
-// for it, two chains and four wavefronts (2 a chain): 5.1 ms a sweep at L = 300.
+// for it, two chains and four wavefronts (2 a chain): 5.0 ms a sweep at L = 300.
 int waves_per_chain(int64_t chains, int L, int n_cu) {
   const int64_t per_cu = (chains + n_cu - 1) / n_cu;
   return per_cu <= 1 ? (L > 256 ? 16 : 8) : per_cu <= 2 ? 8 : per_cu <= 4 || L > 160 ? 4 : 2;
@@ -511,7 +512,8 @@ amh_status minimize_impl(amh_ctx* x, double* s_dev, int32_t B, const amh_lbfgs_o
     P.v_state = x->v;
     P.s_best = x->s_best;
   }
-  const GradShape shape = grad_shape(L, B, amh::kReduceThreads, amh::lbfgs_lds_bytes(L, 0, 0, o->m, o->nonmonotone) - amh::grad_lds_bytes(L, 0, 0));
+  const size_t history = amh::lbfgs_lds_bytes(L, 0, 0, o->m, o->nonmonotone) - amh::grad_lds_bytes(L, 0, 0);
+  const GradShape shape = grad_shape(L, B, amh::kReduceThreads, history);
   const size_t lds = shape.lds;
   P.cap = shape.cap;
   if (lds > kMaxLds) return sfail(AMH_E_INVAL, "L=%d needs %zu bytes of LDS for L-BFGS", L, lds);
@@ -563,17 +565,30 @@ amh_status amh_init(const amh_config* cfg, const float* y_dev, const double* s0_
   const int L = cfg->L, C = cfg->n_chains, n = 2 * L;
   const int64_t P = (int64_t)L * (L - 1) / 2;
   x->stride = row_stride(cfg->n_bins);
-  if ((st = dev_alloc(&x->table, (size_t)P * x->stride)) != AMH_OK ||
-      (st = dev_alloc(&x->ydev, (size_t)(P + 1) * x->stride)) != AMH_OK ||
-      (st = dev_alloc(&x->s, (size_t)C * n)) != AMH_OK ||
-      (st = dev_alloc(&x->s_best, (size_t)C * n)) != AMH_OK ||
-      (st = dev_alloc(&x->atoms, (size_t)C * L * 12)) != AMH_OK ||
-      (st = dev_alloc(&x->v, (size_t)C * 2)) != AMH_OK ||
-      (st = dev_alloc(&x->counters, (size_t)C * 4)) != AMH_OK ||
-      (st = dev_alloc(&x->err, 1)) != AMH_OK) {
+  // one allocation a context: an allocation and its release cost 17 us of host time together,
+  // of eight arrays 0.8 ms for six served jobs
+  size_t used = 0;
+  const auto take = [&](size_t bytes) {
+    const size_t at = used;
+    used += (bytes + 255) & ~(size_t)255;
+    return at;
+  };
+  const size_t o_table = take(sizeof(float) * P * x->stride), o_ydev = take(sizeof(float) * (P + 1) * x->stride),
+               o_s = take(sizeof(double) * C * n), o_best = take(sizeof(double) * C * n),
+               o_atoms = take(sizeof(double) * C * L * 12), o_v = take(sizeof(double) * C * 2),
+               o_cnt = take(sizeof(int64_t) * C * 4), o_err = take(sizeof(unsigned int)), o_vfar = take(sizeof(double));
+  if ((st = dev_alloc(&x->slab, used)) != AMH_OK) {
     free_ctx(x);
     return st;
   }
+  x->table = reinterpret_cast<float*>(x->slab + o_table);
+  x->ydev = reinterpret_cast<float*>(x->slab + o_ydev);
+  x->s = reinterpret_cast<double*>(x->slab + o_s);
+  x->s_best = reinterpret_cast<double*>(x->slab + o_best);
+  x->atoms = reinterpret_cast<double*>(x->slab + o_atoms);
+  x->v = reinterpret_cast<double*>(x->slab + o_v);
+  x->counters = reinterpret_cast<int64_t*>(x->slab + o_cnt);
+  x->err = reinterpret_cast<unsigned int*>(x->slab + o_err);
   hipError_t e = hipMemsetAsync(x->err, 0, sizeof(unsigned int), x->stream);
   if (e == hipSuccess)   // row P of the deviation table is the zero row
     e = hipMemsetAsync(x->ydev + (size_t)P * x->stride, 0, sizeof(float) * x->stride, x->stream);
@@ -586,17 +601,13 @@ amh_status amh_init(const amh_config* cfg, const float* y_dev, const double* s0_
     e = hipGetLastError();
   }
   if (e == hipSuccess) {   // the energy of the all-far conformation, read back once
-    double* d_vfar = nullptr;
-    e = hipMalloc(reinterpret_cast<void**>(&d_vfar), sizeof(double));
-    if (e == hipSuccess) {
-      hipLaunchKernelGGL(amh::far_sum_kernel, dim3(1), dim3(512), 0, x->stream, x->table, P, x->stride,
-                         cfg->n_bins, d_vfar);
-      e = hipGetLastError();
-      if (e == hipSuccess)
-        e = hipMemcpyAsync(&x->vfar, d_vfar, sizeof(double), hipMemcpyDeviceToHost, x->stream);
-      if (e == hipSuccess) e = hipStreamSynchronize(x->stream);
-      (void)hipFree(d_vfar);
-    }
+    double* const d_vfar = reinterpret_cast<double*>(x->slab + o_vfar);
+    hipLaunchKernelGGL(amh::far_sum_kernel, dim3(1), dim3(512), 0, x->stream, x->table, P, x->stride,
+                       cfg->n_bins, d_vfar);
+    e = hipGetLastError();
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(&x->vfar, d_vfar, sizeof(double), hipMemcpyDeviceToHost, x->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(x->stream);
   }
   if (e == hipSuccess && s0_dev)
     e = hipMemcpyAsync(x->s, s0_dev, sizeof(double) * C * n, hipMemcpyDeviceToDevice, x->stream);
@@ -923,6 +934,7 @@ struct amh_batch {
   };
   std::vector<Launch> launches;
   amh::SweepParams* d_desc = nullptr;
+  amh::SweepParams* h_ring = nullptr;   // pinned, kRing staging buffers
   amh::SweepParams* h_desc[kRing] = {};
   hipEvent_t ev[kRing] = {};
   bool ev_used[kRing] = {};
@@ -940,8 +952,8 @@ void free_batch(amh_batch* b) {
   if (!b) return;
   free_launches(b);
   (void)hipFree(b->d_desc);
+  if (b->h_ring) (void)hipHostFree(b->h_ring);
   for (int i = 0; i < kRing; ++i) {
-    if (b->h_desc[i]) (void)hipHostFree(b->h_desc[i]);
     if (b->ev[i]) (void)hipEventDestroy(b->ev[i]);
   }
   delete b;
@@ -1052,9 +1064,12 @@ amh_status amh_batch_create(amh_ctx* const* ctxs, int32_t n, amh_batch** out) {
   b->m.assign(ctxs, ctxs + n);
   b->stream = ctxs[0]->stream;
   hipError_t e = hipMalloc(reinterpret_cast<void**>(&b->d_desc), sizeof(amh::SweepParams) * kMaxRuns * n);
+  // (one pinned allocation for the ring: 42 us of host time each, with its release)
+  if (e == hipSuccess)
+    e = hipHostMalloc(reinterpret_cast<void**>(&b->h_ring), sizeof(amh::SweepParams) * kMaxRuns * n * kRing);
   for (int i = 0; e == hipSuccess && i < kRing; ++i) {
-    e = hipHostMalloc(reinterpret_cast<void**>(&b->h_desc[i]), sizeof(amh::SweepParams) * kMaxRuns * n);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&b->ev[i], hipEventDisableTiming);
+    b->h_desc[i] = b->h_ring + (size_t)i * kMaxRuns * n;
+    e = hipEventCreateWithFlags(&b->ev[i], hipEventDisableTiming);
   }
   if (e != hipSuccess) {
     free_batch(b);

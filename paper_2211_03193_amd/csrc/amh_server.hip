@@ -87,6 +87,10 @@ struct amh_server {
   int64_t* d_cnt = nullptr;
   double* d_v = nullptr;
   size_t cap_chains = 0;
+  // staging of a step's admissions and retirements (tables up, best states down): one device
+  // allocation that grows as they need it and is given back at the end of the step
+  void* d_stage = nullptr;
+  size_t cap_stage = 0;
   std::vector<int64_t> h_cnt;
   std::vector<double> h_v;
 };
@@ -110,10 +114,25 @@ void drop_batch(amh_server* s) {
   s->batch_members.clear();
 }
 
+void drop_stage(amh_server* s) {
+  (void)hipFree(s->d_stage);
+  s->d_stage = nullptr;
+  s->cap_stage = 0;
+}
+
+amh_status stage(amh_server* s, size_t bytes) {
+  if (bytes <= s->cap_stage) return AMH_OK;
+  drop_stage(s);   // (its users have synchronised the stream)
+  SHIP(hipMalloc(&s->d_stage, bytes));
+  s->cap_stage = bytes;
+  return AMH_OK;
+}
+
 amh_status admit(amh_server* s, Job* j) {
-  float* y_dev = nullptr;
   const size_t n = j->y.size();
-  SHIP(hipMalloc(reinterpret_cast<void**>(&y_dev), sizeof(float) * (n ? n : 1)));
+  const amh_status got = stage(s, sizeof(float) * (n ? n : 1));
+  if (got != AMH_OK) return got;
+  float* const y_dev = static_cast<float*>(s->d_stage);
   hipError_t e = hipMemcpyAsync(y_dev, j->y.data(), sizeof(float) * n, hipMemcpyHostToDevice, s->stream);
   amh_status st = AMH_OK;
   if (e != hipSuccess) st = sfail(AMH_E_DEVICE, "table upload: %s", hipGetErrorString(e));
@@ -122,7 +141,6 @@ amh_status admit(amh_server* s, Job* j) {
     if (st != AMH_OK) j->error = amh_last_error();
   }
   (void)hipStreamSynchronize(s->stream);
-  (void)hipFree(y_dev);
   if (st == AMH_OK && (st = amh_set_target(j->ctx, j->target)) != AMH_OK) j->error = amh_last_error();
   if (st == AMH_OK && j->traced &&
       (st = amh_set_trace(j->ctx, 1, &j->trace.chain, j->trace.dE_dev, j->trace.delta_dev,
@@ -146,9 +164,10 @@ amh_status admit(amh_server* s, Job* j) {
 
 amh_status retire(amh_server* s, Job* j) {
   const size_t C = j->cfg.n_chains, n = 2 * (size_t)j->cfg.L;
-  double* d_sb = nullptr;
-  SHIP(hipMalloc(reinterpret_cast<void**>(&d_sb), sizeof(double) * C * n));
-  amh_status st = amh_get_state(j->ctx, nullptr, d_sb, nullptr, nullptr, nullptr, nullptr);
+  amh_status st = stage(s, sizeof(double) * C * n);
+  if (st != AMH_OK) return st;
+  double* const d_sb = static_cast<double*>(s->d_stage);
+  st = amh_get_state(j->ctx, nullptr, d_sb, nullptr, nullptr, nullptr, nullptr);
   j->s_best.resize(C * n);
   if (st == AMH_OK) {
     hipError_t e = hipMemcpyAsync(j->s_best.data(), d_sb, sizeof(double) * C * n,
@@ -156,7 +175,6 @@ amh_status retire(amh_server* s, Job* j) {
     if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
     if (e != hipSuccess) st = sfail(AMH_E_DEVICE, "best-state read-back: %s", hipGetErrorString(e));
   }
-  (void)hipFree(d_sb);
   if (st != AMH_OK) return st;
   drop_batch(s);   // the batch borrows the context: never let it outlive it
   (void)amh_destroy(j->ctx);
@@ -248,6 +266,7 @@ amh_status amh_server_step(amh_server* s, int32_t* n_active, int32_t* n_pending)
     amh_status st = admit(s, j);
     if (st != AMH_OK) return st;
   }
+  drop_stage(s);
   if (!s->active.empty()) {
     // every active job advances its own chunk of sweeps (fewer at the end of its run)
     std::vector<amh_ctx*> ctxs;
@@ -334,6 +353,7 @@ amh_status amh_server_step(amh_server* s, int32_t* n_active, int32_t* n_pending)
       still.push_back(j->id);
     }
     s->active.swap(still);
+    drop_stage(s);
   }
   if (n_active) *n_active = (int32_t)s->active.size();
   if (n_pending) *n_pending = (int32_t)s->pending.size();
@@ -366,6 +386,7 @@ amh_status amh_server_destroy(amh_server* s) {
     if (kv.second->ctx) (void)amh_destroy(kv.second->ctx);
   (void)hipFree(s->d_cnt);
   (void)hipFree(s->d_v);
+  (void)hipFree(s->d_stage);
   delete s;
   return AMH_OK;
 }
