@@ -89,9 +89,21 @@ def pair_evals_per_cycle(L: int, d: int, cycle: int) -> tuple[int, int]:
 
 def schedule_work(L: int, d: int, cycle: int) -> dict:
     """Work of one chain in one alternation cycle that the schedule fixes (no
-    counting needed): localized changed pairs (two stencils each), candidate tiles
+    counting needed): localized changed pairs, the pairs that carry their energy from one
+    proposal to the next and the C-betas a proposal turns, candidate tiles
     of the global rectangle (8 x 8 residue blocks), transition pairs of the psi
     proposals and the anchor's pairs."""
+    h = d // 2
+    carry = turned = 0
+    for k in range(1, 2 * L - 1):
+        c, odd = k >> 1, k & 1
+        lo, hi = max(0, c - h), min(L - 1, c + h)
+        turned += hi - c + 1 - odd
+        if odd:      # the pivot moves past residue c
+            carry += (c - lo) + (hi - c)
+        else:        # the window moves on by a residue
+            lo1, hi1 = max(0, c - 1 - h), min(L - 1, c - 1 + h)
+            carry += (hi1 - c + 1 if lo > lo1 else 0) + (c - lo if hi > hi1 else 0)
     nb8 = (L + 7) // 8
     cand = 0
     for k in range(2 * L):
@@ -99,31 +111,33 @@ def schedule_work(L: int, d: int, cycle: int) -> dict:
         if p >= 1 and L - p >= 1:
             cand += (((p - 1) >> 3) + 1) * (nb8 - (p >> 3))
     _, loc = pair_evals_per_cycle(L, d, cycle)
-    return {"local_pairs": loc, "candidate_tiles": cand, "transition_pairs": L * (L - 1),
+    return {"local_pairs": loc, "local_carry_pairs": carry * (cycle - 1), "local_turned": turned * (cycle - 1),
+            "candidate_tiles": cand, "transition_pairs": L * (L - 1),
             "anchor_pairs": L * (L - 1) // 2}
 
 
 def executed_work(fixed: dict, counted: dict, chains: int) -> dict:
     """Executed work of one step, split by kernel: the localized-sweep launch (the
-    schedule's localized pairs: two stencils and a rotation each) and the
+    schedule's localized pairs and the pairs that carry their energy, a stencil each, and
+    a rotation for each C-beta turned) and the
     global-sweep launch (the schedule's candidate tiles, transition pairs and the
     anchor's pairs, plus the counted surviving tiles, pair tests and near pairs)."""
     loc = fixed["local_pairs"] * chains
+    carry = fixed["local_carry_pairs"] * chains
+    turned = fixed["local_turned"] * chains
     trans = fixed["transition_pairs"] * chains
     anch = fixed["anchor_pairs"] * chains
     cand = fixed["candidate_tiles"] * chains
     tests = counted["pair_tests"]
     near = counted["near_pairs"]
-    st_l = 2 * loc
+    st_l = loc + carry
     st_g = near + trans + anch
-    fl_l = FLOPS_TEST * 2 * loc + FLOPS_SPLINE * st_l + FLOPS_ROTATE * loc
+    fl_l = (FLOPS_TEST + FLOPS_SPLINE) * st_l + FLOPS_ROTATE * turned
     fl_g = FLOPS_TEST * (tests + cand + trans + anch) + FLOPS_SPLINE * st_g
-    # L2 gathers: one per localized pair (its second stencil, at the proposed distance,
-    # reads the same table row right after the first and mostly the same cache line),
-    # one per stencil of the global sweep
+    # L2 gathers: one per stencil
     return {
-        "local": {"local_pairs": loc, "stencils": st_l, "stencil_bytes": STENCIL_BYTES * st_l,
-                  "l2_gather_bytes": STENCIL_BYTES * loc, "flops": fl_l},
+        "local": {"local_pairs": loc, "carry_pairs": carry, "turned": turned, "stencils": st_l,
+                  "stencil_bytes": STENCIL_BYTES * st_l, "l2_gather_bytes": STENCIL_BYTES * st_l, "flops": fl_l},
         "global": {"candidate_tiles": cand, "surviving_tiles": counted["tiles"], "pair_tests": tests,
                    "near_pairs": near, "transition_pairs": trans, "anchor_pairs": anch, "stencils": st_g,
                    "stencil_bytes": STENCIL_BYTES * st_g, "l2_gather_bytes": STENCIL_BYTES * st_g, "flops": fl_g},

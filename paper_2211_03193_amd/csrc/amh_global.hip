@@ -31,8 +31,8 @@
 // Measured against global sweeps that rotated all atoms in LDS (128 bytes a residue), took
 // one tile at a time and wrote the next rotation after the decision, with a third barrier:
 // 1024 chains of 300 residues (2 chains and 4 wavefronts a workgroup) 6.8 -> 4.3 ms a
-// sweep; 128 chains of 300 2.9 -> 2.0 ms; 64 of 800 27.7 -> 14 ms; one of 64 residues
-// 370 -> 255 us.  What bounds it is instructions: a wavefront alone issues one in 5 to 8
+// sweep; 128 chains of 300 2.9 -> 1.7 ms; 64 of 800 27.7 -> 12.1 ms; one of 64 residues
+// 370 -> 250 us.  What bounds it is instructions: a wavefront alone issues one in 5 to 8
 // cycles (8 where it needs the one before), and with two a SIMD the vector units are busy
 // 52 % of the time at 1024 chains of 300 residues (1518 instructions a wavefront and
 // proposal).  Four wavefronts a SIMD fit (the helper's state is in LDS and the randoms are
@@ -106,8 +106,12 @@ __device__ __attribute__((noinline)) void draw_batch(CParams* P, int kn, uint32_
 template <int NW>
 __device__ __forceinline__ void global_body(CParams& P, const int group, const int G) {
   extern __shared__ __align__(16) unsigned char lds[];
-  // From four wavefronts on the helper leaves the tiles to the others and takes the
-  // transitions; below, the wavefronts share both.
+  // From four wavefronts on the helper leaves the tiles to the others; with four it takes the
+  // transitions (16 wavefronts a unit are busy, and taking them elsewhere cost 4 % at 1500
+  // chains of 250 residues), below, the wavefronts share both.  With eight and more (kWide) the
+  // helper's next rotation alone is as long as the others' tiles, so these take the
+  // transitions too, gathered before the candidate tests, and the helper goes first on its
+  // vector unit: 128 chains of 300 residues 1970 -> 1735 us a sweep, 64 of 800 8670 -> 7390.
   constexpr int TW = NW >= 4 ? NW - 1 : NW;
   constexpr bool kWide = NW >= 8;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

@@ -136,7 +136,8 @@ __device__ double block_maxabs(const double* __restrict__ x, int n, double* red)
 //   * every lane adds the forces of its row and then of its column, each in the order
 //     u = (j - i) mod 64.  A list that its LDS does not hold is taken in ranges of u.
 // A tile's forces on a residue and a pair's energy, rounded to multiples of 2^-44, are added as
-// integers (the energy's whole numbers and fractions apart, which bounds neither): the totals do not depend on the order of the tiles or on the launch shape.
+// integers (the energy's whole numbers and fractions apart, which bounds neither): the totals
+// do not depend on the order of the tiles or on the launch shape.
 // At 512 conformations of 400 residues (two workgroups of 4 wavefronts a unit, one pair in six
 // inside the last knot) the time goes to the sums (27 %), the marks (20 %), the coordinates
 // (19 %) and the evaluations (17 %): vector instructions, at two wavefronts a SIMD.  Evaluating
@@ -178,7 +179,9 @@ __device__ double value_grad(const double* __restrict__ s, int L, const float* _
   __builtin_amdgcn_s_waitcnt(0);
   for (;;) {
     int tile = 0;
-    if (lane == 0) tile = (int)__hip_atomic_fetch_add((__attribute__((address_space(3))) int*)(vacc + 1), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (lane == 0)
+      tile = (int)__hip_atomic_fetch_add((__attribute__((address_space(3))) int*)(vacc + 1), 1, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_WORKGROUP);
     tile = __builtin_amdgcn_readfirstlane(tile);
     if (tile >= ntile) break;
     int off = 0, I = tile;   // J - I, I
@@ -469,7 +472,8 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) l
     if (xtr) xtr[e] = sb[e];
   }
   __syncthreads();
-  double f = value_grad(x, L, P.table, P.stride, P.nb, P.d_min, P.bin_w, P.vfar, x64, ft, sph, pairs, P.cap, reinterpret_cast<long long*>(red), g);
+  double f = value_grad(x, L, P.table, P.stride, P.nb, P.d_min, P.bin_w, P.vfar, x64, ft, sph, pairs, P.cap,
+                        reinterpret_cast<long long*>(red), g);
   if (trace && tid == 0) trace[0] = f;
   if (tid == 0) fh[0] = f;
   int k = 0, head = 0, nf = 1, it = 0, status = 1;
@@ -530,7 +534,8 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) l
     for (int ls = 0; ls < P.max_ls; ++ls) {
       for (int e = tid; e < n; e += T) xn[e] = x[e] + alpha * d[e];
       __syncthreads();
-      fnew = value_grad(xn, L, P.table, P.stride, P.nb, P.d_min, P.bin_w, P.vfar, x64, ft, sph, pairs, P.cap, reinterpret_cast<long long*>(red), gn);
+      fnew = value_grad(xn, L, P.table, P.stride, P.nb, P.d_min, P.bin_w, P.vfar, x64, ft, sph, pairs, P.cap,
+                        reinterpret_cast<long long*>(red), gn);
       if (fnew <= fref + P.c1 * alpha * gd) { ok = true; break; }
       alpha *= P.shrink;
     }

@@ -90,7 +90,8 @@ struct EnergyQueue {
 };
 
 inline size_t conf_lds_bytes(int L, int threads, bool energy) {
-  const size_t frames = 8 * 12 * ((3 * ((size_t)L - 1) + 63) / 64), queues = energy ? sizeof(EnergyQueue) * (threads / 64) : 0;
+  const size_t frames = 8 * 12 * ((3 * ((size_t)L - 1) + 63) / 64);
+  const size_t queues = energy ? sizeof(EnergyQueue) * (threads / 64) : 0;
   return 8 * (14 * (size_t)L + 2) + 16 * (size_t)((L + 7) / 8) + (frames > queues ? frames : queues);
 }
 

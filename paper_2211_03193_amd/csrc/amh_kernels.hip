@@ -7,35 +7,12 @@
 // within d/2 of residue k/2 (localized MH, Sec. 2.3); global and localized sweeps
 // alternate (Algorithm 1, Fig. 1); acceptance min(1, exp(-beta dE)) (Sec. 2.1).
 //
-// Mapping to the GPU (our design, not the paper's block-per-chain layout):
-//   * a workgroup owns G chains that walk the same proposal index k in lockstep,
-//     so every table row a global proposal needs is fetched once per workgroup
-//     from L2 and shared by the G chains;
-//   * localized sweeps are run by one wavefront per chain with no workgroup
-//     barrier; residues beyond the window are brought up to date lazily with one
-//     accumulated rigid transform (float64) when they enter the window;
-//   * pair energies are handled as deviations from the pair's no-contact value
-//     (a second copy of the table with that value subtracted), which are exactly
-//     zero beyond the last knot: a pair farther apart than 20.25 A costs a
-//     distance and a compare, no table access;
-//   * global proposals use every wavefront of the workgroup; dE of pivot p is
-//     D_new(p) - D(p), where D(p), the deviation energy of the pair rectangle
-//     i < p <= j of the current conformation, is carried from proposal to
-//     proposal (the new rectangle sum on accept, an O(L) row/column update when
-//     p advances), so each global proposal evaluates one spline per changed near
-//     pair instead of two;
-//   * the rectangle is walked in 8 x 8 tiles (blocks of 8 residues); a tile whose
-//     two bounding spheres lie farther apart than the last knot holds only pairs
-//     that add zero and is skipped whole, a decision uniform over the wavefront;
-//   * the proposal randoms come from Philox4x32-10 at counter (k, t, chain, 0),
-//     the same stream the oracle replays, drawn 64 proposals at a time, one per lane;
-//   * the master coordinates (N, CA, C, C-beta) live in LDS in float64 and are
-//     rotated in float64; the O(L^2) pair loop reads float32 C-beta positions taken
-//     relative to the pivot point, rounded once per proposal, so float32 never
-//     accumulates error in the state (an extended 300-residue chain spans ~1000 A,
-//     where float32 resolves only ~6e-5 A);
-//   * after every anchor sweep the coordinates are rebuilt from the float64
-//     torsions by NeRF and V is re-anchored in float64 with Neumaier summation.
+// The localized sweeps are in amh_local.hip, the global ones in amh_global.hip, the gradient
+// and L-BFGS in amh_grad.hip.  Here: the table's repacking, energies and coordinates of given
+// conformations, and anchors.  After every anchor sweep the coordinates are rebuilt from the
+// float64 torsions by NeRF and V is re-anchored in float64, so that neither the sweeps'
+// rotations nor their float32 distances accumulate an error in the state (an extended
+// 300-residue chain spans ~1000 A, where float32 resolves only ~6e-5 A).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

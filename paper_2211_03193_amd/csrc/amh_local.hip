@@ -189,7 +189,8 @@ __device__ __forceinline__ void local_sweep(CParams& P, const Lds& S, int nact, 
     // (hardware reciprocals: quotients of numbers below 2^11 stay exact)
     const float inv = __builtin_amdgcn_rcpf((float)cols);
     const int groups = (int)(((float)LW + 0.5f) * inv);
-    rows = __builtin_amdgcn_readfirstlane((int)(((float)(nF + groups - 1) + 0.5f) * __builtin_amdgcn_rcpf((float)groups)));
+    rows = __builtin_amdgcn_readfirstlane(
+        (int)(((float)(nF + groups - 1) + 0.5f) * __builtin_amdgcn_rcpf((float)groups)));
     const int g = (int)(((float)ll + 0.5f) * inv), j = p + b0 + (ll - g * cols), i0 = lo + g * rows;
     const int cnt = g < groups && i0 < p ? (i0 + rows < p ? rows : p - i0) : 0;
     return (j - c) | ((cnt > 0 ? c - i0 : 0) << 10) | (cnt << 21);

@@ -1,5 +1,5 @@
 // amh_proposal.h -- proposal randoms, schedule and trace helpers shared by the localized
-// (amh_kernels.hip) and global (amh_global.hip) sweep kernels.
+// (amh_local.hip) and global (amh_global.hip) sweep kernels.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
