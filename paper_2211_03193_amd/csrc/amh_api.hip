@@ -282,9 +282,9 @@ amh::SweepParams sweep_params(const amh_ctx* x, int64_t n_sweeps) {
   P.vfar = x->vfar;
   P.L = c.L;
   P.C = c.n_chains;
-  P.half_window = c.window_d / 2;
+  P.half_window = amh::half_window(c.window_d, c.L);
   P.n_cascade = c.n_cascade;
-  for (int i = 0; i < 3; ++i) P.cascade_hw[i] = i < c.n_cascade ? c.cascade_d[i] / 2 : 0;
+  for (int i = 0; i < 3; ++i) P.cascade_hw[i] = i < c.n_cascade ? amh::half_window(c.cascade_d[i], c.L) : 0;
   P.sigma_end = c.sigma_end;
   P.global_every = c.global_every;
   P.n_global = c.n_global < 1 ? 1 : c.n_global;

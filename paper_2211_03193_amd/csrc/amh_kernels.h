@@ -83,6 +83,11 @@ __host__ __device__ inline bool is_global(const SweepParams& P, int64_t t) {
   return P.global_every > 0 && (int)((uint32_t)t % (uint32_t)P.global_every) >= P.global_every - P.n_global;
 }
 
+// Half-width of a localization radius d >= 0 in a chain of L residues.  The window [max(0, c - h),
+// min(L - 1, c + h)] is the whole chain from h = L - 1 on, so a wider one is cut to it: the
+// kernels' loops and sums of half-widths (c + 2h, 4h) stay within a few L whatever the d.
+inline int half_window(int d, int L) { return d / 2 < L - 1 ? d / 2 : L - 1; }
+
 // A wavefront's pairs inside the last knot, waiting for their energies.
 struct EnergyQueue {
   double d2[128];           // (63 and a tile at most)

@@ -1,0 +1,34 @@
+"""GPU tests of localized sweeps whose window is wider than the chain."""
+import numpy as np
+import pytest
+
+import synthetic as sy
+
+pytestmark = pytest.mark.gpu
+
+import gpu_util as gu  # noqa: E402  (an import error fails the run)
+
+
+@pytest.mark.parametrize("G", [1, 2, 4])
+def test_windows_wider_than_the_chain(G):
+    """Radii up to the largest 32-bit number, one after the other in a cascade: every proposal
+    as with radii of twice the chain, and as the oracle's."""
+    L, C, n = 21, 5, 15
+    w = sy.Workload(f"wide-{G}", L=L, n_chains=C, total_sweeps=n, window_d=2 * L, cascade=(2 * L, 6, 2 * L),
+                    global_every=0, anchor_every=15, seed=0x31d, protein_seed=8, noise_seed=9)
+    s_ref, y = gu.protein(w)
+    rng = np.random.Generator(np.random.PCG64(3))
+    s0 = sy._wrap(s_ref[None] + 0.2 * rng.standard_normal((C, 2 * L)))
+    out = []
+    for radii in ((2 * L, 2 * L, 6, 2 * L), (2**31 - 1, 10**6, 6, 2**30)):
+        gu.say("windows wider than the chain", G, radii)
+        wide = w.replace(window_d=radii[0], cascade=radii[1:])
+        ctx = gu.context(wide, y, s0=s0, chains_per_group=G, waves_per_group=4)
+        tr = gu.traced_run(ctx, [0, 4], n)
+        st = ctx.get_state()
+        ctx.close()
+        for slot, chain in enumerate((0, 4)):
+            rc, rep, _ = gu.replay_chain(w, y, tr, slot, chain, s0[chain])
+            assert rc == 0 and rep["n_de_fail"] == 0 and rep["n_logic_fail"] == 0, (radii, rep)
+        out.append([st[k].cpu().numpy() for k in ("s", "v", "counters")] + [tr["dE"]])
+    assert all(np.array_equal(a, b) for a, b in zip(*out))
