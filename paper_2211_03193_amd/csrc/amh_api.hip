@@ -273,10 +273,7 @@ amh::SweepParams sweep_params(const amh_ctx* x, int64_t n_sweeps) {
   P.inv_w = (float)(1.0 / c.bin_w);
   P.off = (float)((c.d_min + 0.5 * c.bin_w) / c.bin_w);
   P.tmax = (float)(c.n_bins - 1);
-  {
-    const double dfar = c.d_min + c.bin_w * (c.n_bins - 0.5);   // last knot
-    P.d2far = (float)(dfar * dfar);
-  }
+  P.d2far = amh::last_knot2(c.d_min, c.bin_w, c.n_bins);
   P.d_min = c.d_min;
   P.bin_w = c.bin_w;
   P.vfar = x->vfar;

@@ -88,6 +88,15 @@ __host__ __device__ inline bool is_global(const SweepParams& P, int64_t t) {
 // kernels' loops and sums of half-widths (c + 2h, 4h) stay within a few L whatever the d.
 inline int half_window(int d, int L) { return d / 2 < L - 1 ? d / 2 : L - 1; }
 
+// Squared distance of the last knot as the sweeps test it.  The global kernel's absent rows and
+// columns stand 1e18 A off, and the localized one's unused slots at +inf: both have to lie beyond
+// it, or they would be taken for pairs and read past the table.  No two residues of a chain are
+// 1e15 A apart, so a knot farther off than that is as good as there.
+inline float last_knot2(double d_min, double bin_w, int n_bins) {
+  const double d = d_min + bin_w * (n_bins - 0.5), d2 = d * d;
+  return d2 < 1e30 ? (float)d2 : 1e30f;
+}
+
 // A wavefront's pairs inside the last knot, waiting for their energies.
 struct EnergyQueue {
   double d2[128];           // (63 and a tile at most)

@@ -1,6 +1,7 @@
 // Prints what the host rules of amh_kernels.h give for the arguments of a command line, for
 // tests/test_host_rules.py (no GPU needed).
 //   half_window <d> <L>
+//   last_knot2 <d_min> <bin_w> <n_bins>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -11,6 +12,10 @@ int main(int argc, char** argv) {
   const auto num = [&](int i) { return std::atoll(i < argc ? argv[i] : "0"); };
   if (argc == 4 && !std::strcmp(argv[1], "half_window")) {
     std::printf("%d\n", amh::half_window((int)num(2), (int)num(3)));
+    return 0;
+  }
+  if (argc == 5 && !std::strcmp(argv[1], "last_knot2")) {
+    std::printf("%.9g\n", (double)amh::last_knot2(std::atof(argv[2]), std::atof(argv[3]), (int)num(4)));
     return 0;
   }
   return 2;

@@ -32,3 +32,22 @@ def test_windows_wider_than_the_chain(G):
             assert rc == 0 and rep["n_de_fail"] == 0 and rep["n_logic_fail"] == 0, (radii, rep)
         out.append([st[k].cpu().numpy() for k in ("s", "v", "counters")] + [tr["dE"]])
     assert all(np.array_equal(a, b) for a, b in zip(*out))
+
+
+@pytest.mark.parametrize("bin_w", [1e19, 1e30])
+def test_bins_wider_than_any_chain(bin_w):
+    """Every pair below the first knot, where the energy is flat: nothing a proposal does changes
+    it, localized or global, and absent residues of the last tiles are no pairs."""
+    w = sy.Workload("bins", L=13, n_chains=3, total_sweeps=4, window_d=6, global_every=2, anchor_every=2, seed=0xb1,
+                    protein_seed=5, noise_seed=6)
+    _, y = gu.protein(w)
+    gu.say("bins of", bin_w)
+    ctx = gu.context(w, y, bin_w=bin_w, d_min=0.0)
+    tr = gu.traced_run(ctx, [0, 2], 4)
+    V, _, _ = ctx.energy()
+    V = V.cpu().numpy()
+    ctx.close()
+    assert np.all(tr["dE"] == 0.0) and np.all(tr["acc"] == 1)
+    first = np.asarray(y, dtype=np.float32)[:, 0].astype(np.float64).sum()
+    assert V == pytest.approx(np.full(3, first), rel=1e-12)
+    assert tr["anchor"][:2, :2] == pytest.approx(np.full((2, 2), first), rel=1e-12)

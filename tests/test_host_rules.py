@@ -3,6 +3,7 @@ import os
 import shutil
 import subprocess
 
+import numpy as np
 import pytest
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -29,3 +30,19 @@ def test_half_window_is_at_most_the_chain(rule, L):
         assert h <= L - 1
         for c in range(L):   # the same window as the radius asks for
             assert max(0, c - h) == max(0, c - d // 2) and min(L - 1, c + h) == min(L - 1, c + d // 2)
+
+
+@pytest.mark.parametrize("d_min, bin_w, n_bins", [(2.0, 0.5, 37), (0.0, 1e3, 64), (-40.0, 1.0, 37), (0.0, 1e18, 4),
+                                                  (1e19, 1.0, 37), (-1e300, 1e30, 37), (0.0, 1e300, 64)])
+def test_absent_residues_lie_beyond_the_last_knot(rule, d_min, bin_w, n_bins):
+    """The squared distances at which the global kernel places absent rows (-1e18 A on every
+    axis) and columns (+1e18 A): from each other and from residues of a chain, whatever the
+    configured bins, and no pair of a chain of 1024 residues is taken out by the bound."""
+    d2 = np.float32(rule("last_knot2", d_min, bin_w, n_bins)[0])
+    far = np.float32(1e18)
+    for x in (0.0, 5e3, -5e3):
+        a = np.float32(x) - far
+        assert not a * a + a * a + a * a < d2
+    assert not np.float32(np.inf) < d2
+    knot = d_min + bin_w * (n_bins - 0.5)
+    assert d2 == np.float32(knot * knot) if abs(knot) < 1e15 else d2 > 1e8
