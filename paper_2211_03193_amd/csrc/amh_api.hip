@@ -426,15 +426,6 @@ size_t global_launch_lds(const amh_ctx* x) {
   return amh::global_lds_bytes(x->G_global, x->cfg.L, global_waves(x->G_global, x->W_global));
 }
 
-// End of the run of sweeps that starts at t: sweeps of one kind (localized or global), up
-// to an anchor (after a sweep count that anchor_every divides) or `end`.
-int64_t run_end(const amh::SweepParams& P, int64_t t, int64_t end) {
-  const bool glob = amh::is_global(P, t);
-  int64_t e = t + 1;
-  while (e < end && e % P.anchor_every != 0 && amh::is_global(P, e) == glob) ++e;
-  return e;
-}
-
 }  // namespace
 
 namespace {
@@ -645,7 +636,7 @@ amh_status amh_sweep(amh_ctx* x, int64_t n_sweeps) {
   const int64_t end = x->t + n_sweeps;
   for (int64_t t = x->t; t < end;) {
     const bool glob = amh::is_global(P, t);
-    const int64_t e = run_end(P, t, end);
+    const int64_t e = amh::run_end(P, t, end);
     P.t0 = t;
     P.n_sweeps = e - t;
     amh_status st = AMH_OK;
@@ -1141,7 +1132,7 @@ amh_status amh_batch_sweep_each(amh_batch* b, const int64_t* n_sweeps) {
     amh_status st = add_step(glob ? Step::global : Step::local, [&](size_t i, amh::SweepParams& P) {
       if (t[i] >= end[i] || amh::is_global(base[i], t[i]) != glob) return false;
       P.t0 = t[i];
-      t[i] = run_end(base[i], t[i], end[i]);
+      t[i] = amh::run_end(base[i], t[i], end[i]);
       P.n_sweeps = t[i] - P.t0;
       return true;
     });

@@ -157,7 +157,7 @@ __device__ __forceinline__ void global_body(CParams& P, const int group, const i
   // sums of a wavefront's rows of 16 lanes: rows 0 and 1 the rectangle's, 2 and 3 the
   // transition's; part holds the former in its first half, the latter in its second
   constexpr int kHalf = NW == 16 ? 32 : 16;
-  int n_acc = 0;
+  int n_acc = 0;   // accepted proposals (run_end keeps them below 2^31)
   unsigned int wk_tiles = 0, wk_tests = 0, wk_near = 0;   // executed work (tests: of this lane)
 
   for (int r = lane + 64 * wl; r < nres8; r += 64 * NW) {

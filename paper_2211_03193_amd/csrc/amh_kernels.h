@@ -83,6 +83,17 @@ __host__ __device__ inline bool is_global(const SweepParams& P, int64_t t) {
   return P.global_every > 0 && (int)((uint32_t)t % (uint32_t)P.global_every) >= P.global_every - P.n_global;
 }
 
+// End of the run of sweeps that starts at t and goes into one launch: sweeps of one kind
+// (localized or global), up to an anchor (after a sweep count that anchor_every divides) or `end`,
+// and at most 2^30 proposals a chain, which a launch counts the accepted of in 32 bits.
+inline int64_t run_end(const SweepParams& P, int64_t t, int64_t end) {
+  const bool glob = is_global(P, t);
+  const int64_t most = t + (1 << 30) / (2 * P.L);
+  int64_t e = t + 1;
+  while (e < end && e < most && e % P.anchor_every != 0 && is_global(P, e) == glob) ++e;
+  return e;
+}
+
 // Half-width of a localization radius d >= 0 in a chain of L residues.  The window [max(0, c - h),
 // min(L - 1, c + h)] is the whole chain from h = L - 1 on, so a wider one is cut to it: the
 // kernels' loops and sums of half-widths (c + 2h, 4h) stay within a few L whatever the d.

@@ -397,7 +397,7 @@ __device__ __forceinline__ void local_body(CParams& P, const int group) {
   }
   for (int e = tid; e < nact * n; e += T) S.s(e / n)[e % n] = P.s[(size_t)c0 * n + e];
   const int lslot = (lane / (64 / G)) < nact ? trace_slot(P, c0 + lane / (64 / G)) : -1;
-  int acc_stage = 0;   // accepted proposals of this lane's chain
+  int acc_stage = 0;   // accepted proposals of this lane's chain (run_end keeps them below 2^31)
   bool stalled = false;
   // blocks of at most 4096 sweeps (the progress counters' range)
   for (int64_t t = P.t0, t_end = P.t0 + P.n_sweeps; t < t_end;) {

@@ -2,6 +2,7 @@
 // tests/test_host_rules.py (no GPU needed).
 //   half_window <d> <L>
 //   last_knot2 <d_min> <bin_w> <n_bins>
+//   run_end <L> <global_every> <n_global> <anchor_every> <t> <end>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -16,6 +17,15 @@ int main(int argc, char** argv) {
   }
   if (argc == 5 && !std::strcmp(argv[1], "last_knot2")) {
     std::printf("%.9g\n", (double)amh::last_knot2(std::atof(argv[2]), std::atof(argv[3]), (int)num(4)));
+    return 0;
+  }
+  if (argc == 8 && !std::strcmp(argv[1], "run_end")) {
+    amh::SweepParams P{};
+    P.L = (int)num(2);
+    P.global_every = (int)num(3);
+    P.n_global = (int)num(4);
+    P.anchor_every = (int)num(5);
+    std::printf("%lld\n", (long long)amh::run_end(P, num(6), num(7)));
     return 0;
   }
   return 2;

@@ -46,3 +46,25 @@ def test_absent_residues_lie_beyond_the_last_knot(rule, d_min, bin_w, n_bins):
     assert not np.float32(np.inf) < d2
     knot = d_min + bin_w * (n_bins - 0.5)
     assert d2 == np.float32(knot * knot) if abs(knot) < 1e15 else d2 > 1e8
+
+
+@pytest.mark.parametrize("L", [2, 3, 300, 1024])
+@pytest.mark.parametrize("every", [0, 1])
+def test_a_launch_counts_its_accepted_proposals_in_32_bits(rule, L, every):
+    """The longest run of sweeps of one kind without an anchor that a configuration allows: a
+    launch has fewer proposals a chain than a 32-bit counter holds, and the runs follow on."""
+    end = 2**32 - 1
+    t = 0
+    for _ in range(3):
+        e = int(rule("run_end", L, every, every, 2**31 - 1, t, end)[0])
+        assert t < e and (e - t) * 2 * L < 2**31
+        t = e
+
+
+def test_runs_end_at_anchors_and_kinds(rule):
+    """Cycles of ten with two global sweeps, anchors every three sweeps."""
+    ends, t = [], 0
+    while t < 20:
+        t = int(rule("run_end", 50, 10, 2, 3, t, 20)[0])
+        ends.append(t)
+    assert ends == [3, 6, 8, 9, 10, 12, 15, 18, 20]
