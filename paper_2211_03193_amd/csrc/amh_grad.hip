@@ -135,9 +135,9 @@ __device__ double block_maxabs(const double* __restrict__ x, int n, double* red)
 //   * the pairs are listed row by row and evaluated 64 at a time, dE/dd / d going to LDS;
 //   * every lane adds the forces of its row and then of its column, each in the order
 //     u = (j - i) mod 64.  A list that its LDS does not hold is taken in ranges of u.
-// A tile's forces on a residue and a pair's energy, rounded to multiples of 2^-44, are added as
-// integers (the energy's whole numbers and fractions apart, which bounds neither): the totals
-// do not depend on the order of the tiles or on the launch shape.
+// A tile's forces on a residue, rounded to multiples of 2^-44, and a pair's energy, in multiples of
+// 2^-26 and 2^-70, are added as integers: the totals do not depend on the order of the tiles or
+// on the launch shape.
 // At 512 conformations of 400 residues (two workgroups of 4 wavefronts a unit, one pair in six
 // inside the last knot) the time goes to the sums (27 %), the marks (20 %), the coordinates
 // (19 %) and the evaluations (17 %): vector instructions, at two wavefronts a SIMD.  Evaluating
@@ -280,9 +280,12 @@ __device__ double value_grad(const double* __restrict__ s, int L, const float* _
         if (!a.use) return;
         double E, dE;
         spline64_ed((double)a.q0, (double)a.q1, (double)a.q2, (double)a.q3, a.t, a.b, nb, inv_w, E, dE);
-        const double e = E - (double)a.qn, n = rint(e);   // (sums of integers below 2^53)
+        // deviation e + low from the no-contact value, exactly (Knuth's two-sum), in multiples
+        // of 2^-26 and of 2^-70: every digit of a pair's energy down to these
+        const double qn = (double)a.qn, e = E - qn, z = e - E, low = (E - (e - z)) - (qn + z);
+        const double n = rint(e * 0x1p26);   // (sums of integers below 2^53)
         whole += n;
-        part += rint((e - n) * 0x1p44);
+        part += rint((fma(n, -0x1p-26, e) + low) * 0x1p70);
         qs[k] = a.inv_d > 0.0 ? dE * a.inv_d : 0.0;
       };
       // two records in turn, so that no gathered value is copied
@@ -361,7 +364,12 @@ __device__ double value_grad(const double* __restrict__ s, int L, const float* _
     o[5] = kx * fy - ky * fx;
   }
   wide = __syncthreads_or(wide);   // (also the barrier that publishes ft)
-  const double V = wide ? __builtin_nan("") : vfar + ((double)vacc[0] + (double)vacc[2] * 0x1p-44);
+  double V = vfar, Vc = 0.0;   // the two sums, split so that each part converts exactly
+  neumaier_add(V, Vc, (double)(vacc[0] >> 32) * 0x1p6);
+  neumaier_add(V, Vc, (double)(vacc[0] & 0xffffffffLL) * 0x1p-26);
+  neumaier_add(V, Vc, (double)(vacc[2] >> 32) * 0x1p-38);
+  neumaier_add(V, Vc, (double)(vacc[2] & 0xffffffffLL) * 0x1p-70);
+  V = wide ? __builtin_nan("") : V + Vc;
   // suffix sums S_p, T_p (six components, one lane each, in chain order; eight residues
   // are read ahead of the additions, which alone are a chain)
   if (wave == 0 && lane < 6) {
