@@ -120,6 +120,41 @@ __device__ double block_maxabs(const double* __restrict__ x, int n, double* red)
   return m;
 }
 
+__device__ __forceinline__ double pair_dist2(double ex, double ey, double ez) {
+  return fma(ez, ez, fma(ex, ex, ey * ey));
+}
+
+// V by one wavefront, pair by pair in a fixed order with Neumaier's compensation, of any finite
+// energies: for tables with a pair 2^16 nats or more from its no-contact value, which the
+// integer sums of value_grad do not hold.
+__device__ __attribute__((noinline)) double ordered_energy(int L, const gfloat* table, int stride, int nb,
+                                                           double first, double inv_w, double d2far,
+                                                           const double* x64) {
+  const int lane = threadIdx.x & 63;
+  double s = 0.0, c = 0.0;
+  for (int i = 0; i < L; ++i) {
+    const double* xi = atom(x64, i, 3);
+    for (int j = i + 1 + lane; j < L; j += 64) {
+      const double* xj = atom(x64, j, 3);
+      const double d2 = pair_dist2(xj[0] - xi[0], xj[1] - xi[1], xj[2] - xi[2]);
+      const gfloat* row = table + (size_t)pair_row(i, j, L) * stride;
+      double E = (double)row[nb], dE;
+      if (!(d2 >= d2far)) {   // (a NaN distance gives a NaN energy)
+        const double t = fma(d2, d2 > 0.0 ? rsqrt64(d2) : 0.0, -first) * inv_w;
+        const int b = stencil_base(t, nb);
+        spline64_ed((double)row[b], (double)row[b + 1], (double)row[b + 2], (double)row[b + 3], t, b, nb, inv_w, E, dE);
+      }
+      neumaier_add(s, c, E);
+    }
+  }
+  double a = 0.0, b = 0.0;
+  for (int l = 0; l < 64; ++l) {
+    neumaier_add(a, b, readlane_d(s, l));
+    b += readlane_d(c, l);
+  }
+  return a + b;
+}
+
 // V(s) and, if g != null, dV/ds of one conformation, by the whole workgroup.
 // x64 [12 L], ft [6 (L + 1)], sph [(L + 7) / 8] and pairs [wavefronts] (of grad_pair_bytes(cap)
 // bytes each) are LDS scratch, vacc three LDS words.
@@ -164,6 +199,7 @@ __device__ double value_grad(const double* __restrict__ s, int L, const float* _
   block_spheres(x64, L, sph);
   __syncthreads();
   bool wide = false;   // an item's sum beyond the integer range (or NaN): V is returned NaN
+  bool huge = false;   // a pair's deviation beyond the range of the energy's integers
   const int nb64 = (L + 63) >> 6, ntile = nb64 * (nb64 + 1) / 2;
   // this wavefront's list of a tile's pairs: dE/dd / d, the marks and list positions of its
   // rows, and the pairs themselves (row | u << 6)
@@ -172,7 +208,6 @@ __device__ double value_grad(const double* __restrict__ s, int L, const float* _
   unsigned long long* const marks = reinterpret_cast<unsigned long long*>(qs + cap);
   unsigned short* const base = reinterpret_cast<unsigned short*>(marks + 64);
   unsigned short* const code = base + 64;
-  auto dist2 = [&](double ex, double ey, double ez) { return fma(ez, ez, fma(ex, ex, ey * ey)); };
   // retire every memory operation before the tiles (the NeRF's spill stores among them),
   // so that inside them only the table gathers are counted and each step waits for
   // the gather of the pairs it evaluates, not for the one issued for the next step
@@ -202,7 +237,7 @@ __device__ double value_grad(const double* __restrict__ s, int L, const float* _
 #pragma unroll
       for (int r = 0; r < 8; ++r) {   // (NaN distances are evaluated, so V turns NaN)
         const double* x = atom(x64, j0 + q + r < L ? j0 + q + r : 0, 3);
-        const bool use = !(dist2(x[0] - ix, x[1] - iy, x[2] - iz) >= d2far);
+        const bool use = !(pair_dist2(x[0] - ix, x[1] - iy, x[2] - iz) >= d2far);
         const unsigned long long bal = __ballot(use);
         mine |= use ? 1u << r : 0u;
         if ((lane & 7) == r) rows = bal;
@@ -266,7 +301,7 @@ __device__ double value_grad(const double* __restrict__ s, int L, const float* _
         const int pi = i0 + (cd & 63), pj = a.use ? j0 + (((cd & 63) + (cd >> 6)) & 63) : 0;
         const double* xa = atom(x64, pi, 3);
         const double* xb = atom(x64, pj, 3);
-        const double d2 = dist2(xb[0] - xa[0], xb[1] - xa[1], xb[2] - xa[2]);
+        const double d2 = pair_dist2(xb[0] - xa[0], xb[1] - xa[1], xb[2] - xa[2]);
         // distance through the hardware reciprocal square root and two Newton steps
         a.inv_d = a.use && d2 > 0.0 ? rsqrt64(d2) : 0.0;
         a.t = fma(d2, a.inv_d, -first) * inv_w;
@@ -283,6 +318,7 @@ __device__ double value_grad(const double* __restrict__ s, int L, const float* _
         // deviation e + low from the no-contact value, exactly (Knuth's two-sum), in multiples
         // of 2^-26 and of 2^-70: every digit of a pair's energy down to these
         const double qn = (double)a.qn, e = E - qn, z = e - E, low = (E - (e - z)) - (qn + z);
+        huge = huge || !(fabs(e) < 0x1p16);
         const double n = rint(e * 0x1p26);   // (sums of integers below 2^53)
         whole += n;
         part += rint((fma(n, -0x1p-26, e) + low) * 0x1p70);
@@ -334,7 +370,7 @@ __device__ double value_grad(const double* __restrict__ s, int L, const float* _
     }
     const double lim = 0x1p13;   // |tile sum| < 2^13: a residue's total stays below 2^19
     wide = wide || !(fabs(rx) < lim && fabs(ry) < lim && fabs(rz) < lim && fabs(cx) < lim &&
-                     fabs(cy) < lim && fabs(cz) < lim && fabs(whole) < 0x1p53);
+                     fabs(cy) < lim && fabs(cz) < lim);
     if (!wide) {
       if (row != 0) {
         lds_add(facc + 6 * i, fixed44(rx));
@@ -346,8 +382,10 @@ __device__ double value_grad(const double* __restrict__ s, int L, const float* _
         lds_add(facc + 6 * j + 1, fixed44(cy));
         lds_add(facc + 6 * j + 2, fixed44(cz));
       }
-      lds_add(vacc, (long long)whole);
-      lds_add(vacc + 2, (long long)part);
+      if (!huge) {
+        lds_add(vacc, (long long)whole);
+        lds_add(vacc + 2, (long long)part);
+      }
     }
   }
   __syncthreads();
@@ -363,13 +401,22 @@ __device__ double value_grad(const double* __restrict__ s, int L, const float* _
     o[4] = kz * fx - kx * fz;
     o[5] = kx * fy - ky * fx;
   }
-  wide = __syncthreads_or(wide);   // (also the barrier that publishes ft)
+  const bool other = __syncthreads_or(wide || huge);   // (also the barrier that publishes ft)
   double V = vfar, Vc = 0.0;   // the two sums, split so that each part converts exactly
   neumaier_add(V, Vc, (double)(vacc[0] >> 32) * 0x1p6);
   neumaier_add(V, Vc, (double)(vacc[0] & 0xffffffffLL) * 0x1p-26);
   neumaier_add(V, Vc, (double)(vacc[2] >> 32) * 0x1p-38);
   neumaier_add(V, Vc, (double)(vacc[2] & 0xffffffffLL) * 0x1p-70);
-  V = wide ? __builtin_nan("") : V + Vc;
+  V += Vc;
+  if (other) {   // (V's integers are not all there)
+    wide = __syncthreads_or(wide);
+    if (!wide && wave == 0) {
+      const double v = ordered_energy(L, gtable, stride, nb, first, inv_w, d2far, x64);
+      if (lane == 0) *reinterpret_cast<double*>(vacc) = v;
+    }
+    __syncthreads();
+    V = wide ? __builtin_nan("") : *reinterpret_cast<const double*>(vacc);
+  }
   // suffix sums S_p, T_p (six components, one lane each, in chain order; eight residues
   // are read ahead of the additions, which alone are a chain)
   if (wave == 0 && lane < 6) {

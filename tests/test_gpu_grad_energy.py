@@ -42,3 +42,20 @@ def test_gradient_energies_keep_every_digit(L, scale):
     V, e = _flat_energy(L, scale * rng.random(P), 3.0 + rng.random(P))
     exact = math.fsum(e)
     assert abs(V - exact) <= np.spacing(abs(exact)) + P * 2.0**-71
+
+
+@pytest.mark.parametrize("L", [2, 9, 65, 130])
+@pytest.mark.parametrize("scale", [7e4, 1e10, 1e17, 1e30])
+def test_gradient_energies_of_any_size(L, scale):
+    """Finite energies far beyond those of a probability (walls), some pairs' and all: no numeric
+    error, the sum of Neumaier's compensated order (an ulp) and the same for every launch."""
+    gu.say("large energies of the gradient, L", L, "scale", scale)
+    rng = np.random.Generator(np.random.PCG64(L))
+    P = L * (L - 1) // 2
+    for share in (0.1, 1.0):
+        y0 = np.where(rng.random(P) < share, scale, 1.0) * (1.0 + rng.random(P))
+        y0[0] = scale
+        for B in (1, 600):
+            V, e = _flat_energy(L, y0, 3.0 + rng.random(P), B)
+            exact = math.fsum(e)
+            assert abs(V - exact) <= 2 * np.spacing(exact)
