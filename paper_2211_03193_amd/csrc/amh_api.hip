@@ -70,8 +70,10 @@ struct amh_ctx {
   double target = -INFINITY;
   // shape of the context (chains and wavefronts per workgroup)
   int G = 1, W = 4;
-  // sum of every table row's no-contact value (far_sum_kernel)
+  // sum of every table row's no-contact value (far_sum_kernel), and the largest deviation of an
+  // entry from it (ingest_kernel)
   double vfar = 0.0;
+  float dev_max = 0.0f;
   // launches of the localized-sweep kernel: chains [first, first + chains), G per workgroup
   struct LocalPart { int first = 0, chains = 0, G = 1, W = 4; };
   LocalPart local[2];
@@ -127,6 +129,14 @@ amh_status scratch_address(int dev, double** out) {
 }  // namespace
 
 namespace {
+
+// What the kernels of amh_init leave of a table: the context's error word and, read back once,
+// the rest.
+struct TableFacts {
+  unsigned int err;
+  float dev_max;
+  double vfar;
+};
 
 // n_cu: compute units of the device (for the automatic launch shape).
 amh_status validate(const amh_config* c, int n_cu, int* G, int* W) {
@@ -481,6 +491,7 @@ amh_status minimize_impl(amh_ctx* x, double* s_dev, int32_t B, const amh_lbfgs_o
   P.d_min = x->cfg.d_min;
   P.bin_w = x->cfg.bin_w;
   P.vfar = x->vfar;
+  P.ordered = amh::ordered_energies(x->dev_max);
   P.n_iter = o->n_iter;
   P.m = o->m;
   P.nonmonotone = o->nonmonotone;
@@ -564,7 +575,7 @@ amh_status amh_init(const amh_config* cfg, const float* y_dev, const double* s0_
   const size_t o_table = take(sizeof(float) * P * x->stride), o_ydev = take(sizeof(float) * (P + 1) * x->stride),
                o_s = take(sizeof(double) * C * n), o_best = take(sizeof(double) * C * n),
                o_atoms = take(sizeof(double) * C * L * 12), o_v = take(sizeof(double) * C * 2),
-               o_cnt = take(sizeof(int64_t) * C * 4), o_err = take(sizeof(unsigned int)), o_vfar = take(sizeof(double));
+               o_cnt = take(sizeof(int64_t) * C * 4), o_err = take(sizeof(TableFacts));
   if ((st = dev_alloc(&x->slab, used)) != AMH_OK) {
     free_ctx(x);
     return st;
@@ -577,7 +588,7 @@ amh_status amh_init(const amh_config* cfg, const float* y_dev, const double* s0_
   x->v = reinterpret_cast<double*>(x->slab + o_v);
   x->counters = reinterpret_cast<int64_t*>(x->slab + o_cnt);
   x->err = reinterpret_cast<unsigned int*>(x->slab + o_err);
-  hipError_t e = hipMemsetAsync(x->err, 0, sizeof(unsigned int), x->stream);
+  hipError_t e = hipMemsetAsync(x->err, 0, sizeof(TableFacts), x->stream);
   if (e == hipSuccess)   // row P of the deviation table is the zero row
     e = hipMemsetAsync(x->ydev + (size_t)P * x->stride, 0, sizeof(float) * x->stride, x->stream);
   if (e == hipSuccess) {
@@ -589,13 +600,15 @@ amh_status amh_init(const amh_config* cfg, const float* y_dev, const double* s0_
     e = hipGetLastError();
   }
   if (e == hipSuccess) {   // the energy of the all-far conformation, read back once
-    double* const d_vfar = reinterpret_cast<double*>(x->slab + o_vfar);
+    TableFacts* const facts = reinterpret_cast<TableFacts*>(x->err);
+    TableFacts got{};
     hipLaunchKernelGGL(amh::far_sum_kernel, dim3(1), dim3(512), 0, x->stream, x->table, P, x->stride,
-                       cfg->n_bins, d_vfar);
+                       cfg->n_bins, &facts->vfar);
     e = hipGetLastError();
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(&x->vfar, d_vfar, sizeof(double), hipMemcpyDeviceToHost, x->stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(&got, facts, sizeof(got), hipMemcpyDeviceToHost, x->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(x->stream);
+    x->vfar = got.vfar;
+    x->dev_max = got.dev_max;
   }
   if (e == hipSuccess && s0_dev)
     e = hipMemcpyAsync(x->s, s0_dev, sizeof(double) * C * n, hipMemcpyDeviceToDevice, x->stream);
@@ -857,6 +870,7 @@ amh_status amh_grad(amh_ctx* x, const double* s_dev, int32_t B, double* V_out_de
   P.d_min = x->cfg.d_min;
   P.bin_w = x->cfg.bin_w;
   P.vfar = x->vfar;
+  P.ordered = amh::ordered_energies(x->dev_max);
   P.V = V_out_dev;
   P.g = g_out_dev;
   P.err = x->err;

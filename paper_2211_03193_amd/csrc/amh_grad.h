@@ -25,6 +25,7 @@ struct GradParams {
   int stride, nb;
   double d_min, bin_w;
   double vfar;          // sum of every row's no-contact value
+  int ordered;          // V pair by pair (ordered_energies)
   int cap;              // pairs a wavefront's list holds
   double* V;            // [B] or null
   double* g;            // [B][2L] or null
@@ -38,6 +39,7 @@ struct LbfgsParams {
   int stride, nb;
   double d_min, bin_w;
   double vfar;          // sum of every row's no-contact value
+  int ordered;          // V pair by pair (ordered_energies)
   int cap;              // pairs a wavefront's list holds
   int n_iter, m, nonmonotone, max_ls;
   double c1, shrink, gtol, step0;
@@ -51,6 +53,11 @@ struct LbfgsParams {
   double* s_best;       // [B][2L], updated with v_state
   unsigned int* err;
 };
+
+// Whether a table whose entries deviate from their row's no-contact value by dev_max at most can
+// have a pair outside the range of value_grad's integer energy sums (|deviation| < 2^16; a
+// Catmull-Rom value is at most 1.25 times the largest of its four).
+inline bool ordered_energies(float dev_max) { return !(1.3 * (double)dev_max < 65536.0); }
 
 // A wavefront's list of cap pairs (a multiple of 8, 64 at least).
 __host__ __device__ inline size_t grad_pair_bytes(int cap) { return 10 * (size_t)cap + 640; }

@@ -120,13 +120,20 @@ __device__ double block_maxabs(const double* __restrict__ x, int n, double* red)
   return m;
 }
 
+// Adds x to s and what the addition rounds off to c (Knuth's two-sum).
+__device__ __forceinline__ void two_sum(double& s, double& c, double x) {
+  const double t = s + x, b = t - s;
+  c += (s - (t - b)) + (x - b);
+  s = t;
+}
+
 __device__ __forceinline__ double pair_dist2(double ex, double ey, double ez) {
   return fma(ez, ez, fma(ex, ex, ey * ey));
 }
 
 // V by one wavefront, pair by pair in a fixed order with Neumaier's compensation, of any finite
-// energies: for tables with a pair 2^16 nats or more from its no-contact value, which the
-// integer sums of value_grad do not hold.
+// energies: for tables whose pairs can be 2^16 nats or more from their no-contact value, which
+// the integer sums of value_grad do not hold.
 __device__ __attribute__((noinline)) double ordered_energy(int L, const gfloat* table, int stride, int nb,
                                                            double first, double inv_w, double d2far,
                                                            const double* x64) {
@@ -172,7 +179,8 @@ __device__ __attribute__((noinline)) double ordered_energy(int L, const gfloat* 
 //     u = (j - i) mod 64.  A list that its LDS does not hold is taken in ranges of u.
 // A tile's forces on a residue, rounded to multiples of 2^-44, and a pair's energy, in multiples of
 // 2^-26 and 2^-70, are added as integers: the totals do not depend on the order of the tiles or
-// on the launch shape.
+// on the launch shape.  `ordered` (of the table alone): V comes from
+// ordered_energy instead, and what is returned is a number unless it is NaN.
 // At 512 conformations of 400 residues (two workgroups of 4 wavefronts a unit, one pair in six
 // inside the last knot) the time goes to the sums (27 %), the marks (20 %), the coordinates
 // (19 %) and the evaluations (17 %): vector instructions, at two wavefronts a SIMD.  Evaluating
@@ -180,7 +188,7 @@ __device__ __attribute__((noinline)) double ordered_energy(int L, const gfloat* 
 // 291; one of 300 146, now 86; 1024 of 300 355, now 294; 128 of 200 minimised for 20
 // iterations 4.4 ms, now 2.2.
 __device__ double value_grad(const double* __restrict__ s, int L, const float* __restrict__ table,
-                             int stride, int nb, double d_min, double w, double vfar, double* x64, double* ft,
+                             int stride, int nb, double d_min, double w, double vfar, bool ordered, double* x64, double* ft,
                              float4* sph, unsigned char* pairs, int cap, long long* vacc,
                              double* __restrict__ g) {
   const int tid = threadIdx.x, T = blockDim.x, lane = tid & 63, wave = tid >> 6;
@@ -199,7 +207,6 @@ __device__ double value_grad(const double* __restrict__ s, int L, const float* _
   block_spheres(x64, L, sph);
   __syncthreads();
   bool wide = false;   // an item's sum beyond the integer range (or NaN): V is returned NaN
-  bool huge = false;   // a pair's deviation beyond the range of the energy's integers
   const int nb64 = (L + 63) >> 6, ntile = nb64 * (nb64 + 1) / 2;
   // this wavefront's list of a tile's pairs: dE/dd / d, the marks and list positions of its
   // rows, and the pairs themselves (row | u << 6)
@@ -317,8 +324,8 @@ __device__ double value_grad(const double* __restrict__ s, int L, const float* _
         spline64_ed((double)a.q0, (double)a.q1, (double)a.q2, (double)a.q3, a.t, a.b, nb, inv_w, E, dE);
         // deviation e + low from the no-contact value, exactly (Knuth's two-sum), in multiples
         // of 2^-26 and of 2^-70: every digit of a pair's energy down to these
-        const double qn = (double)a.qn, e = E - qn, z = e - E, low = (E - (e - z)) - (qn + z);
-        huge = huge || !(fabs(e) < 0x1p16);
+        double e = E, low = 0.0;
+        two_sum(e, low, -(double)a.qn);
         const double n = rint(e * 0x1p26);   // (sums of integers below 2^53)
         whole += n;
         part += rint((fma(n, -0x1p-26, e) + low) * 0x1p70);
@@ -382,7 +389,7 @@ __device__ double value_grad(const double* __restrict__ s, int L, const float* _
         lds_add(facc + 6 * j + 1, fixed44(cy));
         lds_add(facc + 6 * j + 2, fixed44(cz));
       }
-      if (!huge) {
+      if (!ordered) {
         lds_add(vacc, (long long)whole);
         lds_add(vacc + 2, (long long)part);
       }
@@ -401,22 +408,12 @@ __device__ double value_grad(const double* __restrict__ s, int L, const float* _
     o[4] = kz * fx - kx * fz;
     o[5] = kx * fy - ky * fx;
   }
-  const bool other = __syncthreads_or(wide || huge);   // (also the barrier that publishes ft)
-  double V = vfar, Vc = 0.0;   // the two sums, split so that each part converts exactly
-  neumaier_add(V, Vc, (double)(vacc[0] >> 32) * 0x1p6);
-  neumaier_add(V, Vc, (double)(vacc[0] & 0xffffffffLL) * 0x1p-26);
-  neumaier_add(V, Vc, (double)(vacc[2] >> 32) * 0x1p-38);
-  neumaier_add(V, Vc, (double)(vacc[2] & 0xffffffffLL) * 0x1p-70);
-  V += Vc;
-  if (other) {   // (V's integers are not all there)
-    wide = __syncthreads_or(wide);
-    if (!wide && wave == 0) {
-      const double v = ordered_energy(L, gtable, stride, nb, first, inv_w, d2far, x64);
-      if (lane == 0) *reinterpret_cast<double*>(vacc) = v;
-    }
-    __syncthreads();
-    V = wide ? __builtin_nan("") : *reinterpret_cast<const double*>(vacc);
-  }
+  wide = __syncthreads_or(wide);   // (also the barrier that publishes ft)
+  // far constant and the two sums; the first is split so that both parts convert exactly
+  double V = vfar, Vc = (double)vacc[2] * 0x1p-70;
+  two_sum(V, Vc, (double)(vacc[0] >> 32) * 0x1p6);
+  two_sum(V, Vc, (double)(vacc[0] & 0xffffffffLL) * 0x1p-26);
+  V = wide ? __builtin_nan("") : V + Vc;
   // suffix sums S_p, T_p (six components, one lane each, in chain order; eight residues
   // are read ahead of the additions, which alone are a chain)
   if (wave == 0 && lane < 6) {
@@ -471,6 +468,27 @@ __device__ double value_grad(const double* __restrict__ s, int L, const float* _
   return V;
 }
 
+// value_grad for a kernel whose parameters are P; V by ordered_energy where the table asks for it
+// (called from here and not from value_grad, which a call would cost 2 % of a minimisation).
+template <class Params>
+__device__ __forceinline__ double evaluate(const Params& P, const double* s, double* x64, double* ft, float4* sph,
+                                           unsigned char* pairs, double* red, double* g) {
+  double V = value_grad(s, P.L, P.table, P.stride, P.nb, P.d_min, P.bin_w, P.vfar, P.ordered, x64, ft, sph, pairs, P.cap,
+                        reinterpret_cast<long long*>(red), g);
+  if (P.ordered && V == V) {
+    if (threadIdx.x < 64) {
+      const double dfar = P.d_min + P.bin_w * ((double)P.nb - 0.5);
+      const double v = ordered_energy(P.L, (const gfloat*)P.table, P.stride, P.nb, P.d_min + 0.5 * P.bin_w,
+                                      1.0 / P.bin_w, dfar * dfar, x64);
+      if (threadIdx.x == 0) red[0] = v;
+    }
+    __syncthreads();
+    V = red[0];
+    __syncthreads();
+  }
+  return V;
+}
+
 // ---------------------------------------------------------------------------
 // Both kernels are held to two wavefronts per SIMD (at most 256 registers a lane).
 // Left free, the compiler gives the NeRF scan 271 registers and every kernel one wavefront
@@ -485,9 +503,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) g
   unsigned char* pairs = reinterpret_cast<unsigned char*>(sph + ((L + 7) >> 3));
   double* red = reinterpret_cast<double*>(pairs + (blockDim.x >> 6) * grad_pair_bytes(P.cap));
   const int b = blockIdx.x;
-  const double V = value_grad(P.s + (size_t)b * 2 * L, L, P.table, P.stride, P.nb, P.d_min,
-                              P.bin_w, P.vfar, x64, ft, sph, pairs, P.cap, reinterpret_cast<long long*>(red),
-                              P.g ? P.g + (size_t)b * 2 * L : nullptr);
+  const double V = evaluate(P, P.s + (size_t)b * 2 * L, x64, ft, sph, pairs, red, P.g ? P.g + (size_t)b * 2 * L : nullptr);
   if (threadIdx.x == 0) {
     if (!isfinite(V)) atomicOr(P.err, kErrGradEnergy);
     if (P.V) P.V[b] = V;
@@ -527,8 +543,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) l
     if (xtr) xtr[e] = sb[e];
   }
   __syncthreads();
-  double f = value_grad(x, L, P.table, P.stride, P.nb, P.d_min, P.bin_w, P.vfar, x64, ft, sph, pairs, P.cap,
-                        reinterpret_cast<long long*>(red), g);
+  double f = evaluate(P, x, x64, ft, sph, pairs, red, g);
   if (trace && tid == 0) trace[0] = f;
   if (tid == 0) fh[0] = f;
   int k = 0, head = 0, nf = 1, it = 0, status = 1;
@@ -589,8 +604,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) l
     for (int ls = 0; ls < P.max_ls; ++ls) {
       for (int e = tid; e < n; e += T) xn[e] = x[e] + alpha * d[e];
       __syncthreads();
-      fnew = value_grad(xn, L, P.table, P.stride, P.nb, P.d_min, P.bin_w, P.vfar, x64, ft, sph, pairs, P.cap,
-                        reinterpret_cast<long long*>(red), gn);
+      fnew = evaluate(P, xn, x64, ft, sph, pairs, red, gn);
       if (fnew <= fref + P.c1 * alpha * gd) { ok = true; break; }
       alpha *= P.shrink;
     }

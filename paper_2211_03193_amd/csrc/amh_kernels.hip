@@ -26,11 +26,13 @@ namespace amh {
 // ---------------------------------------------------------------------------
 // Table ingest: repack [P][nb] rows into padded rows [y1, y0..y_{nb-1}, y_{nb-2}, 0...]
 // (`out`) and the same rows minus the row's no-contact value y_{nb-1} (`dev`, rounded
-// once from float64), and flag non-finite entries.
+// once from float64), flag non-finite entries in err[0] and raise err[1] to the bits of the
+// largest magnitude in `dev`.
 __global__ void ingest_kernel(const float* __restrict__ y, int64_t P, int nb, int stride,
                               float* __restrict__ out, float* __restrict__ dev, unsigned int* err) {
   const int64_t n = P * (int64_t)stride;
   bool bad = false;
+  float most = 0.0f;
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n;
        e += (int64_t)gridDim.x * blockDim.x) {
     const int64_t r = e / stride;
@@ -41,9 +43,13 @@ __global__ void ingest_kernel(const float* __restrict__ y, int64_t P, int nb, in
     else if (c == nb + 1) v = y[r * nb + (nb - 2)];
     if (c <= nb && !isfinite(v)) bad = true;
     out[e] = v;
-    dev[e] = c <= nb + 1 ? (float)((double)v - (double)y[r * nb + (nb - 1)]) : 0.0f;
+    const float d = c <= nb + 1 ? (float)((double)v - (double)y[r * nb + (nb - 1)]) : 0.0f;
+    dev[e] = d;
+    most = fmaxf(most, fabsf(d));
   }
   if (bad) atomicOr(err, kErrTable);
+  for (int o = 32; o > 0; o >>= 1) most = fmaxf(most, __shfl_xor(most, o, 64));
+  if ((threadIdx.x & 63) == 0) atomicMax(err + 1, __float_as_uint(most));
 }
 
 // Noisy restart: s_k += amplitude (2u - 1) with u from Philox at (k, tag, chain, 1),
