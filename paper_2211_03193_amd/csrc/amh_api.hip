@@ -389,13 +389,28 @@ const void* global_fn(int nw, bool batch) {
   }
 }
 
-const void* local_fn(int G, bool batch) {
+template <int G, bool CARRY>
+const void* local_fn(bool batch) {
+  return batch ? (const void*)amh::local_batch_kernel<G, CARRY> : (const void*)amh::local_kernel<G, CARRY>;
+}
+
+const void* local_fn(int G, bool carry, bool batch) {
   switch (G) {
-    case 1: return batch ? (const void*)amh::local_batch_kernel<1> : (const void*)amh::local_kernel<1>;
-    case 2: return batch ? (const void*)amh::local_batch_kernel<2> : (const void*)amh::local_kernel<2>;
-    default: return batch ? (const void*)amh::local_batch_kernel<4> : (const void*)amh::local_kernel<4>;
+    case 1: return carry ? local_fn<1, true>(batch) : local_fn<1, false>(batch);
+    case 2: return carry ? local_fn<2, true>(batch) : local_fn<2, false>(batch);
+    default: return carry ? local_fn<4, true>(batch) : local_fn<4, false>(batch);
   }
 }
+
+// The widest half-width of a context's localized sweeps.
+int widest(const amh_ctx* x) {
+  int h = amh::half_window(x->cfg.window_d, x->cfg.L);
+  for (int i = 0; i < x->cfg.n_cascade; ++i) h = std::max(h, amh::half_window(x->cfg.cascade_d[i], x->cfg.L));
+  return h;
+}
+
+// Whether localized launches carry this context's energies along.
+bool carries(const amh_ctx* x) { return amh::carry_exact(widest(x), x->dev_max); }
 
 // Wavefronts of a localized launch: kLocalWaves where their LDS fits, else W.
 int local_waves(int G, int L, int W) { return amh::local_lds_bytes(G, L, kLocalWaves) <= kMaxLds ? kLocalWaves : W; }
@@ -662,7 +677,7 @@ amh_status amh_sweep(amh_ctx* x, int64_t n_sweeps) {
       const auto& l = x->local[i];
       P.chain0 = l.first;
       P.C = l.first + l.chains;
-      st = launch(local_fn(l.G, false), dim3((l.chains + l.G - 1) / l.G), 64 * l.W,
+      st = launch(local_fn(l.G, carries(x), false), dim3((l.chains + l.G - 1) / l.G), 64 * l.W,
                   amh::local_lds_bytes(l.G, c.L, l.W), x->stream, P);
     }
     P.C = c.n_chains;
@@ -929,6 +944,7 @@ struct amh_batch {
   struct Launch {
     int G = 1, W = 4;
     int W_local = 4, W_global = 4;   // wavefronts of a localized and a global launch
+    bool carry = false;              // localized launches carry their energies along
     size_t lds_local = 0, lds_global = 0, lds_anchor = 0;   // of the longest member
     int anchor_threads = 256;
     int n_wg = 0;
@@ -999,11 +1015,13 @@ amh_status build_launches(amh_batch* b, int plan) {
     l.W = shapes[s].second;
     int longest = 2;
     bool automatic = true;   // no member has a shape of its caller's choice
+    bool exact = true;       // every member's energies can be carried along
     std::vector<std::pair<double, int2>> items;
     for (size_t i = 0; i < b->m.size(); ++i) {
       if (shape_of[i] != (int)s) continue;
       const amh_ctx* x = b->m[i];
       longest = std::max(longest, x->cfg.L);
+      exact = exact && carries(x);
       automatic = automatic && x->cfg.chains_per_group == 0 && x->cfg.waves_per_group == 0;
       const int groups = (x->cfg.n_chains + l.G - 1) / l.G;
       for (int g = 0; g < groups; ++g) items.push_back({member_cost(x), make_int2((int)i, g)});
@@ -1013,6 +1031,7 @@ amh_status build_launches(amh_batch* b, int plan) {
     std::vector<int2> map;
     for (auto& it : items) map.push_back(it.second);
     l.n_wg = (int)map.size();
+    l.carry = exact;
     l.W_local = local_waves(l.G, longest, l.W);
     l.lds_local = amh::local_lds_bytes(l.G, longest, l.W_local);
     // (single-chain groups of the contexts' own shapes share the units with all the batch)
@@ -1037,7 +1056,7 @@ amh_status launch_step(const amh_batch* b, Step kind, const amh::SweepParams* de
     const int2* map = l.d_map;
     const int G = l.G, nw = global_waves(l.G, l.W_global);
     const amh_status st =
-        kind == Step::local ? launch(local_fn(G, true), dim3(l.n_wg), 64 * l.W_local, l.lds_local, b->stream, descs, map)
+        kind == Step::local ? launch(local_fn(G, l.carry, true), dim3(l.n_wg), 64 * l.W_local, l.lds_local, b->stream, descs, map)
         : kind == Step::global
             ? launch(global_fn(nw, true), dim3(l.n_wg), 64 * l.W_global, l.lds_global, b->stream, descs, map, G)
             : launch((const void*)amh::anchor_batch_kernel, dim3(l.n_wg, G), l.anchor_threads, l.lds_anchor, b->stream,

@@ -66,6 +66,17 @@ struct D3 { double x, y, z; };
 __device__ __forceinline__ D3 ld3(const double* p) { return D3{p[0], p[1], p[2]}; }
 __device__ __forceinline__ void st3(double* p, D3 v) { p[0] = v.x; p[1] = v.y; p[2] = v.z; }
 
+// A row of a 3x3 matrix times a vector, and the same plus an offset.  Here and in the rotations
+// below the order of the fused operations is written out (which product the compiler would
+// round on its own depends on the code around it): every kernel, whatever its launch shape,
+// builds the same coordinates, bit for bit.
+__device__ __forceinline__ double row3(const double* m, double x, double y, double z) {
+  return fma(m[2], z, fma(m[0], x, m[1] * y));
+}
+__device__ __forceinline__ double row3(double o, const double* m, double x, double y, double z) {
+  return fma(m[2], z, fma(m[1], y, fma(m[0], x, o)));
+}
+
 // Rotation by angle (c, s) about the unit axis through `a` along B - A (float64).
 struct Rot {
   double r[9];
@@ -81,43 +92,31 @@ __device__ __forceinline__ double rsqrt64(double x) {
   return y;
 }
 
-__device__ __forceinline__ void make_rot(D3 A, D3 B, double c, double s, Rot& R) {
-  double ux = B.x - A.x, uy = B.y - A.y, uz = B.z - A.z;
-  const double inv = rsqrt64(ux * ux + uy * uy + uz * uz);
-  ux *= inv; uy *= inv; uz *= inv;
-  const double t = 1.0 - c;
-  R.r[0] = c + t * ux * ux;      R.r[1] = t * ux * uy - s * uz; R.r[2] = t * ux * uz + s * uy;
-  R.r[3] = t * uy * ux + s * uz; R.r[4] = c + t * uy * uy;      R.r[5] = t * uy * uz - s * ux;
-  R.r[6] = t * uz * ux - s * uy; R.r[7] = t * uz * uy + s * ux; R.r[8] = c + t * uz * uz;
-  R.a[0] = A.x; R.a[1] = A.y; R.a[2] = A.z;
-}
-
 // Rotation by angle (c, s) about the unit axis u through the point A.
 __device__ __forceinline__ void make_rot_u(D3 A, D3 u, double c, double s, Rot& R) {
-  const double t = 1.0 - c;
-  R.r[0] = c + t * u.x * u.x;       R.r[1] = t * u.x * u.y - s * u.z; R.r[2] = t * u.x * u.z + s * u.y;
-  R.r[3] = t * u.y * u.x + s * u.z; R.r[4] = c + t * u.y * u.y;       R.r[5] = t * u.y * u.z - s * u.x;
-  R.r[6] = t * u.z * u.x - s * u.y; R.r[7] = t * u.z * u.y + s * u.x; R.r[8] = c + t * u.z * u.z;
+  const double t = 1.0 - c, tx = t * u.x, ty = t * u.y, tz = t * u.z, sx = s * u.x, sy = s * u.y, sz = s * u.z;
+  R.r[0] = fma(tx, u.x, c);  R.r[1] = fma(tx, u.y, -sz); R.r[2] = fma(tx, u.z, sy);
+  R.r[3] = fma(ty, u.x, sz); R.r[4] = fma(ty, u.y, c);   R.r[5] = fma(ty, u.z, -sx);
+  R.r[6] = fma(tz, u.x, -sy); R.r[7] = fma(tz, u.y, sx); R.r[8] = fma(tz, u.z, c);
   R.a[0] = A.x; R.a[1] = A.y; R.a[2] = A.z;
 }
 
 __device__ __forceinline__ D3 unit(D3 A, D3 B) {
   const double ux = B.x - A.x, uy = B.y - A.y, uz = B.z - A.z;
-  const double inv = rsqrt64(ux * ux + uy * uy + uz * uz);
+  const double inv = rsqrt64(fma(uz, uz, fma(ux, ux, uy * uy)));
   return D3{ux * inv, uy * inv, uz * inv};
 }
 
+__device__ __forceinline__ void make_rot(D3 A, D3 B, double c, double s, Rot& R) { make_rot_u(A, unit(A, B), c, s, R); }
+
 // R v for a direction v (no translation).
 __device__ __forceinline__ D3 rot_dir(const Rot& R, D3 v) {
-  return D3{R.r[0] * v.x + R.r[1] * v.y + R.r[2] * v.z, R.r[3] * v.x + R.r[4] * v.y + R.r[5] * v.z,
-            R.r[6] * v.x + R.r[7] * v.y + R.r[8] * v.z};
+  return D3{row3(R.r, v.x, v.y, v.z), row3(R.r + 3, v.x, v.y, v.z), row3(R.r + 6, v.x, v.y, v.z)};
 }
 
 // R (x - a): the rotated position relative to the pivot point.
 __device__ __forceinline__ D3 rot_rel(const Rot& R, D3 x) {
-  const double vx = x.x - R.a[0], vy = x.y - R.a[1], vz = x.z - R.a[2];
-  return D3{R.r[0] * vx + R.r[1] * vy + R.r[2] * vz, R.r[3] * vx + R.r[4] * vy + R.r[5] * vz,
-            R.r[6] * vx + R.r[7] * vy + R.r[8] * vz};
+  return rot_dir(R, D3{x.x - R.a[0], x.y - R.a[1], x.z - R.a[2]});
 }
 
 __device__ __forceinline__ D3 apply_rot(const Rot& R, D3 x) {

@@ -38,15 +38,6 @@ __device__ __forceinline__ const double* atom(const double* x64, int r, int a) {
 //
 // x64 [12L] and fr [nerf_scratch(L)] are in LDS, s [2L] anywhere; s is complete (a barrier
 // if the workgroup wrote it) and nobody uses fr; ends with a barrier of the workgroup.
-// A row of a 3x3 matrix times a vector, and the same plus an offset, with the order of the
-// fused operations written out: every kernel builds the same coordinates, bit for bit.
-__device__ __forceinline__ double row3(const double* m, double x, double y, double z) {
-  return fma(m[2], z, fma(m[0], x, m[1] * y));
-}
-__device__ __forceinline__ double row3(double o, const double* m, double x, double y, double z) {
-  return fma(m[2], z, fma(m[1], y, fma(m[0], x, o)));
-}
-
 __host__ __device__ inline int nerf_scratch(int L) { return 12 * ((3 * (L - 1) + 63) / 64); }
 
 __device__ inline void nerf_wg(const double* __restrict__ s, int L, double* __restrict__ x64,

@@ -208,8 +208,7 @@ __device__ __forceinline__ void global_body(CParams& P, const int group, const i
       const Batch b = hs->batch[kn & 63];
       Rot R;
       if (prev) R = get(prev);
-      const D3 q{A[0] * x + A[1] * y + A[2] * z + A[9], A[3] * x + A[4] * y + A[5] * z + A[10],
-                 A[6] * x + A[7] * y + A[8] * z + A[11]};
+      const D3 q{row3(A, x, y, z) + A[9], row3(A + 3, x, y, z) + A[10], row3(A + 6, x, y, z) + A[11]};
       if (done >= 0 && lane >= 4 && lane < 7) st3(atom(gatoms, done, lane - 4), q);
       if (kn >= n) return;
       D3 a{readlane_d(q.x, 0), readlane_d(q.y, 0), readlane_d(q.z, 0)};
@@ -496,7 +495,7 @@ __device__ __forceinline__ void global_body(CParams& P, const int group, const i
           if (q == 3) { v0 -= R.a[0]; v1 -= R.a[1]; v2 -= R.a[2]; }
           double w[3];
 #pragma unroll
-          for (int r = 0; r < 3; ++r) w[r] = R.r[3 * r] * v0 + R.r[3 * r + 1] * v1 + R.r[3 * r + 2] * v2;
+          for (int r = 0; r < 3; ++r) w[r] = row3(R.r + 3 * r, v0, v1, v2);
           if (q == 3) { w[0] += R.a[0]; w[1] += R.a[1]; w[2] += R.a[2]; }
           wave_sync();
           if (lane < 4) { A[q < 3 ? q : 9] = w[0]; A[q < 3 ? 3 + q : 10] = w[1]; A[q < 3 ? 6 + q : 11] = w[2]; }

@@ -94,6 +94,16 @@ inline int64_t run_end(const SweepParams& P, int64_t t, int64_t end) {
   return e;
 }
 
+// Whether localized sweeps of half-width h (the widest, where several are taken in turn) can carry
+// the energy of their changed pairs along as one float64 count of 2^-30: it has to be exact, below
+// 2^53, through every proposal, whatever the chain does, with a table whose entries deviate from
+// their row's no-contact value by dev_max at most (a Catmull-Rom value is at most 1.25 times the
+// largest of its four).  A wall of 1e15 nats would leave a nat's error in all energy changes.
+inline bool carry_exact(int h, float dev_max) {
+  const double pairs = (h + 1.0) * (h + 1.0) + 2.0 * h + 1.0;
+  return pairs * 1.3 * (double)dev_max < 8388608.0;
+}
+
 // Half-width of a localization radius d >= 0 in a chain of L residues.  The window [max(0, c - h),
 // min(L - 1, c + h)] is the whole chain from h = L - 1 on, so a wider one is cut to it: the
 // kernels' loops and sums of half-widths (c + 2h, 4h) stay within a few L whatever the d.
@@ -129,10 +139,11 @@ __global__ void perturb_kernel(double* s, int64_t n_total, int n, uint32_t chain
                                uint32_t k0, uint32_t k1, double amplitude);
 __global__ void anchor_kernel(SweepParams P);
 __global__ void anchor_batch_kernel(const SweepParams* descs, const int2* map, int G);
-// localized sweeps: G chains per workgroup, any number of wavefronts (<= 12)
-template <int G>
+// localized sweeps: G chains per workgroup, any number of wavefronts (<= 12); CARRY: the energy
+// of the changed pairs is carried from proposal to proposal (carry_exact)
+template <int G, bool CARRY>
 __global__ void local_kernel(SweepParams P);
-template <int G>
+template <int G, bool CARRY>
 __global__ void local_batch_kernel(const SweepParams* descs, const int2* map);
 // global sweeps: G chains per workgroup, NW wavefronts each (1, 2, 4, 8 or 16)
 template <int NW>

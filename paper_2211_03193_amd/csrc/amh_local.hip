@@ -147,8 +147,10 @@ __device__ __attribute__((noinline)) Batch draw(CParams* P, int k, uint32_t t, u
 }
 
 // One localized sweep of the workgroup's chains (G of them, nact active) by one
-// wavefront, with no workgroup barrier inside.
-template <int G>
+// wavefront, with no workgroup barrier inside.  CARRY: the energy of the changed pairs is carried
+// from proposal to proposal (carry_exact), else each energy change is summed pair by pair; both
+// give the same bits where the carried sum is exact.
+template <int G, bool CARRY>
 __device__ __forceinline__ void local_sweep(CParams& P, const Lds& S, int nact, int c0, int64_t t, double beta, int h,
                                             int h_prev, int lane, int slot, int& n_acc, const Pipe& pipe,
                                             bool& stalled) {
@@ -227,9 +229,10 @@ __device__ __forceinline__ void local_sweep(CParams& P, const Lds& S, int nact, 
     if (pipe.wait_on) {
       // the previous sweep (half-width h_prev) must be done with every proposal that reads
       // residue c + h: those of residues up to c' = c + h + h_prev, whose windows reach it,
-      // and phi of the next one, which takes the pairs of the row before its window away
-      const int need = (pipe.m - 1) * 4096 +
-                       (2 * (c + h + h_prev) + 3 < n ? 2 * (c + h + h_prev) + 3 : n);
+      // and with carries phi of the next one, which takes the pairs of the row before its window
+      // away
+      const int ahead = 2 * (c + h + h_prev) + (CARRY ? 3 : 2);
+      const int need = (pipe.m - 1) * 4096 + (ahead < n ? ahead : n);
       if (seen < need) seen = wait_progress(P, pipe.wait_on, need, stalled);
     }
     if (!odd && c > 0) {
@@ -240,9 +243,9 @@ __device__ __forceinline__ void local_sweep(CParams& P, const Lds& S, int nact, 
         double* const x = ll < 3 ? bb + 3 * (3 * c + ll) : cb + hi;
         const int step = ll < 3 ? 1 : L;
         const double X = x[0], Y = x[step], Z = x[2 * step];
-        x[0] = A[0] * X + A[1] * Y + A[2] * Z + tb[0];
-        x[step] = A[3] * X + A[4] * Y + A[5] * Z + tb[1];
-        x[2 * step] = A[6] * X + A[7] * Y + A[8] * Z + tb[2];
+        x[0] = row3(A, X, Y, Z) + tb[0];
+        x[step] = row3(A + 3, X, Y, Z) + tb[1];
+        x[2 * step] = row3(A + 6, X, Y, Z) + tb[2];
       }
       wave_sync();
     }
@@ -262,72 +265,107 @@ __device__ __forceinline__ void local_sweep(CParams& P, const Lds& S, int nact, 
       const int nF = p - lo, nM = hi - p + 1;
       const double* ax = bb + 3 * (3 * c + odd);   // phi_c: N_c -> CA_c; psi_c: CA_c -> C_c
       double str = 0.0;
-      if (!known[odd] || !(interior || narrow)) {
-        deal(c, odd, narrow ? c - h : lo, narrow ? c + h : hi);
-        known[odd] = interior || narrow;
-      }
-      int u = carry[odd], w = column[odd];
-      if (!interior && narrow) {
-        if (c < (u & 2047) || c + ((u >> 11) & 2047) > hi) u = 0;
-        const int out = ((w >> 10) & 2047) - c;   // rows before the chain's first residue
-        if (out > 0) w -= out << 21 | out << 10;
-        if (w < 0 || c + (w & 1023) > hi) w = 0;
-      }
-      if (one[odd]) {
-        // every pair in a lane of its own: 3 = changed, 1 and 2 = carries, taken off and added
-        const int kind = u >> 22, i = c - (u & 2047), j = c + ((u >> 11) & 2047);
-        const D3 xi = ldx(i), xj = ldx(j);
-        make_rot(ld3(ax), ld3(ax + 3), cd, sd, Rk);
-        const D3 xr = apply_rot(Rk, xj);
-        const D3 y{kind == 3 ? xr.x : xj.x, kind == 3 ? xr.y : xj.y, kind == 3 ? xr.z : xj.z};
-        float4 e;
-        float fr;
-        gather((unsigned)pair_row(i, j, L), kind != 0 ? dist2_64(xi, y) : __builtin_inff(), e, fr);
-        const float v = rintf(catmull_rom(e.x, e.y, e.z, e.w, fr) * 1073741824.0f);
-        snew = (double)(kind == 3 ? v : 0.0f);
-        str = (double)(kind == 3 ? 0.0f : kind == 1 ? -v : v);
-      } else {
-        // the carries, at their current distance: their gathers overlap the rotation's set-up
-        float4 te;
-        float tf;
-        auto carry_load = [&]() {
-          const int i = c - (u & 2047), j = c + ((u >> 11) & 2047);
-          gather((unsigned)pair_row(i, j, L), u >> 22 ? dist2_64(ldx(i), ldx(j)) : __builtin_inff(), te, tf);
-        };
-        auto carry_add = [&]() {
-          const float v = rintf(catmull_rom(te.x, te.y, te.z, te.w, tf) * 1073741824.0f);
-          str += (double)(u >> 22 == 1 ? -v : v);
-        };
-        carry_load();
-        make_rot(ld3(ax), ld3(ax + 3), cd, sd, Rk);
-        // the changed pairs: a lane has one column (turned once) and some rows of it
-        int rows = nrow[odd];
-        for (int b0 = 0;;) {
-          const int j = c + (w & 1023), i0 = c - ((w >> 10) & 2047), i1 = i0 + (w >> 21);
-          const D3 xj = apply_rot(Rk, ldx(j));
-          for (int r0 = 0; r0 < rows; r0 += R) {
-            float4 e[R];
-            float fr[R];
+      if constexpr (!CARRY) {
+        // the changed pairs (lo + a, p + b), pair x = a nM + b in slot x / LW of lane x mod LW, at
+        // the distance they have and at the proposed one
+        const int npair = nF > 0 && nM > 0 ? nF * nM : 0;
+        // (hardware reciprocal, 1 ulp: floor((x + 1/2) / nM) stays exact for x < 2^22)
+        const float inv_nM = __builtin_amdgcn_rcpf((float)(nM > 0 ? nM : 1));
+        for (int x0 = 0; x0 == 0 || x0 < npair; x0 += LW * R) {
+          int row[R], col[R];
+          float4 e0[R], e1[R];
+          float f0[R], f1[R];
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-              const int i = i0 + r0 + r;
-              const bool use = i < i1;
-              const int ii = use ? i : c;
-              gather((unsigned)pair_row(ii, j, L), use ? dist2_64(ldx(ii), xj) : __builtin_inff(), e[r], fr[r]);
-            }
-            if (b0 + r0 == 0) carry_add();
-#pragma unroll
-            for (int r = 0; r < R; ++r)
-              snew += fixed30_units(catmull_rom(e[r].x, e[r].y, e[r].z, e[r].w, fr[r]));
+          for (int r = 0; r < R; ++r) {
+            const int x = x0 + r * LW + ll, a = (int)(((float)x + 0.5f) * inv_nM);
+            const bool use = x < npair;
+            row[r] = use ? lo + a : -1;
+            col[r] = use ? p + (x - a * nM) : c;
+            const int i = use ? row[r] : c;
+            gather((unsigned)pair_row(i, col[r], L),
+                   use ? dist2_64(ldx(i), ldx(col[r])) : __builtin_inff(), e0[r], f0[r]);
           }
-          b0 += LW;
-          if (b0 >= nM) break;
-          w = deal_column(c, odd, lo, hi, b0, rows);
+          if (x0 == 0) make_rot(ld3(ax), ld3(ax + 3), cd, sd, Rk);
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            const bool use = row[r] >= 0;
+            const int i = use ? row[r] : c;
+            gather((unsigned)pair_row(i, col[r], L),
+                   use ? dist2_64(ldx(i), apply_rot(Rk, ldx(col[r]))) : __builtin_inff(), e1[r], f1[r]);
+          }
+#pragma unroll
+          for (int r = 0; r < R; ++r)
+            snew += fixed30_units(catmull_rom(e1[r].x, e1[r].y, e1[r].z, e1[r].w, f1[r])) -
+                    fixed30_units(catmull_rom(e0[r].x, e0[r].y, e0[r].z, e0[r].w, f0[r]));
         }
-        for (int y = LW; y < (odd ? 2 * h : 2 * h + 1); y += LW) {
-          u = deal_carry(c, odd, lo, hi, y + ll);
+      } else {
+        if (!known[odd] || !(interior || narrow)) {
+          deal(c, odd, narrow ? c - h : lo, narrow ? c + h : hi);
+          known[odd] = interior || narrow;
+        }
+        int u = carry[odd], w = column[odd];
+        if (!interior && narrow) {
+          if (c < (u & 2047) || c + ((u >> 11) & 2047) > hi) u = 0;
+          const int out = ((w >> 10) & 2047) - c;   // rows before the chain's first residue
+          if (out > 0) w -= out << 21 | out << 10;
+          if (w < 0 || c + (w & 1023) > hi) w = 0;
+        }
+        if (one[odd]) {
+          // every pair in a lane of its own: 3 = changed, 1 and 2 = carries, taken off and added
+          const int kind = u >> 22, i = c - (u & 2047), j = c + ((u >> 11) & 2047);
+          const D3 xi = ldx(i), xj = ldx(j);
+          make_rot(ld3(ax), ld3(ax + 3), cd, sd, Rk);
+          const D3 xr = apply_rot(Rk, xj);
+          const D3 y{kind == 3 ? xr.x : xj.x, kind == 3 ? xr.y : xj.y, kind == 3 ? xr.z : xj.z};
+          float4 e;
+          float fr;
+          gather((unsigned)pair_row(i, j, L), kind != 0 ? dist2_64(xi, y) : __builtin_inff(), e, fr);
+          const float v = rintf(catmull_rom(e.x, e.y, e.z, e.w, fr) * 1073741824.0f);
+          snew = (double)(kind == 3 ? v : 0.0f);
+          str = (double)(kind == 3 ? 0.0f : kind == 1 ? -v : v);
+        } else {
+          // the carries, at their current distance: their gathers overlap the rotation's set-up
+          float4 te;
+          float tf;
+          auto carry_load = [&]() {
+            const int i = c - (u & 2047), j = c + ((u >> 11) & 2047);
+            gather((unsigned)pair_row(i, j, L), u >> 22 ? dist2_64(ldx(i), ldx(j)) : __builtin_inff(), te, tf);
+          };
+          auto carry_add = [&]() {
+            const float v = rintf(catmull_rom(te.x, te.y, te.z, te.w, tf) * 1073741824.0f);
+            str += (double)(u >> 22 == 1 ? -v : v);
+          };
           carry_load();
-          carry_add();
+          make_rot(ld3(ax), ld3(ax + 3), cd, sd, Rk);
+          // the changed pairs: a lane has one column (turned once) and some rows of it
+          int rows = nrow[odd];
+          for (int b0 = 0;;) {
+            const int j = c + (w & 1023), i0 = c - ((w >> 10) & 2047), i1 = i0 + (w >> 21);
+            const D3 xj = apply_rot(Rk, ldx(j));
+            for (int r0 = 0; r0 < rows; r0 += R) {
+              float4 e[R];
+              float fr[R];
+  #pragma unroll
+              for (int r = 0; r < R; ++r) {
+                const int i = i0 + r0 + r;
+                const bool use = i < i1;
+                const int ii = use ? i : c;
+                gather((unsigned)pair_row(ii, j, L), use ? dist2_64(ldx(ii), xj) : __builtin_inff(), e[r], fr[r]);
+              }
+              if (b0 + r0 == 0) carry_add();
+  #pragma unroll
+              for (int r = 0; r < R; ++r)
+                snew += fixed30_units(catmull_rom(e[r].x, e[r].y, e[r].z, e[r].w, fr[r]));
+            }
+            b0 += LW;
+            if (b0 >= nM) break;
+            w = deal_column(c, odd, lo, hi, b0, rows);
+          }
+          for (int y = LW; y < (odd ? 2 * h : 2 * h + 1); y += LW) {
+            u = deal_carry(c, odd, lo, hi, y + ll);
+            carry_load();
+            carry_add();
+          }
         }
       }
       pair_sums<LW>(act ? snew : 0.0, act ? str : 0.0, lane, snew, str);
@@ -343,7 +381,7 @@ __device__ __forceinline__ void local_sweep(CParams& P, const Lds& S, int nact, 
       if (ll == 0) s[k] = wrap_angle(s[k] + delta);
       ++n_acc;
       if (live) {
-        sum = snew;
+        if constexpr (CARRY) sum = snew;
         // rotate the C-betas of the window that the torsion moves, and for phi_c also C_c
         // (which leaves N_c and CA_c in place); further residues follow when they are reached
         const int nat = hi - p + 1 + (odd ? 0 : 1);
@@ -359,9 +397,9 @@ __device__ __forceinline__ void local_sweep(CParams& P, const Lds& S, int nact, 
         for (int r = 0; r < 3; ++r) {
 #pragma unroll
           for (int qq = 0; qq < 3; ++qq)
-            nA[3 * r + qq] = Rk.r[3 * r] * A[qq] + Rk.r[3 * r + 1] * A[3 + qq] + Rk.r[3 * r + 2] * A[6 + qq];
-          nb[r] = Rk.r[3 * r] * (tb[0] - Rk.a[0]) + Rk.r[3 * r + 1] * (tb[1] - Rk.a[1]) +
-                  Rk.r[3 * r + 2] * (tb[2] - Rk.a[2]) + Rk.a[r];
+            nA[3 * r + qq] = row3(Rk.r + 3 * r, A[qq], A[3 + qq], A[6 + qq]);
+          const double* m = Rk.r + 3 * r;
+          nb[r] = fma(m[2], tb[2] - Rk.a[2], fma(m[1], tb[1] - Rk.a[1], m[0] * (tb[0] - Rk.a[0]))) + Rk.a[r];
         }
 #pragma unroll
         for (int qq = 0; qq < 9; ++qq) A[qq] = nA[qq];
@@ -378,7 +416,7 @@ __device__ __forceinline__ void local_sweep(CParams& P, const Lds& S, int nact, 
 // P.chain0 + group G on, of the protein that P describes.  Every wavefront runs all chains of
 // the workgroup (64 / G lanes each); the W wavefronts run the consecutive sweeps in turn,
 // pipelined.
-template <int G>
+template <int G, bool CARRY>
 __device__ __forceinline__ void local_body(CParams& P, const int group) {
   extern __shared__ __align__(16) unsigned char lds[];
   const int tid = threadIdx.x, T = blockDim.x, lane = tid & 63, W = T >> 6;
@@ -410,8 +448,8 @@ __device__ __forceinline__ void local_body(CParams& P, const int group) {
       pipe.m = m;
       pipe.publish = S.prog() + wave;
       pipe.wait_on = m > 0 ? S.prog() + ((m - 1) % W) : nullptr;
-      local_sweep<G>(P, S, nact, c0, tm, sweep_beta(&P, tm), half_window_at(P, tm),
-                     tm > 0 ? half_window_at(P, tm - 1) : 0, lane, lslot, acc_stage, pipe, stalled);
+      local_sweep<G, CARRY>(P, S, nact, c0, tm, sweep_beta(&P, tm), half_window_at(P, tm),
+                            tm > 0 ? half_window_at(P, tm - 1) : 0, lane, lslot, acc_stage, pipe, stalled);
     }
     __syncthreads();
     t += nblk;
@@ -431,28 +469,31 @@ __device__ __forceinline__ void local_body(CParams& P, const int group) {
   for (int e = tid; e < nact * n; e += T) P.s[(size_t)c0 * n + e] = S.s(e / n)[e % n];
 }
 
-template <int G>
+template <int G, bool CARRY>
 __global__ __launch_bounds__(768) void local_kernel(SweepParams) {
   // (the parameters stand at the start of the kernel's argument segment)
-  local_body<G>(*(CParams*)__builtin_amdgcn_kernarg_segment_ptr(), blockIdx.x);
+  local_body<G, CARRY>(*(CParams*)__builtin_amdgcn_kernarg_segment_ptr(), blockIdx.x);
 }
 
 // Several proteins in one launch: workgroup b runs chain group map[b].y of the
 // protein described by descs[map[b].x] (the grid is ordered by decreasing work).
-template <int G>
+template <int G, bool CARRY>
 __global__ __launch_bounds__(768) void local_batch_kernel(const SweepParams* __restrict__ descs,
                                                           const int2* __restrict__ map) {
   const int2 wm = map[blockIdx.x];
   CParams& P = *(CParams*)(uintptr_t)(descs + wm.x);
   if (P.n_sweeps == 0) return;
-  local_body<G>(P, wm.y);
+  local_body<G, CARRY>(P, wm.y);
 }
 
-template __global__ void local_kernel<1>(SweepParams);
-template __global__ void local_kernel<2>(SweepParams);
-template __global__ void local_kernel<4>(SweepParams);
-template __global__ void local_batch_kernel<1>(const SweepParams*, const int2*);
-template __global__ void local_batch_kernel<2>(const SweepParams*, const int2*);
-template __global__ void local_batch_kernel<4>(const SweepParams*, const int2*);
+#define AMH_LOCAL(G, CARRY)                                       \
+  template __global__ void local_kernel<G, CARRY>(SweepParams); \
+  template __global__ void local_batch_kernel<G, CARRY>(const SweepParams*, const int2*);
+AMH_LOCAL(1, true)
+AMH_LOCAL(2, true)
+AMH_LOCAL(4, true)
+AMH_LOCAL(1, false)
+AMH_LOCAL(2, false)
+AMH_LOCAL(4, false)
 
 }  // namespace amh

@@ -68,3 +68,15 @@ def test_runs_end_at_anchors_and_kinds(rule):
         t = int(rule("run_end", 50, 10, 2, 3, t, 20)[0])
         ends.append(t)
     assert ends == [3, 6, 8, 9, 10, 12, 15, 18, 20]
+
+
+@pytest.mark.parametrize("h", [0, 1, 6, 7, 100, 1023])
+def test_carried_energies_are_exact_counts(rule, h):
+    """The largest table deviation at which localized sweeps may carry their energy along: the
+    changed pairs ((h + 1)^2 at most) and the carries (2h + 1), each 1.25 times that, stay below
+    2^53 multiples of 2^-30; a wall does not."""
+    pairs = (h + 1) ** 2 + 2 * h + 1
+    for dev in (0.0, 20.0, 2.0**23 / pairs / 1.31, 2.0**23 / pairs / 1.25, 1e15, 3e38):
+        exact = rule("carry", h, repr(float(np.float32(dev))))[0] == "1"
+        assert not exact or pairs * 1.25 * dev * 2.0**30 < 2.0**53
+        assert exact or dev >= 2.0**23 / pairs / 1.301
