@@ -409,8 +409,10 @@ int widest(const amh_ctx* x) {
   return h;
 }
 
-// Whether localized launches carry this context's energies along.
-bool carries(const amh_ctx* x) { return amh::carry_exact(widest(x), x->dev_max); }
+// Whether localized launches of G chains a workgroup carry this context's energies along.
+bool carries(const amh_ctx* x, int G) {
+  return amh::carry_pays(G, widest(x), x->cfg.L) && amh::carry_exact(widest(x), x->dev_max);
+}
 
 // Wavefronts of a localized launch: kLocalWaves where their LDS fits, else W.
 int local_waves(int G, int L, int W) { return amh::local_lds_bytes(G, L, kLocalWaves) <= kMaxLds ? kLocalWaves : W; }
@@ -677,7 +679,7 @@ amh_status amh_sweep(amh_ctx* x, int64_t n_sweeps) {
       const auto& l = x->local[i];
       P.chain0 = l.first;
       P.C = l.first + l.chains;
-      st = launch(local_fn(l.G, carries(x), false), dim3((l.chains + l.G - 1) / l.G), 64 * l.W,
+      st = launch(local_fn(l.G, carries(x, l.G), false), dim3((l.chains + l.G - 1) / l.G), 64 * l.W,
                   amh::local_lds_bytes(l.G, c.L, l.W), x->stream, P);
     }
     P.C = c.n_chains;
@@ -1016,12 +1018,14 @@ amh_status build_launches(amh_batch* b, int plan) {
     int longest = 2;
     bool automatic = true;   // no member has a shape of its caller's choice
     bool exact = true;       // every member's energies can be carried along
+    const amh_ctx* most = nullptr;   // the member that takes longest
     std::vector<std::pair<double, int2>> items;
     for (size_t i = 0; i < b->m.size(); ++i) {
       if (shape_of[i] != (int)s) continue;
       const amh_ctx* x = b->m[i];
       longest = std::max(longest, x->cfg.L);
-      exact = exact && carries(x);
+      exact = exact && amh::carry_exact(widest(x), x->dev_max);
+      if (!most || member_cost(x) > member_cost(most)) most = x;
       automatic = automatic && x->cfg.chains_per_group == 0 && x->cfg.waves_per_group == 0;
       const int groups = (x->cfg.n_chains + l.G - 1) / l.G;
       for (int g = 0; g < groups; ++g) items.push_back({member_cost(x), make_int2((int)i, g)});
@@ -1031,7 +1035,7 @@ amh_status build_launches(amh_batch* b, int plan) {
     std::vector<int2> map;
     for (auto& it : items) map.push_back(it.second);
     l.n_wg = (int)map.size();
-    l.carry = exact;
+    l.carry = exact && amh::carry_pays(l.G, widest(most), most->cfg.L);
     l.W_local = local_waves(l.G, longest, l.W);
     l.lds_local = amh::local_lds_bytes(l.G, longest, l.W_local);
     // (single-chain groups of the contexts' own shapes share the units with all the batch)

@@ -104,6 +104,36 @@ inline bool carry_exact(int h, float dev_max) {
   return pairs * 1.3 * (double)dev_max < 8388608.0;
 }
 
+// Whether carrying is also the faster way, for workgroups of G chains (64 / G lanes each, R rows of
+// pairs a lane at a time) and a chain of L residues.  Summed afresh, a proposal gathers each
+// changed pair's stencil twice; carried, once, with about 2h pairs more in a gather of their own,
+// deals of the pairs by columns that leave lanes idle, and one proposal more between the
+// pipelined sweeps.  Nine localized sweeps afresh / carried, us:
+//   * pairs that fit the lanes once are summed afresh (1 chain of 16 residues, d = 12 296 / 386; of
+//     64, d = 12 442 / 468, d = 15 466 / 616; 512 chains of 64, d = 8 518 / 589; 1024, d = 12 750 / 800)
+//     unless the chain is so long that the gathers outweigh the deals made anew near its ends:
+//     from 100 residues for four chains a wavefront, which are bound by instruction issue (1024
+//     chains, d = 8, 100 850 / 826, 300 2145 / 1984; d = 12, 100 1017 / 1040, 200 1679 / 1649,
+//     300 2405 / 2318), from 400 for two with d = 12 on (512 chains of 400 2464 / 2434, but with d = 8
+//     of 300 1716 / 1814) and one, as long as pairs and carries fit together (512 chains of 800, one a
+//     workgroup, d = 12 6411 / 6328; with d = 15 one of 300 1320 / 1623);
+//   * beyond, by the gathers of a phi and a psi: carrying has to save more than three of them (200
+//     residues: 1 chain, d = 20 1389 / 1480, d = 30 2430 / 2233; 512 chains, d = 16 1883 / 1659;
+//     1024 chains, d = 15 2379 / 1837, d = 18 2783 / 2826, d = 30 6656 / 4454), and not in chains hardly
+//     longer than the window, where no deal is kept (32 residues, 1 chain, d = 30 971 / 1177).
+inline bool carry_pays(int G, int h, int L) {
+  const int LW = 64 / G, R = G > 2 ? 3 : G;
+  if (h * (h + 1) <= LW * R)
+    return G == 4 ? L >= 100 : L >= 400 && (G == 2 ? h >= 6 : h * (h + 1) + 2 * h + 1 <= LW);
+  const auto up = [](int a, int b) { return (a + b - 1) / b; };
+  const auto rows = [&](int nF, int nM) {   // of a lane, with the changed pairs dealt by columns
+    return R * (nM > LW ? up(nM, LW) * up(nF, R) : up(up(nF, LW / nM), R));
+  };
+  const int afresh = 2 * (2 * R * up(h * (h + 1), LW * R));
+  const int carried = rows(h, h + 1) + rows(h + 1, h) + up(2 * h, LW) + up(2 * h + 1, LW);
+  return L >= 16 + 32 / G && carried + 3 < afresh;
+}
+
 // Half-width of a localization radius d >= 0 in a chain of L residues.  The window [max(0, c - h),
 // min(L - 1, c + h)] is the whole chain from h = L - 1 on, so a wider one is cut to it: the
 // kernels' loops and sums of half-widths (c + 2h, 4h) stay within a few L whatever the d.

@@ -54,22 +54,22 @@ __device__ __forceinline__ int half_window_at(CParams& P, int64_t t) {
 // geometry differs between the lane groups.  The wavefronts of a workgroup are
 // consecutive sweeps of a block, pipelined.
 //
-// Four chains a wavefront are bound by instruction issue (three wavefronts a SIMD, 560 vector
-// instructions a proposal), one chain by the chain of dependent ones (2500 cycles a proposal,
-// of them 400 for the gathers, 470 for the rotation, 360 for the sums).  So a proposal does as
-// little as it can: one spline a changed pair (the energy as it is, is carried along; about 2h
-// pairs correct it), commits that write the window's C-betas only (the backbone follows when
-// the sweep reaches it), one column of pairs a lane (its C-beta turned once), pair deals kept
-// from residue to residue.  9 sweeps, d = 12, before -> now, us: L = 64 x 1 chain 428 -> 431;
-// 300 x 128 1284 -> 1257; 300 x 1024 2400 -> 2240; 250 x 1500 4130 -> 3845; 800 x 64
-// 3000 -> 2900; 100 x 4096 4055 -> 3910.
+// Four chains a wavefront are bound by instruction issue (9 of the 12 wavefronts at work in a run of
+// 9 sweeps, 2.25 a SIMD, 560 vector instructions a proposal), one chain by the chain of dependent
+// ones.  So a proposal does as little as it can: commits write the window's C-betas only (the
+// backbone follows when the sweep reaches it); where it pays (carry_pays) the energy as it is is
+// carried along, one spline a changed pair and about 2h pairs that correct it, with one column of
+// pairs a lane (its C-beta turned once) and pair deals kept from residue to residue.  9 sweeps of
+// d = 12 against commits of all atoms, pair by pair throughout, us: L = 64 x 1 chain 489 -> 422;
+// 300 x 128 1409 -> 1253; 300 x 1024 2612 -> 2247; 250 x 1500 4393 -> 3469; 800 x 64 3358 -> 2981;
+// 100 x 4096 4401 -> 3980.
 //
 // Pipelining: the m-th sweep of a block of consecutive localized sweeps publishes
 // m * 4096 + (proposals done) in `publish`; sweep m+1 waits on that counter so that
-// it runs proposal k' (residue c') only once sweep m is past phi of residue c'+2h+1.  A
-// localized proposal reads the geometry of its window and (phi) the residue before it,
-// and turns residues downstream of its bond, so the two sweeps never touch the same
-// residues and the results equal those of running them in turn.
+// it runs proposal k' (residue c') only once sweep m is past residue c'+2h, with carries past
+// phi of the next one.  A localized proposal reads the geometry of its window and (phi) the
+// residue before it, and turns residues downstream of its bond, so the two sweeps never touch
+// the same residues and the results equal those of running them in turn.
 struct Pipe {
   const int* wait_on;   // progress counter of the previous sweep, or null
   int* publish;         // this sweep's progress counter

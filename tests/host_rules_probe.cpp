@@ -2,7 +2,7 @@
 // tests/test_host_rules.py (no GPU needed).
 //   half_window <d> <L>
 //   last_knot2 <d_min> <bin_w> <n_bins>
-//   carry <h> <dev_max>
+//   carry <G> <h> <L> <dev_max>
 //   run_end <L> <global_every> <n_global> <anchor_every> <t> <end>
 #include <cstdio>
 #include <cstdlib>
@@ -20,8 +20,9 @@ int main(int argc, char** argv) {
     std::printf("%.9g\n", (double)amh::last_knot2(std::atof(argv[2]), std::atof(argv[3]), (int)num(4)));
     return 0;
   }
-  if (argc == 4 && !std::strcmp(argv[1], "carry")) {
-    std::printf("%d\n", amh::carry_exact((int)num(2), (float)std::atof(argv[3])) ? 1 : 0);
+  if (argc == 6 && !std::strcmp(argv[1], "carry")) {
+    const int G = (int)num(2), h = (int)num(3), L = (int)num(4);
+    std::printf("%d %d\n", amh::carry_pays(G, h, L) ? 1 : 0, amh::carry_exact(h, (float)std::atof(argv[5])) ? 1 : 0);
     return 0;
   }
   if (argc == 8 && !std::strcmp(argv[1], "run_end")) {

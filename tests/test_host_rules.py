@@ -77,6 +77,17 @@ def test_carried_energies_are_exact_counts(rule, h):
     2^53 multiples of 2^-30; a wall does not."""
     pairs = (h + 1) ** 2 + 2 * h + 1
     for dev in (0.0, 20.0, 2.0**23 / pairs / 1.31, 2.0**23 / pairs / 1.25, 1e15, 3e38):
-        exact = rule("carry", h, repr(float(np.float32(dev))))[0] == "1"
+        exact = rule("carry", 4, h, 300, repr(float(np.float32(dev))))[1] == "1"
         assert not exact or pairs * 1.25 * dev * 2.0**30 < 2.0**53
         assert exact or dev >= 2.0**23 / pairs / 1.301
+
+
+@pytest.mark.parametrize("G", [1, 2, 4])
+def test_every_half_width_has_a_way(rule, G):
+    """The rule's quotients over all half-widths up to the chain's length, the shortest and the
+    longest chains: an answer, and the narrow windows of short chains summed afresh."""
+    for L in (2, 3, 32, 99, 100, 1024):
+        for h in {0, 1, 2, 6, 7, 8, 15, 16, 31, 32, 33, 63, 64, 65, 200, 1023}:
+            if h <= L - 1:
+                pays = rule("carry", G, h, L, 20.0)[0] == "1"
+                assert not pays or L >= 24
