@@ -227,14 +227,16 @@ int compute_units() {
   return n;
 }
 
-// Threads of a conformation's workgroup (conformation, energy and anchor kernels): the 16
-// wavefronts that a unit holds are divided among its conformations (128 registers a lane).
-// With 4 wavefronts always and now: energies of one conformation of 300 residues 71 -> 42 us, 256 of them 100 -> 69,
-// 64 of 600 228 -> 122; 1024 of 300 have 4 still.  Coordinates alone take 4: 16 are no faster
+// Threads of a conformation's workgroup (energy and anchor kernels): the 16 wavefronts that a unit
+// holds are divided among its conformations (128 registers a lane), but a short chain has no work
+// for them and waits for their start and barriers.  Energies with 4 wavefronts throughout and so,
+// us: one conformation of 300 residues 42 and 25, 256 of them 120 and 68, 64 of 500 186 and 97;
+// 1024 of 300 have 4 still.  With 16, 4 and 2: 256 of 16 residues 10.2, 8.4 and 8.2, of 32 11.4, 10.3
+// and 10.9, of 64 13.6, 14.6 and 20.0.  Coordinates alone take 4: 16 are no faster
 // (L = 300: 1 conformation 29 against 27 us, 256 34 against 40).
-int conf_threads(int64_t B) {
+int conf_threads(int64_t B, int L) {
   const int64_t per_cu = (B + compute_units() - 1) / compute_units();
-  return per_cu <= 1 ? 1024 : per_cu <= 2 ? 512 : 256;
+  return std::min(per_cu <= 1 ? 1024 : per_cu <= 2 ? 512 : 256, L <= 16 ? 128 : L <= 40 ? 256 : 1024);
 }
 
 // Shape of a conformation's workgroup in the gradient and L-BFGS kernels: threads, of which a
@@ -263,7 +265,7 @@ GradShape grad_shape(int L, int64_t B, int least, size_t extra) {
 
 amh_status launch_conf(const amh::ConfParams& P, int B, hipStream_t st) {
   if (B <= 0) return AMH_OK;
-  const int threads = P.table ? conf_threads(B) : 256;
+  const int threads = P.table ? conf_threads(B, P.L) : 256;
   const size_t lds = amh::conf_lds_bytes(P.L, threads, P.table != nullptr);
   HIP_OK(hipFuncSetAttribute((const void*)amh::conf_energy_kernel,
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
@@ -685,8 +687,9 @@ amh_status amh_sweep(amh_ctx* x, int64_t n_sweeps) {
     P.C = c.n_chains;
     if (st == AMH_OK && e % c.anchor_every == 0) {
       P.t0 = e;
-      st = launch((const void*)amh::anchor_kernel, dim3(c.n_chains), conf_threads(c.n_chains),
-                  amh::conf_lds_bytes(c.L, conf_threads(c.n_chains), true), x->stream, P);
+      const int threads = conf_threads(c.n_chains, c.L);
+      st = launch((const void*)amh::anchor_kernel, dim3(c.n_chains), threads,
+                  amh::conf_lds_bytes(c.L, threads, true), x->stream, P);
     }
     if (st != AMH_OK) return st;
     t = e;
@@ -1041,7 +1044,7 @@ amh_status build_launches(amh_batch* b, int plan) {
     // (single-chain groups of the contexts' own shapes share the units with all the batch)
     l.W_global = plan == 0 && l.G == 1 && automatic ? waves_per_chain(chains, longest, compute_units()) : l.W;
     l.lds_global = amh::global_lds_bytes(l.G, longest, global_waves(l.G, l.W_global));
-    l.anchor_threads = conf_threads((int64_t)l.n_wg * l.G);
+    l.anchor_threads = conf_threads((int64_t)l.n_wg * l.G, longest);
     l.lds_anchor = amh::conf_lds_bytes(longest, l.anchor_threads, true);
     hipError_t e = hipMalloc(reinterpret_cast<void**>(&l.d_map), sizeof(int2) * map.size());
     if (e != hipSuccess) return sfail(AMH_E_NOMEM, "hipMalloc: %s", hipGetErrorString(e));

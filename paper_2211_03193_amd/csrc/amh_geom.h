@@ -40,7 +40,7 @@ __device__ __forceinline__ const double* atom(const double* x64, int r, int a) {
 // if the workgroup wrote it) and nobody uses fr; ends with a barrier of the workgroup.
 __host__ __device__ inline int nerf_scratch(int L) { return 12 * ((3 * (L - 1) + 63) / 64); }
 
-__device__ inline void nerf_wg(const double* __restrict__ s, int L, double* __restrict__ x64,
+__device__ __forceinline__ void nerf_wg(const double* __restrict__ s, int L, double* __restrict__ x64,
                                double* __restrict__ fr) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, W = blockDim.x >> 6;
   const double ct_cacn = cos(kAngCACN * kDeg), st_cacn = sin(kAngCACN * kDeg);
