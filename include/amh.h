@@ -336,7 +336,10 @@ amh_status amh_server_destroy(amh_server* server);
  * workgroup runs one chain group of one member, with the LDS of the launch sized
  * for its longest member and the grid ordered by decreasing work per workgroup.
  * Localized runs, global runs and anchors of the members are launched in turn; members
- * at the same point of their cycles share every launch.
+ * at the same point of their cycles share every launch, members whose runs and anchors
+ * fall apart are advanced side by side, on up to three streams of the batch's own (work
+ * there starts behind what the common stream held at the call, and the common stream
+ * waits for it).
  * Members with different launch shapes (chains per workgroup, wavefronts) are
  * advanced by one launch per shape.  Trajectories do not depend on the launch
  * shape or on the batch: a member advanced in a batch follows exactly the sweeps

@@ -936,9 +936,26 @@ namespace {
 
 constexpr int kRing = 8;   // pinned descriptor staging buffers in flight
 constexpr int kMaxRuns = 8;   // descriptor sets (one a launch) uploaded together
+constexpr int kLanes = 4;     // groups of members advanced side by side (hardware queues)
 // launch plans: 0 = each context's own shape, then uniform (chains per group, waves)
 constexpr int kPlans = 6;
 constexpr int kPlanShape[kPlans][2] = {{0, 0}, {1, 4}, {2, 4}, {2, 8}, {4, 4}, {4, 8}};
+
+// What a lane of a batch's sweeps is launched with: a stream, the parameter blocks of its steps
+// (staged in a ring of pinned buffers) and its own list of workgroups.
+struct Lane {
+  hipStream_t stream = nullptr;
+  amh::SweepParams* d_desc = nullptr;   // [kMaxRuns][members]
+  amh::SweepParams* h_ring = nullptr;   // pinned, kRing of these
+  hipEvent_t ev[kRing] = {};
+  bool ev_used[kRing] = {};
+  int ring = 0;
+  // where a batch takes several: their workgroups (of all launches in turn; staged in kRing
+  // buffers too) and the event that the batch's stream waits for
+  int2* d_map = nullptr;
+  int2* h_map = nullptr;   // pinned
+  hipEvent_t done = nullptr;
+};
 
 }  // namespace
 
@@ -952,16 +969,12 @@ struct amh_batch {
     bool carry = false;              // localized launches carry their energies along
     size_t lds_local = 0, lds_global = 0, lds_anchor = 0;   // of the longest member
     int anchor_threads = 256;
-    int n_wg = 0;
+    std::vector<int2> map;           // workgroups: (member, chain group)
     int2* d_map = nullptr;
   };
   std::vector<Launch> launches;
-  amh::SweepParams* d_desc = nullptr;
-  amh::SweepParams* h_ring = nullptr;   // pinned, kRing staging buffers
-  amh::SweepParams* h_desc[kRing] = {};
-  hipEvent_t ev[kRing] = {};
-  bool ev_used[kRing] = {};
-  int ring = 0;
+  Lane lane[kLanes];
+  hipEvent_t fork = nullptr;
 };
 
 namespace {
@@ -969,17 +982,56 @@ namespace {
 void free_launches(amh_batch* b) {
   for (auto& l : b->launches) (void)hipFree(l.d_map);
   b->launches.clear();
+  for (Lane& l : b->lane) {
+    (void)hipFree(l.d_map);
+    if (l.h_map) (void)hipHostFree(l.h_map);
+    l.d_map = l.h_map = nullptr;
+  }
 }
 
 void free_batch(amh_batch* b) {
   if (!b) return;
   free_launches(b);
-  (void)hipFree(b->d_desc);
-  if (b->h_ring) (void)hipHostFree(b->h_ring);
-  for (int i = 0; i < kRing; ++i) {
-    if (b->ev[i]) (void)hipEventDestroy(b->ev[i]);
+  for (Lane& l : b->lane) {
+    (void)hipFree(l.d_desc);
+    if (l.h_ring) (void)hipHostFree(l.h_ring);
+    for (hipEvent_t e : l.ev)
+      if (e) (void)hipEventDestroy(e);
+    if (l.done) (void)hipEventDestroy(l.done);
+    if (&l != b->lane && l.stream) (void)hipStreamDestroy(l.stream);
   }
+  if (b->fork) (void)hipEventDestroy(b->fork);
   delete b;
+}
+
+int workgroups(const amh_batch* b) {
+  int wg = 0;
+  for (const auto& l : b->launches) wg += (int)l.map.size();
+  return wg;
+}
+
+// The buffers and events of lane i, made on its first use, alone or as one of `several`.
+amh_status ready_lane(amh_batch* b, int i, bool several) {
+  Lane& l = b->lane[i];
+  const size_t n = b->m.size();
+  hipError_t e = hipSuccess;
+  const auto event = [&](hipEvent_t* ev) {
+    if (e == hipSuccess && !*ev) e = hipEventCreateWithFlags(ev, hipEventDisableTiming);
+  };
+  if (!l.d_desc) e = hipMalloc(reinterpret_cast<void**>(&l.d_desc), sizeof(amh::SweepParams) * kMaxRuns * n);
+  // (one pinned allocation for the ring: 42 us of host time each, with its release)
+  if (e == hipSuccess && !l.h_ring)
+    e = hipHostMalloc(reinterpret_cast<void**>(&l.h_ring), sizeof(amh::SweepParams) * kMaxRuns * n * kRing);
+  for (hipEvent_t& ev : l.ev) event(&ev);
+  if (several) {
+    event(&b->fork);
+    event(&l.done);
+    const size_t wg = workgroups(b);
+    if (e == hipSuccess && !l.stream && i > 0) e = hipStreamCreateWithFlags(&l.stream, hipStreamNonBlocking);
+    if (e == hipSuccess && !l.d_map) e = hipMalloc(reinterpret_cast<void**>(&l.d_map), sizeof(int2) * wg);
+    if (e == hipSuccess && !l.h_map) e = hipHostMalloc(reinterpret_cast<void**>(&l.h_map), sizeof(int2) * wg * kRing);
+  }
+  return e == hipSuccess ? AMH_OK : sfail(AMH_E_NOMEM, "batch buffers: %s", hipGetErrorString(e));
 }
 
 void member_shape(const amh_ctx* x, int plan, int* G, int* W) {
@@ -1035,21 +1087,19 @@ amh_status build_launches(amh_batch* b, int plan) {
     }
     std::stable_sort(items.begin(), items.end(),
                      [](const auto& a, const auto& c) { return a.first > c.first; });
-    std::vector<int2> map;
-    for (auto& it : items) map.push_back(it.second);
-    l.n_wg = (int)map.size();
+    for (auto& it : items) l.map.push_back(it.second);
     l.carry = exact && amh::carry_pays(l.G, widest(most), most->cfg.L);
     l.W_local = local_waves(l.G, longest, l.W);
     l.lds_local = amh::local_lds_bytes(l.G, longest, l.W_local);
     // (single-chain groups of the contexts' own shapes share the units with all the batch)
     l.W_global = plan == 0 && l.G == 1 && automatic ? waves_per_chain(chains, longest, compute_units()) : l.W;
     l.lds_global = amh::global_lds_bytes(l.G, longest, global_waves(l.G, l.W_global));
-    l.anchor_threads = conf_threads((int64_t)l.n_wg * l.G, longest);
+    l.anchor_threads = conf_threads((int64_t)l.map.size() * l.G, longest);
     l.lds_anchor = amh::conf_lds_bytes(longest, l.anchor_threads, true);
-    hipError_t e = hipMalloc(reinterpret_cast<void**>(&l.d_map), sizeof(int2) * map.size());
+    hipError_t e = hipMalloc(reinterpret_cast<void**>(&l.d_map), sizeof(int2) * l.map.size());
     if (e != hipSuccess) return sfail(AMH_E_NOMEM, "hipMalloc: %s", hipGetErrorString(e));
     b->launches.push_back(l);
-    HIP_OK(hipMemcpy(l.d_map, map.data(), sizeof(int2) * map.size(), hipMemcpyHostToDevice));
+    HIP_OK(hipMemcpy(l.d_map, l.map.data(), sizeof(int2) * l.map.size(), hipMemcpyHostToDevice));
   }
   b->plan = plan;
   return AMH_OK;
@@ -1057,20 +1107,111 @@ amh_status build_launches(amh_batch* b, int plan) {
 
 enum class Step { local, global, anchor };
 
-// The launches of one step (one per shape) over the members' descriptors.
-amh_status launch_step(const amh_batch* b, Step kind, const amh::SweepParams* descs) {
-  for (const auto& l : b->launches) {
-    const int2* map = l.d_map;
+// The launches of one step (one per shape) over the members' descriptors, on a lane's stream and
+// workgroups (n_wg of each launch; null: all, on the batch's own lists).
+amh_status launch_step(const amh_batch* b, const Lane& lane, const std::vector<int>* n_wg, Step kind,
+                       const amh::SweepParams* descs) {
+  size_t at = 0;
+  for (size_t q = 0; q < b->launches.size(); ++q) {
+    const auto& l = b->launches[q];
+    const int2* map = n_wg ? lane.d_map + at : l.d_map;
+    const int wg = n_wg ? (*n_wg)[q] : (int)l.map.size();
+    at += wg;
+    if (wg == 0) continue;
     const int G = l.G, nw = global_waves(l.G, l.W_global);
     const amh_status st =
-        kind == Step::local ? launch(local_fn(G, l.carry, true), dim3(l.n_wg), 64 * l.W_local, l.lds_local, b->stream, descs, map)
+        kind == Step::local
+            ? launch(local_fn(G, l.carry, true), dim3(wg), 64 * l.W_local, l.lds_local, lane.stream, descs, map)
         : kind == Step::global
-            ? launch(global_fn(nw, true), dim3(l.n_wg), 64 * l.W_global, l.lds_global, b->stream, descs, map, G)
-            : launch((const void*)amh::anchor_batch_kernel, dim3(l.n_wg, G), l.anchor_threads, l.lds_anchor, b->stream,
+            ? launch(global_fn(nw, true), dim3(wg), 64 * l.W_global, l.lds_global, lane.stream, descs, map, G)
+            : launch((const void*)amh::anchor_batch_kernel, dim3(wg, G), l.anchor_threads, l.lds_anchor, lane.stream,
                      descs, map, G);
     if (st != AMH_OK) return st;
   }
   return AMH_OK;
+}
+
+// A member's way through its sweeps: runs of one kind (run_end) and anchors.
+struct Walk {
+  amh::SweepParams P;
+  int64_t t, end, anchored;
+  // the sweeps of its next run if that is of the given kind, else 0; the walk goes on behind it
+  int64_t run(bool glob) {
+    if (t >= end || amh::is_global(P, t) != glob) return 0;
+    const int64_t from = t;
+    t = amh::run_end(P, t, end);
+    return t - from;
+  }
+  // (a walk that did not advance in a step stands at an anchor it has already made, or at its start)
+  bool anchor() {
+    if (t == anchored || t % P.anchor_every != 0) return false;
+    anchored = t;
+    return true;
+  }
+};
+
+// Time of the first steps of walks that share every step, each as long as its longest run: one
+// localized sweep of L residues counts L, 8 more pipelined behind it 1.3 L, a global one (1.8 + L / 400) L,
+// an anchor 10 + L / 20 (measured at 64, 300 and 800 residues).
+double shared_time(std::vector<Walk> w) {
+  double sum = 0.0;
+  bool left = true;
+  for (int step = 0; left && step < 128; ++step) {
+    double run = 0.0, anchor = 0.0;
+    left = false;
+    for (Walk& x : w) {
+      const double L = x.P.L, n = (double)x.run(step & 1);
+      if (n > 0.0) run = std::max(run, L * (step & 1 ? n * (1.8 + L / 400.0) : 0.84 + 0.16 * n));
+      if (x.anchor()) anchor = std::max(anchor, 10.0 + L / 20.0);
+      left = left || x.t < x.end;
+    }
+    sum += run + anchor;
+  }
+  return sum;
+}
+
+// The lane of every member.  Members whose runs of sweeps and anchors fall together share their
+// launches.  Where they do not, a shared step takes as long as its longest run and the others wait,
+// which side by side they need not (40 sweeps of two proteins, in one lane / in two, ms: 64 chains of
+// 40 residues each, anchors every 2 and 10 sweeps 5.1 / 3.5, cycles of 10 and localized only
+// 3.2 / 2.2; of 300 residues, anchors every 1 and 1000 sweeps 40.1 / 31.7; 256 chains of 100, anchors
+// every 1 and 1000 15.1 / 14.8).  So a member joins the lane whose time it prolongs least, if that
+// is by a twentieth at most, and else opens one, up to kLanes.
+std::vector<int> assign_lanes(const std::vector<Walk>& w) {
+  std::vector<int> lane(w.size(), 0), order;
+  const auto same = [&](const Walk& a, const Walk& b) {
+    return a.t == b.t && a.end == b.end && a.P.global_every == b.P.global_every && a.P.n_global == b.P.n_global &&
+           a.P.anchor_every == b.P.anchor_every;
+  };
+  for (size_t i = 0; i < w.size(); ++i)
+    if (w[i].t < w[i].end) order.push_back((int)i);
+  bool all = true;
+  for (const int i : order) all = all && same(w[i], w[order[0]]);
+  if (all) return lane;
+  std::vector<double> alone(w.size());
+  for (const int i : order) alone[i] = shared_time({w[i]});
+  std::stable_sort(order.begin(), order.end(), [&](int a, int c) { return alone[a] > alone[c]; });
+  std::vector<Walk> in[kLanes];
+  double time[kLanes];
+  int n = 0;
+  for (const int i : order) {
+    int best = -1;
+    double best_time = 0.0;
+    for (int q = 0; q < n; ++q) {
+      std::vector<Walk> with = in[q];
+      with.push_back(w[i]);
+      const double t = shared_time(std::move(with));
+      if (best < 0 || t - time[q] < best_time - time[best]) { best = q; best_time = t; }
+    }
+    if (best < 0 || (n < kLanes && best_time > 1.05 * time[best])) {
+      best = n++;
+      best_time = alone[i];
+    }
+    in[best].push_back(w[i]);
+    time[best] = best_time;
+    lane[i] = best;
+  }
+  return lane;
 }
 
 }  // namespace
@@ -1091,19 +1232,9 @@ amh_status amh_batch_create(amh_ctx* const* ctxs, int32_t n, amh_batch** out) {
   amh_batch* b = new amh_batch;
   b->m.assign(ctxs, ctxs + n);
   b->stream = ctxs[0]->stream;
-  hipError_t e = hipMalloc(reinterpret_cast<void**>(&b->d_desc), sizeof(amh::SweepParams) * kMaxRuns * n);
-  // (one pinned allocation for the ring: 42 us of host time each, with its release)
-  if (e == hipSuccess)
-    e = hipHostMalloc(reinterpret_cast<void**>(&b->h_ring), sizeof(amh::SweepParams) * kMaxRuns * n * kRing);
-  for (int i = 0; e == hipSuccess && i < kRing; ++i) {
-    b->h_desc[i] = b->h_ring + (size_t)i * kMaxRuns * n;
-    e = hipEventCreateWithFlags(&b->ev[i], hipEventDisableTiming);
-  }
-  if (e != hipSuccess) {
-    free_batch(b);
-    return sfail(AMH_E_NOMEM, "amh_batch_create: %s", hipGetErrorString(e));
-  }
-  amh_status st = build_launches(b, 0);
+  b->lane[0].stream = b->stream;
+  amh_status st = ready_lane(b, 0, false);
+  if (st == AMH_OK) st = build_launches(b, 0);
   if (st != AMH_OK) { free_batch(b); return st; }
   *out = b;
   return AMH_OK;
@@ -1123,73 +1254,119 @@ amh_status amh_batch_sweep_each(amh_batch* b, const int64_t* n_sweeps) {
   }
   if (most == 0) return AMH_OK;
   const size_t nm = b->m.size();
-  // Steps of one kind in turn: every member whose next run of sweeps is of that kind
+  std::vector<Walk> walk(nm);
+  for (size_t i = 0; i < nm; ++i) {
+    const int64_t t = b->m[i]->t;
+    walk[i] = Walk{sweep_params(b->m[i], n_sweeps[i]), t, t + n_sweeps[i], t};
+  }
+  const std::vector<int> lane_of = assign_lanes(walk);
+  const int n_lanes = 1 + *std::max_element(lane_of.begin(), lane_of.end());
+  // Steps of one kind in turn: every member of a lane whose next run of sweeps is of that kind
   // (localized or global, up to an anchor or its last sweep) takes part, the others pass
   // through (n_sweeps = 0); an anchor step follows for the members that reached one.
   // Members at the same point of their cycles share every step.  Descriptors go up
   // kMaxRuns steps at a time (stream order keeps an upload behind the launches that read
   // the last).
-  std::vector<int64_t> t(nm), end(nm), anchored(nm);
-  std::vector<amh::SweepParams> base(nm);
-  for (size_t i = 0; i < nm; ++i) {
-    base[i] = sweep_params(b->m[i], n_sweeps[i]);
-    t[i] = b->m[i]->t;
-    end[i] = t[i] + n_sweeps[i];
-    anchored[i] = t[i];
-  }
-  std::vector<Step> steps;
-  auto upload_and_launch = [&]() -> amh_status {
-    if (steps.empty()) return AMH_OK;
-    const int slot = b->ring;
-    HIP_OK(hipMemcpyAsync(b->d_desc, b->h_desc[slot], sizeof(amh::SweepParams) * steps.size() * nm,
-                          hipMemcpyHostToDevice, b->stream));
-    HIP_OK(hipEventRecord(b->ev[slot], b->stream));
-    b->ev_used[slot] = true;
-    b->ring = (slot + 1) % kRing;
-    for (size_t r = 0; r < steps.size(); ++r) {
-      const amh_status st = launch_step(b, steps[r], b->d_desc + r * nm);
+  struct Progress {
+    std::vector<int> n_wg;      // workgroups of each launch (lanes beyond the first)
+    std::vector<Step> steps;    // staged, not yet launched
+    bool glob = false, left = true;
+  };
+  std::vector<Progress> progress(n_lanes);
+  auto upload_and_launch = [&](int q) -> amh_status {
+    Lane& l = b->lane[q];
+    Progress& p = progress[q];
+    if (p.steps.empty()) return AMH_OK;
+    const int slot = l.ring;
+    HIP_OK(hipMemcpyAsync(l.d_desc, l.h_ring + (size_t)slot * kMaxRuns * nm, sizeof(amh::SweepParams) * p.steps.size() * nm,
+                          hipMemcpyHostToDevice, l.stream));
+    HIP_OK(hipEventRecord(l.ev[slot], l.stream));
+    l.ev_used[slot] = true;
+    l.ring = (slot + 1) % kRing;
+    for (size_t r = 0; r < p.steps.size(); ++r) {
+      const amh_status st = launch_step(b, l, n_lanes > 1 ? &p.n_wg : nullptr, p.steps[r], l.d_desc + r * nm);
       if (st != AMH_OK) return st;
     }
-    steps.clear();
+    p.steps.clear();
     return AMH_OK;
   };
-  // one more step; fill(i, P) completes member i's descriptor and says whether it takes part
-  auto add_step = [&](Step kind, auto fill) -> amh_status {
-    if (steps.empty() && b->ev_used[b->ring]) HIP_OK(hipEventSynchronize(b->ev[b->ring]));
-    amh::SweepParams* d = b->h_desc[b->ring] + steps.size() * nm;
+  // one more step of lane q; fill(x, P) completes a member's descriptor and says whether it takes part
+  auto add_step = [&](int q, Step kind, auto fill) -> amh_status {
+    Lane& l = b->lane[q];
+    Progress& p = progress[q];
+    if (p.steps.empty() && l.ev_used[l.ring]) HIP_OK(hipEventSynchronize(l.ev[l.ring]));
+    amh::SweepParams* d = l.h_ring + ((size_t)l.ring * kMaxRuns + p.steps.size()) * nm;
     bool any = false;
     for (size_t i = 0; i < nm; ++i) {
-      d[i] = base[i];
+      d[i] = walk[i].P;
       d[i].n_sweeps = 0;
-      any = fill(i, d[i]) || any;
+      if (lane_of[i] == q) any = fill(walk[i], d[i]) || any;
     }
     if (!any) return AMH_OK;
-    steps.push_back(kind);
-    return steps.size() == (size_t)kMaxRuns ? upload_and_launch() : AMH_OK;
+    p.steps.push_back(kind);
+    return p.steps.size() == (size_t)kMaxRuns ? upload_and_launch(q) : AMH_OK;
   };
-  bool left = true;
-  for (bool glob = false; left; glob = !glob) {
-    amh_status st = add_step(glob ? Step::global : Step::local, [&](size_t i, amh::SweepParams& P) {
-      if (t[i] >= end[i] || amh::is_global(base[i], t[i]) != glob) return false;
-      P.t0 = t[i];
-      t[i] = amh::run_end(base[i], t[i], end[i]);
-      P.n_sweeps = t[i] - P.t0;
-      return true;
+  auto advance = [&](int q) -> amh_status {
+    Progress& p = progress[q];
+    amh_status st = add_step(q, p.glob ? Step::global : Step::local, [&](Walk& x, amh::SweepParams& P) {
+      P.t0 = x.t;
+      P.n_sweeps = x.run(p.glob);
+      return P.n_sweeps > 0;
     });
-    // (a member that did not advance in this step stands at an anchor it has already made,
-    // or at its start)
     if (st == AMH_OK)
-      st = add_step(Step::anchor, [&](size_t i, amh::SweepParams& P) {
-        if (t[i] == anchored[i] || t[i] % P.anchor_every != 0) return false;
-        P.t0 = anchored[i] = t[i];
+      st = add_step(q, Step::anchor, [&](Walk& x, amh::SweepParams& P) {
+        if (!x.anchor()) return false;
+        P.t0 = x.t;
         P.n_sweeps = 1;
         return true;
       });
     if (st != AMH_OK) return st;
-    left = false;
-    for (size_t i = 0; i < nm; ++i) left = left || t[i] < end[i];
+    p.glob = !p.glob;
+    p.left = false;
+    for (size_t i = 0; i < nm; ++i) p.left = p.left || (lane_of[i] == q && walk[i].t < walk[i].end);
+    return p.left ? AMH_OK : upload_and_launch(q);
+  };
+  // a lane's workgroups: those of its members
+  const auto open_lane = [&](int q) -> amh_status {
+    Lane& l = b->lane[q];
+    if (l.ev_used[l.ring]) HIP_OK(hipEventSynchronize(l.ev[l.ring]));   // (the ring's slots hold them too)
+    int2* const h = l.h_map + (size_t)l.ring * workgroups(b);
+    int n = 0;
+    for (const auto& launch : b->launches) {
+      const int first = n;
+      for (const int2& wg : launch.map)
+        if (lane_of[wg.x] == q) h[n++] = wg;
+      progress[q].n_wg.push_back(n - first);
+    }
+    HIP_OK(hipMemcpyAsync(l.d_map, h, sizeof(int2) * n, hipMemcpyHostToDevice, l.stream));
+    return AMH_OK;
+  };
+  amh_status st = AMH_OK;
+  int forked = 0;
+  if (n_lanes > 1) {   // the lanes' work starts behind what the batch's stream holds
+    for (int q = 0; q < n_lanes && st == AMH_OK; ++q) st = ready_lane(b, q, true);
+    if (st == AMH_OK) HIP_OK(hipEventRecord(b->fork, b->stream));
+    for (int q = 0; q < n_lanes && st == AMH_OK; ++q) {
+      if (q > 0) HIP_OK(hipStreamWaitEvent(b->lane[q].stream, b->fork, 0));
+      forked = q;
+      st = open_lane(q);
+    }
   }
-  const amh_status st = upload_and_launch();
+  for (bool left = true; left && st == AMH_OK;) {
+    left = false;
+    for (int q = 0; q < n_lanes && st == AMH_OK; ++q) {
+      if (progress[q].left) st = advance(q);
+      left = left || progress[q].left;
+    }
+  }
+  // and what follows on it waits for them, whatever became of them
+  for (int q = 1; q <= forked; ++q) {
+    const hipError_t e = hipEventRecord(b->lane[q].done, b->lane[q].stream);
+    if (e != hipSuccess || hipStreamWaitEvent(b->stream, b->lane[q].done, 0) != hipSuccess) {
+      (void)hipStreamSynchronize(b->lane[q].stream);
+      if (st == AMH_OK) st = sfail(AMH_E_DEVICE, "joining a batch's streams: %s", hipGetErrorString(e));
+    }
+  }
   if (st != AMH_OK) return st;
   for (size_t i = 0; i < nm; ++i) b->m[i]->t += n_sweeps[i];
   return AMH_OK;
@@ -1246,11 +1423,9 @@ amh_status amh_batch_set_plan(amh_batch* b, int32_t plan) {
 
 amh_status amh_batch_info(const amh_batch* b, int32_t* plan, int32_t* n_launches, int32_t* workgroups) {
   if (!b) return sfail(AMH_E_INVAL, "batch is NULL");
-  int wg = 0;
-  for (const auto& l : b->launches) wg += l.n_wg;
   if (plan) *plan = b->plan;
   if (n_launches) *n_launches = (int)b->launches.size();
-  if (workgroups) *workgroups = wg;
+  if (workgroups) *workgroups = ::workgroups(b);
   return AMH_OK;
 }
 
