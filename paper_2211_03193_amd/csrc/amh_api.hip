@@ -347,6 +347,12 @@ amh_status launch(const void* fn, dim3 grid, int threads, size_t lds, hipStream_
   return AMH_OK;
 }
 
+// What a launch takes against what a workgroup can have.
+amh_status check_lds(size_t bytes, const char* what) {
+  return bytes <= kMaxLds ? AMH_OK
+                          : sfail(AMH_E_INVAL, "a %s launch needs %zu bytes of LDS (> %zu)", what, bytes, kMaxLds);
+}
+
 // Wavefronts a chain gets in a global-sweep workgroup of G chains and W wavefronts (a
 // power of two; wavefronts left over idle).
 int global_waves(int G, int W) {
@@ -448,7 +454,7 @@ void local_parts(amh_ctx* x, int n_cu) {
 }
 
 size_t local_launch_lds(const amh_ctx* x) {
-  return amh::local_lds_bytes(x->local[0].G, x->cfg.L, x->local[0].W);   // (the larger of two)
+  return amh::local_lds_bytes(x->local[0].G, x->cfg.L, x->local[0].W);   // (the first of two has most chains)
 }
 
 size_t global_launch_lds(const amh_ctx* x) {
@@ -580,6 +586,11 @@ amh_status amh_init(const amh_config* cfg, const float* y_dev, const double* s0_
   x->G_global = G;
   x->W_global = W;
   if (cfg->chains_per_group == 0 && cfg->waves_per_group == 0) global_shape(cfg, n_cu, G, &x->G_global, &x->W_global);
+  if ((st = check_lds(local_launch_lds(x), "localized")) != AMH_OK ||
+      (st = check_lds(global_launch_lds(x), "global")) != AMH_OK) {
+    free_ctx(x);
+    return st;
+  }
   const int L = cfg->L, C = cfg->n_chains, n = 2 * L;
   const int64_t P = (int64_t)L * (L - 1) / 2;
   x->stride = row_stride(cfg->n_bins);
@@ -1096,6 +1107,11 @@ amh_status build_launches(amh_batch* b, int plan) {
     l.lds_global = amh::global_lds_bytes(l.G, longest, global_waves(l.G, l.W_global));
     l.anchor_threads = conf_threads((int64_t)l.map.size() * l.G, longest);
     l.lds_anchor = amh::conf_lds_bytes(longest, l.anchor_threads, true);
+    for (const auto& need : {std::make_pair(l.lds_local, "localized"), std::make_pair(l.lds_global, "global"),
+                             std::make_pair(l.lds_anchor, "anchor")}) {
+      const amh_status st = check_lds(need.first, need.second);
+      if (st != AMH_OK) return st;
+    }
     hipError_t e = hipMalloc(reinterpret_cast<void**>(&l.d_map), sizeof(int2) * l.map.size());
     if (e != hipSuccess) return sfail(AMH_E_NOMEM, "hipMalloc: %s", hipGetErrorString(e));
     b->launches.push_back(l);

@@ -293,9 +293,11 @@ __global__ __launch_bounds__(1024) void anchor_batch_kernel(const SweepParams* _
 }
 
 // ---------------------------------------------------------------------------
-// The LDS that bounds which shapes (chains and wavefronts per workgroup) a length admits:
-// 128 L bytes a chain and its queues and partial sums.  The launches themselves need no
-// more (local_lds_bytes, global_lds_bytes).
+// The rule for which shapes (chains and wavefronts per workgroup) a length admits, kept so that what
+// was accepted and refused stays so: 128 L bytes a chain and queues and partial sums, as much as
+// a kernel needs that holds all atoms of its chains for localized and global sweeps alike.  It
+// is no bound of what the launches take (a global one of a short chain takes more, for its
+// queues and its helper): that is checked by itself (local_lds_bytes, global_lds_bytes).
 size_t sweep_lds_bytes(int G, int L, int W) {
   const size_t b = 128 * (size_t)L, per = b + ((64 + 256 - (b & 255)) & 255);
   return (size_t)G * per + 208 * (size_t)G + 16 * (size_t)W * G + 128 * (size_t)G + 8 * (size_t)G +

@@ -91,3 +91,32 @@ def test_every_half_width_has_a_way(rule, G):
             if h <= L - 1:
                 pays = rule("carry", G, h, L, 20.0)[0] == "1"
                 assert not pays or L >= 24
+
+
+def test_accepted_shapes_fit_the_launches(rule):
+    """Every length and shape (chains, wavefronts) that the admission rule accepts, and the automatic
+    shapes: what the localized and the global launches take fits a workgroup's 160 KiB."""
+    import ctypes
+
+    from paper_2211_03193_amd import amh
+    lib = ctypes.CDLL(amh.LIB_PATH)
+    names = {k: f"_ZN3amh{len(k)}{k}Eiii" for k in ("sweep_lds_bytes", "local_lds_bytes", "global_lds_bytes")}
+    f = {}
+    for k, n in names.items():
+        f[k] = getattr(lib, n)
+        f[k].argtypes, f[k].restype = [ctypes.c_int] * 3, ctypes.c_size_t
+    limit = 160 * 1024
+    for L in range(2, 1025):
+        for G in (1, 2, 4):
+            for W in range(G, 9):
+                if f["sweep_lds_bytes"](G, L, W) > limit:
+                    continue
+                nw = 1
+                while 2 * nw * G <= W and nw < 16:
+                    nw *= 2
+                assert f["local_lds_bytes"](G, L, 12) <= limit, (G, L, W)
+                assert f["global_lds_bytes"](G, L, nw) <= limit, (G, L, W)
+        # automatic: one chain with up to 16 wavefronts, two with two each
+        assert f["sweep_lds_bytes"](1, L, 4) <= limit and f["global_lds_bytes"](1, L, 16) <= limit, L
+        if f["sweep_lds_bytes"](4, L, 8) <= limit:
+            assert f["global_lds_bytes"](2, L, 2) <= limit, L
