@@ -419,7 +419,7 @@ int widest(const amh_ctx* x) {
 
 // Whether localized launches of G chains a workgroup carry this context's energies along.
 bool carries(const amh_ctx* x, int G) {
-  return amh::carry_pays(G, widest(x), x->cfg.L) && amh::carry_exact(widest(x), x->dev_max);
+  return amh::carry_pays(G, widest(x), x->cfg.L) && amh::carry_exact(widest(x), x->cfg.L, x->dev_max);
 }
 
 // Wavefronts of a localized launch: kLocalWaves where their LDS fits, else W.
@@ -1090,7 +1090,7 @@ amh_status build_launches(amh_batch* b, int plan) {
       if (shape_of[i] != (int)s) continue;
       const amh_ctx* x = b->m[i];
       longest = std::max(longest, x->cfg.L);
-      exact = exact && amh::carry_exact(widest(x), x->dev_max);
+      exact = exact && amh::carry_exact(widest(x), x->cfg.L, x->dev_max);
       if (!most || member_cost(x) > member_cost(most)) most = x;
       automatic = automatic && x->cfg.chains_per_group == 0 && x->cfg.waves_per_group == 0;
       const int groups = (x->cfg.n_chains + l.G - 1) / l.G;

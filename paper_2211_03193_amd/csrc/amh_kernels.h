@@ -99,8 +99,9 @@ inline int64_t run_end(const SweepParams& P, int64_t t, int64_t end) {
 // 2^53, through every proposal, whatever the chain does, with a table whose entries deviate from
 // their row's no-contact value by dev_max at most (a Catmull-Rom value is at most 1.25 times the
 // largest of its four).  A wall of 1e15 nats would leave a nat's error in all energy changes.
-inline bool carry_exact(int h, float dev_max) {
-  const double pairs = (h + 1.0) * (h + 1.0) + 2.0 * h + 1.0;
+inline bool carry_exact(int h, int L, float dev_max) {
+  const double window = (h + 1.0) * (h + 1.0), chain = 0.25 * L * L;
+  const double pairs = (window < chain ? window : chain) + 2.0 * h + 1.0;
   return pairs * 1.3 * (double)dev_max < 8388608.0;
 }
 

@@ -22,7 +22,7 @@ int main(int argc, char** argv) {
   }
   if (argc == 6 && !std::strcmp(argv[1], "carry")) {
     const int G = (int)num(2), h = (int)num(3), L = (int)num(4);
-    std::printf("%d %d\n", amh::carry_pays(G, h, L) ? 1 : 0, amh::carry_exact(h, (float)std::atof(argv[5])) ? 1 : 0);
+    std::printf("%d %d\n", amh::carry_pays(G, h, L) ? 1 : 0, amh::carry_exact(h, L, (float)std::atof(argv[5])) ? 1 : 0);
     return 0;
   }
   if (argc == 8 && !std::strcmp(argv[1], "run_end")) {
