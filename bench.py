@@ -116,31 +116,51 @@ def schedule_work(L: int, d: int, cycle: int) -> dict:
             "anchor_pairs": L * (L - 1) // 2}
 
 
-def executed_work(fixed: dict, counted: dict, chains: int) -> dict:
-    """Executed work of one step, split by kernel: the localized-sweep launch (the
+def carry_pays(G: int, h: int, L: int) -> bool:
+    """Whether localized launches of G chains a workgroup carry the energy of their changed pairs
+    along (the library's rule of the same name, for tables of ordinary energies)."""
+    lanes, at_once = 64 // G, 3 if G > 2 else G
+    if h * (h + 1) <= lanes * at_once:
+        if G == 4:
+            return L >= 100
+        return L >= 400 and (h >= 6 if G == 2 else h * (h + 1) + 2 * h + 1 <= lanes)
+
+    def up(a: int, b: int) -> int:
+        return (a + b - 1) // b
+
+    def rows(fixed: int, moved: int) -> int:
+        steps = up(moved, lanes) * up(fixed, at_once) if moved > lanes else up(up(fixed, lanes // moved), at_once)
+        return at_once * steps
+
+    afresh = 4 * at_once * up(h * (h + 1), lanes * at_once)
+    carried = rows(h, h + 1) + rows(h + 1, h) + up(2 * h, lanes) + up(2 * h + 1, lanes)
+    return L >= 16 + 32 // G and carried + 3 < afresh
+
+
+def executed_work(fixed: dict, counted: dict, chains: int, carried: bool) -> dict:
+    """Executed work of one step, split by kernel: the localized-sweep launch (carried: the
     schedule's localized pairs and the pairs that carry their energy, a stencil each, and
-    a rotation for each C-beta turned) and the
+    a rotation for each C-beta turned; else two stencils and a rotation a localized pair) and the
     global-sweep launch (the schedule's candidate tiles, transition pairs and the
     anchor's pairs, plus the counted surviving tiles, pair tests and near pairs)."""
     loc = fixed["local_pairs"] * chains
-    carry = fixed["local_carry_pairs"] * chains
-    turned = fixed["local_turned"] * chains
+    carry = fixed["local_carry_pairs"] * chains if carried else 0
+    turned = fixed["local_turned"] * chains if carried else loc
     trans = fixed["transition_pairs"] * chains
     anch = fixed["anchor_pairs"] * chains
     cand = fixed["candidate_tiles"] * chains
     tests = counted["pair_tests"]
     near = counted["near_pairs"]
-    st_l = loc + carry
+    st_l = loc + carry if carried else 2 * loc
     st_g = near + trans + anch
     fl_l = (FLOPS_TEST + FLOPS_SPLINE) * st_l + FLOPS_ROTATE * turned
     fl_g = FLOPS_TEST * (tests + cand + trans + anch) + FLOPS_SPLINE * st_g
-    # L2 gathers: one per stencil
     return {
         "local": {"local_pairs": loc, "carry_pairs": carry, "turned": turned, "stencils": st_l,
-                  "stencil_bytes": STENCIL_BYTES * st_l, "l2_gather_bytes": STENCIL_BYTES * st_l, "flops": fl_l},
+                  "stencil_bytes": STENCIL_BYTES * st_l, "flops": fl_l},
         "global": {"candidate_tiles": cand, "surviving_tiles": counted["tiles"], "pair_tests": tests,
                    "near_pairs": near, "transition_pairs": trans, "anchor_pairs": anch, "stencils": st_g,
-                   "stencil_bytes": STENCIL_BYTES * st_g, "l2_gather_bytes": STENCIL_BYTES * st_g, "flops": fl_g},
+                   "stencil_bytes": STENCIL_BYTES * st_g, "flops": fl_g},
         "step": {"stencils": st_l + st_g, "stencil_bytes": STENCIL_BYTES * (st_l + st_g), "flops": fl_l + fl_g},
     }
 
@@ -780,16 +800,17 @@ def main():
     # part plus the counted global-sweep part, averaged over the timed steps, over the
     # kernel's average launch duration (HIP events on the launch stream)
     per_launch = {k: v / args.steps for k, v in r["counted"].items()}
-    ex = executed_work(schedule_work(w.L, w.window_d, cyc), per_launch, w.n_chains)
     glob_s = float(np.mean(r["global_ms"])) * 1e-3
     loc_s = float(np.mean(r["local_ms"])) * 1e-3
     step_s = float(np.mean(r["launch_ms"])) * 1e-3
     Gg, Gl = r["info"]["global_chains_per_group"], r["info"]["local_chains_per_group"]
+    carried = carry_pays(Gl, w.window_d // 2, w.L)
+    ex = executed_work(schedule_work(w.L, w.window_d, cyc), per_launch, w.n_chains, carried)
     l2y = yard["l2_gather_16B"]["GB_per_s"] * 1e9 if yard else None
 
     def roof(work, secs, kernel, traffic):
         a = work["flops"] / secs
-        gb = work["l2_gather_bytes"] / secs
+        gb = work["stencil_bytes"] / secs
         return {"bound": "alu", "achieved": a / 1e12, "peak": PEAK_FP32_NONPACKED / 1e12, "unit": "TFLOP/s",
                 "frac": a / PEAK_FP32_NONPACKED, "traffic": traffic, "traffic_unit": "bytes per launch (HBM)",
                 "kernel": kernel, "avg_launch_ms": secs * 1e3,
@@ -798,9 +819,10 @@ def main():
                 "flops_per": {"pair_test": FLOPS_TEST, "stencil_spline": FLOPS_SPLINE,
                               "local_rotation": FLOPS_ROTATE},
                 "frac_of_published_fp32": a / PEAK_FP32_PUBLISHED,
-                "gather": {"achieved_GB_per_s": gb / 1e9, "yardstick": "l2_gather_16B",
-                           "yardstick_GB_per_s": l2y / 1e9 if l2y else None,
-                           "frac": gb / l2y if l2y else None}}
+                # (stencils loaded, from L1 or L2, against a kernel whose every gather is an L2 request)
+                "stencils": {"GB_per_s": gb / 1e9, "yardstick": "l2_gather_16B",
+                             "yardstick_GB_per_s": l2y / 1e9 if l2y else None,
+                             "of_yardstick": gb / l2y if l2y else None}}
 
     traffic = measured_traffic() if w.name == sy.CFG2.name else None
     roof_g = roof(ex["global"], glob_s, f"global_kernel ({Gg} chains per workgroup) and anchor_kernel",
@@ -808,7 +830,7 @@ def main():
     roof_g["dense_equivalent"] = {"pairs_per_launch": glob * w.n_chains,
                                   "note": "every changed pair of the rectangle counted, culled or not; "
                                           "not executed work"}
-    roof_l = roof(ex["local"], loc_s, f"local_kernel<{Gl}> (localized sweeps)",
+    roof_l = roof(ex["local"], loc_s, f"local_kernel<{Gl}, {str(carried).lower()}> (localized sweeps)",
                   traffic.get("local") if traffic else None)
     a_step = ex["step"]["flops"] / step_s
     cnt = r["counters"]

@@ -47,7 +47,7 @@ using amh::sfail;
   } while (0)
 
 constexpr size_t kMaxLds = 160 * 1024;  // LDS per workgroup on gfx950
-constexpr int kLocalWaves = 12;          // wavefronts of a localized-only sweep launch
+constexpr int kLocalWaves = 12;          // wavefronts of a localized launch (the most its registers allow)
 
 int row_stride(int nb) { return ((nb + 2) + 3) & ~3; }   // nb values + 2 ghosts, 16-byte rows
 
@@ -75,7 +75,7 @@ struct amh_ctx {
   double vfar = 0.0;
   float dev_max = 0.0f;
   // launches of the localized-sweep kernel: chains [first, first + chains), G per workgroup
-  struct LocalPart { int first = 0, chains = 0, G = 1, W = 4; };
+  struct LocalPart { int first = 0, chains = 0, G = 1; };
   LocalPart local[2];
   int n_local = 0;
   // launch shape of the global-sweep kernel (chains and wavefronts per workgroup)
@@ -422,9 +422,6 @@ bool carries(const amh_ctx* x, int G) {
   return amh::carry_pays(G, widest(x), x->cfg.L) && amh::carry_exact(widest(x), x->cfg.L, x->dev_max);
 }
 
-// Wavefronts of a localized launch: kLocalWaves where their LDS fits, else W.
-int local_waves(int G, int L, int W) { return amh::local_lds_bytes(G, L, kLocalWaves) <= kMaxLds ? kLocalWaves : W; }
-
 // Localized launches of a context.  A unit holds one workgroup of the localized kernel (12 of
 // its wavefronts), and takes 1 : 1.45 : 1.75 as long for one of 1 : 2 : 4 chains (L = 250, 9
 // sweeps: 1.12, 1.60, 1.95 ms; L = 100: 0.59, 0.85, 1.03 ms).  So an automatically shaped
@@ -435,13 +432,11 @@ int local_waves(int G, int L, int W) { return amh::local_lds_bytes(G, L, kLocalW
 void local_parts(amh_ctx* x, int n_cu) {
   const amh_config& c = x->cfg;
   if (c.chains_per_group != 0 || c.waves_per_group != 0) {
-    x->local[0] = {0, c.n_chains, x->G, local_waves(x->G, c.L, x->W)};
+    x->local[0] = {0, c.n_chains, x->G};
     x->n_local = 1;
     return;
   }
-  const auto part = [&](int first, int chains, int G) {
-    x->local[x->n_local++] = {first, chains, G, local_waves(G, c.L, x->W)};
-  };
+  const auto part = [&](int first, int chains, int G) { x->local[x->n_local++] = {first, chains, G}; };
   int most = 4;
   while (most > 1 && amh::local_lds_bytes(most, c.L, kLocalWaves) > kMaxLds) most >>= 1;
   const int64_t round = (int64_t)most * n_cu;
@@ -454,7 +449,7 @@ void local_parts(amh_ctx* x, int n_cu) {
 }
 
 size_t local_launch_lds(const amh_ctx* x) {
-  return amh::local_lds_bytes(x->local[0].G, x->cfg.L, x->local[0].W);   // (the first of two has most chains)
+  return amh::local_lds_bytes(x->local[0].G, x->cfg.L, kLocalWaves);   // (the first of two has most chains)
 }
 
 size_t global_launch_lds(const amh_ctx* x) {
@@ -692,8 +687,8 @@ amh_status amh_sweep(amh_ctx* x, int64_t n_sweeps) {
       const auto& l = x->local[i];
       P.chain0 = l.first;
       P.C = l.first + l.chains;
-      st = launch(local_fn(l.G, carries(x, l.G), false), dim3((l.chains + l.G - 1) / l.G), 64 * l.W,
-                  amh::local_lds_bytes(l.G, c.L, l.W), x->stream, P);
+      st = launch(local_fn(l.G, carries(x, l.G), false), dim3((l.chains + l.G - 1) / l.G),
+                  64 * kLocalWaves, amh::local_lds_bytes(l.G, c.L, kLocalWaves), x->stream, P);
     }
     P.C = c.n_chains;
     if (st == AMH_OK && e % c.anchor_every == 0) {
@@ -864,7 +859,7 @@ amh_status amh_info_launches(amh_ctx* x, int32_t* local_G, int32_t* local_W, int
                              int32_t* global_G, int32_t* global_W, int32_t* global_lds) {
   if (!x) return sfail(AMH_E_INVAL, "ctx is NULL");
   if (local_G) *local_G = x->local[0].G;
-  if (local_W) *local_W = x->local[0].W;
+  if (local_W) *local_W = kLocalWaves;
   if (local_lds) *local_lds = (int32_t)local_launch_lds(x);
   if (global_G) *global_G = x->G_global;
   if (global_W) *global_W = x->W_global;
@@ -976,7 +971,7 @@ struct amh_batch {
   int plan = 0;
   struct Launch {
     int G = 1, W = 4;
-    int W_local = 4, W_global = 4;   // wavefronts of a localized and a global launch
+    int W_global = 4;                // wavefronts of a global launch
     bool carry = false;              // localized launches carry their energies along
     size_t lds_local = 0, lds_global = 0, lds_anchor = 0;   // of the longest member
     int anchor_threads = 256;
@@ -1100,8 +1095,7 @@ amh_status build_launches(amh_batch* b, int plan) {
                      [](const auto& a, const auto& c) { return a.first > c.first; });
     for (auto& it : items) l.map.push_back(it.second);
     l.carry = exact && amh::carry_pays(l.G, widest(most), most->cfg.L);
-    l.W_local = local_waves(l.G, longest, l.W);
-    l.lds_local = amh::local_lds_bytes(l.G, longest, l.W_local);
+    l.lds_local = amh::local_lds_bytes(l.G, longest, kLocalWaves);
     // (single-chain groups of the contexts' own shapes share the units with all the batch)
     l.W_global = plan == 0 && l.G == 1 && automatic ? waves_per_chain(chains, longest, compute_units()) : l.W;
     l.lds_global = amh::global_lds_bytes(l.G, longest, global_waves(l.G, l.W_global));
@@ -1137,7 +1131,7 @@ amh_status launch_step(const amh_batch* b, const Lane& lane, const std::vector<i
     const int G = l.G, nw = global_waves(l.G, l.W_global);
     const amh_status st =
         kind == Step::local
-            ? launch(local_fn(G, l.carry, true), dim3(wg), 64 * l.W_local, l.lds_local, lane.stream, descs, map)
+            ? launch(local_fn(G, l.carry, true), dim3(wg), 64 * kLocalWaves, l.lds_local, lane.stream, descs, map)
         : kind == Step::global
             ? launch(global_fn(nw, true), dim3(wg), 64 * l.W_global, l.lds_global, lane.stream, descs, map, G)
             : launch((const void*)amh::anchor_batch_kernel, dim3(wg, G), l.anchor_threads, l.lds_anchor, lane.stream,

@@ -195,8 +195,8 @@ __device__ double value_grad(const double* __restrict__ s, int L, const float* _
   const double dfar = d_min + w * ((double)nb - 0.5), d2far = dfar * dfar;   // the last knot
   const double inv_w = 1.0 / w, first = d_min + 0.5 * w;
   const float rcut = (float)dfar + 0.05f;   // (0.05 A: far above float32 rounding)
-  // the table through a global-memory pointer, so that its gathers wait only on their own
-  // counter and not on the LDS traffic of the same steps
+  // the table through a global-memory pointer: its gathers do not wait for LDS reads (but the LDS
+  // arrays come as generic pointers, whose flat reads wait for the gathers in flight too)
   const gfloat* gtable = (const gfloat*)table;
   // the C-beta forces F_k accumulate as integers (multiples of 2^-44) in the first
   // three slots of ft[6k .. 6k+5]
@@ -215,9 +215,7 @@ __device__ double value_grad(const double* __restrict__ s, int L, const float* _
   unsigned long long* const marks = reinterpret_cast<unsigned long long*>(qs + cap);
   unsigned short* const base = reinterpret_cast<unsigned short*>(marks + 64);
   unsigned short* const code = base + 64;
-  // retire every memory operation before the tiles (the NeRF's spill stores among them),
-  // so that inside them only the table gathers are counted and each step waits for
-  // the gather of the pairs it evaluates, not for the one issued for the next step
+  // retire every memory operation before the tiles (the NeRF's spill stores among them)
   __builtin_amdgcn_s_waitcnt(0);
   for (;;) {
     int tile = 0;
@@ -294,7 +292,8 @@ __device__ double value_grad(const double* __restrict__ s, int L, const float* _
       }
       wave_sync();
       // 64 pairs: ends, distance, stencil base and taps, issued one step ahead of their
-      // evaluation so that the table gather overlaps the previous step
+      // evaluation (the flat read of a pair's code waits for the gather before it, which
+      // therefore overlaps that step's arithmetic only)
       struct Pair {
         double inv_d, t;
         int b;

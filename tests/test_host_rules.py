@@ -123,3 +123,13 @@ def test_accepted_shapes_fit_the_launches(rule):
         assert f["sweep_lds_bytes"](1, L, 4) <= limit and f["global_lds_bytes"](1, L, 16) <= limit, L
         if f["sweep_lds_bytes"](4, L, 8) <= limit:
             assert f["global_lds_bytes"](2, L, 2) <= limit, L
+
+
+def test_benchmark_counts_by_the_same_rule(rule):
+    """The benchmark's copy of the rule, which its work counts use."""
+    import bench
+    for G in (1, 2, 4):
+        for h in (1, 2, 4, 6, 7, 8, 9, 10, 15, 18, 30):
+            for L in (20, 40, 64, 100, 300, 400):
+                if h < L:
+                    assert bench.carry_pays(G, h, L) == (rule("carry", G, h, L, 20.0)[0] == "1"), (G, h, L)
