@@ -591,6 +591,7 @@ amh_status amh_init(const amh_config* cfg, const float* y_dev, const double* s0_
   x->stride = row_stride(cfg->n_bins);
   // one allocation a context: an allocation and its release cost 17 us of host time together,
   // of eight arrays 0.8 ms for six served jobs
+  const int ingest_blocks = (int)std::min<int64_t>((P * x->stride + 255) / 256, 4096);
   size_t used = 0;
   const auto take = [&](size_t bytes) {
     const size_t at = used;
@@ -600,7 +601,8 @@ amh_status amh_init(const amh_config* cfg, const float* y_dev, const double* s0_
   const size_t o_table = take(sizeof(float) * P * x->stride), o_ydev = take(sizeof(float) * (P + 1) * x->stride),
                o_s = take(sizeof(double) * C * n), o_best = take(sizeof(double) * C * n),
                o_atoms = take(sizeof(double) * C * L * 12), o_v = take(sizeof(double) * C * 2),
-               o_cnt = take(sizeof(int64_t) * C * 4), o_err = take(sizeof(TableFacts));
+               o_cnt = take(sizeof(int64_t) * C * 4), o_err = take(sizeof(TableFacts)),
+               o_most = take(sizeof(float) * ingest_blocks);
   if ((st = dev_alloc(&x->slab, used)) != AMH_OK) {
     free_ctx(x);
     return st;
@@ -613,22 +615,20 @@ amh_status amh_init(const amh_config* cfg, const float* y_dev, const double* s0_
   x->v = reinterpret_cast<double*>(x->slab + o_v);
   x->counters = reinterpret_cast<int64_t*>(x->slab + o_cnt);
   x->err = reinterpret_cast<unsigned int*>(x->slab + o_err);
+  float* const most = reinterpret_cast<float*>(x->slab + o_most);
   hipError_t e = hipMemsetAsync(x->err, 0, sizeof(TableFacts), x->stream);
   if (e == hipSuccess)   // row P of the deviation table is the zero row
     e = hipMemsetAsync(x->ydev + (size_t)P * x->stride, 0, sizeof(float) * x->stride, x->stream);
   if (e == hipSuccess) {
-    const int64_t work = P * x->stride;
-    int blocks = (int)((work + 255) / 256);
-    if (blocks > 4096) blocks = 4096;
-    hipLaunchKernelGGL(amh::ingest_kernel, dim3(blocks), dim3(256), 0, x->stream, y_dev, P,
-                       cfg->n_bins, x->stride, x->table, x->ydev, x->err);
+    hipLaunchKernelGGL(amh::ingest_kernel, dim3(ingest_blocks), dim3(256), 0, x->stream, y_dev, P,
+                       cfg->n_bins, x->stride, x->table, x->ydev, most, x->err);
     e = hipGetLastError();
   }
   if (e == hipSuccess) {   // the energy of the all-far conformation, read back once
     TableFacts* const facts = reinterpret_cast<TableFacts*>(x->err);
     TableFacts got{};
     hipLaunchKernelGGL(amh::far_sum_kernel, dim3(1), dim3(512), 0, x->stream, x->table, P, x->stride,
-                       cfg->n_bins, &facts->vfar);
+                       cfg->n_bins, most, ingest_blocks, &facts->vfar, &facts->dev_max);
     e = hipGetLastError();
     if (e == hipSuccess) e = hipMemcpyAsync(&got, facts, sizeof(got), hipMemcpyDeviceToHost, x->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(x->stream);

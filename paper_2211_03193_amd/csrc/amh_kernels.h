@@ -162,9 +162,10 @@ inline size_t conf_lds_bytes(int L, int threads, bool energy) {
 }
 
 __global__ void ingest_kernel(const float* y, int64_t P, int nb, int stride, float* out,
-                              float* dev, unsigned int* err);
+                              float* dev, float* most, unsigned int* err);
 __global__ void conf_energy_kernel(ConfParams P);
-__global__ void far_sum_kernel(const float* table, int64_t P, int stride, int nb, double* out);
+__global__ void far_sum_kernel(const float* table, int64_t P, int stride, int nb, const float* most, int n_most,
+                               double* out, float* dev_max);
 __global__ void philox_kernel(const uint32_t* ctr, int64_t n, uint32_t k0, uint32_t k1, uint32_t* out);
 __global__ void perturb_kernel(double* s, int64_t n_total, int n, uint32_t chain_offset, uint32_t tag,
                                uint32_t k0, uint32_t k1, double amplitude);

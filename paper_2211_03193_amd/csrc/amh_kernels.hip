@@ -26,13 +26,15 @@ namespace amh {
 // ---------------------------------------------------------------------------
 // Table ingest: repack [P][nb] rows into padded rows [y1, y0..y_{nb-1}, y_{nb-2}, 0...]
 // (`out`) and the same rows minus the row's no-contact value y_{nb-1} (`dev`, rounded
-// once from float64), flag non-finite entries in err[0] and raise err[1] to the bits of the
-// largest magnitude in `dev`.
+// once from float64), flag non-finite entries, and leave each workgroup's largest magnitude in
+// `dev` to far_sum_kernel (an atomic maximum of all wavefronts on one word took 65 us more).
 __global__ void ingest_kernel(const float* __restrict__ y, int64_t P, int nb, int stride,
-                              float* __restrict__ out, float* __restrict__ dev, unsigned int* err) {
+                              float* __restrict__ out, float* __restrict__ dev, float* __restrict__ most,
+                              unsigned int* err) {
+  __shared__ float wave_most[4];
   const int64_t n = P * (int64_t)stride;
   bool bad = false;
-  float most = 0.0f;
+  float m = 0.0f;
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n;
        e += (int64_t)gridDim.x * blockDim.x) {
     const int64_t r = e / stride;
@@ -42,14 +44,16 @@ __global__ void ingest_kernel(const float* __restrict__ y, int64_t P, int nb, in
     else if (c <= nb) v = y[r * nb + (c - 1)];
     else if (c == nb + 1) v = y[r * nb + (nb - 2)];
     if (c <= nb && !isfinite(v)) bad = true;
-    out[e] = v;
     const float d = c <= nb + 1 ? (float)((double)v - (double)y[r * nb + (nb - 1)]) : 0.0f;
+    out[e] = v;
     dev[e] = d;
-    most = fmaxf(most, fabsf(d));
+    m = fmaxf(m, fabsf(d));
   }
   if (bad) atomicOr(err, kErrTable);
-  for (int o = 32; o > 0; o >>= 1) most = fmaxf(most, __shfl_xor(most, o, 64));
-  if ((threadIdx.x & 63) == 0) atomicMax(err + 1, __float_as_uint(most));
+  for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+  if ((threadIdx.x & 63) == 0) wave_most[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) most[blockIdx.x] = fmaxf(fmaxf(wave_most[0], wave_most[1]), fmaxf(wave_most[2], wave_most[3]));
 }
 
 // Noisy restart: s_k += amplitude (2u - 1) with u from Philox at (k, tag, chain, 1),
@@ -171,20 +175,28 @@ __device__ double energy64(const float* __restrict__ table, int stride, int nb, 
 // Sum over the P rows of the table of their no-contact value row[nb] (the energy of
 // a conformation whose pairs all lie beyond the last knot), float64 Neumaier in a
 // fixed order: one workgroup; thread t takes rows t, t + T, ...; the partials are
-// combined in thread order by thread 0.
+// combined in thread order by thread 0.  And the largest of ingest_kernel's n_most maxima.
 __global__ void far_sum_kernel(const float* __restrict__ table, int64_t P, int stride, int nb,
-                               double* __restrict__ out) {
+                               const float* __restrict__ most, int n_most, double* __restrict__ out,
+                               float* __restrict__ dev_max) {
   __shared__ double part[2 * 1024];
+  __shared__ float wave_most[16];
   const int tid = threadIdx.x, T = blockDim.x;
   double s = 0.0, c = 0.0;
   for (int64_t r = tid; r < P; r += T) neumaier_add(s, c, (double)table[r * stride + nb]);
   part[2 * tid] = s;
   part[2 * tid + 1] = c;
+  float m = 0.0f;
+  for (int q = tid; q < n_most; q += T) m = fmaxf(m, most[q]);
+  for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+  if ((tid & 63) == 0) wave_most[tid >> 6] = m;
   __syncthreads();
   if (tid == 0) {
     double a = 0.0, b = 0.0;
     for (int t = 0; t < T; ++t) { neumaier_add(a, b, part[2 * t]); b += part[2 * t + 1]; }
     *out = a + b;
+    for (int w = 1; w < T >> 6; ++w) m = fmaxf(m, wave_most[w]);
+    *dev_max = m;
   }
 }
 
