@@ -71,7 +71,8 @@ __device__ __forceinline__ void st3(double* p, D3 v) { p[0] = v.x; p[1] = v.y; p
 // round on its own depends on the code around it): every kernel, whatever its launch shape,
 // builds the same coordinates, bit for bit.
 __device__ __forceinline__ double row3(const double* m, double x, double y, double z) {
-  return fma(m[2], z, fma(m[0], x, m[1] * y));
+  const double a = m[0], b = m[1], c = m[2];
+  return fma(c, z, fma(a, x, b * y));
 }
 __device__ __forceinline__ double row3(double o, const double* m, double x, double y, double z) {
   return fma(m[2], z, fma(m[1], y, fma(m[0], x, o)));
