@@ -240,7 +240,8 @@ int conf_threads(int64_t B, int L) {
 }
 
 // Shape of a conformation's workgroup in the gradient and L-BFGS kernels: threads, of which a
-// unit holds 512 (256 registers a lane: 16 wavefronts of 128 are slower by a quarter), and
+// unit holds 512 (256 registers a lane; 16 wavefronts of 128, with value_grad a call as it is, are
+// slower by a quarter), and
 // pairs a wavefront's list holds, as the LDS of the workgroups a unit is to hold allows.  One
 // conformation a unit takes all 512 threads (one of 300 residues 113 us with 256, 86 with 512);
 // more take 256, and from three a unit on 128 where there are three tiles at most (1024 of 64
@@ -371,20 +372,25 @@ int global_waves(int G, int W) {
 //   L = 300: 256 chains  -   / 2964 / 1887 / 1747;  512  -   / 3571 / 2521 / -;
 //            1024       5127 / 3654 / 4049 / -;   2048 7232 / 6192 / 7536 / -
 //   L = 800: 64 chains   -   / 12313 / 7321 / 5801
-// (16 for longer chains, which have more tiles to share, and where a unit has one chain; at
-// 100 residues and 512 chains on they took 1.7 times as long as 8.  4 instead of 2 for longer
-// chains where every unit is full).  A context of 4-chain groups that takes at most one
-// group per unit, 1024 chains on 256 units, keeps the shape that amh_info_launches documents
-// for it, two chains and four wavefronts (2 a chain): 5.0 ms a sweep at L = 300.
+// 16 where a unit has one chain and that is longer than 256 residues: it has the tiles to share.
+// Below, 16 and 8 lie together (two sweeps with 8 / 16, us: 256 chains of 64 562 / 604, of 100 942 / 951,
+// of 130 1502 / 1402, of 200 2234 / 2106, of 256 2755 / 2631; one chain of 130 1244 / 1206, of 160
+// 1429 / 1450, of 256 2320 / 2342).  2 where every unit is full, up to 160 residues: eight such workgroups
+// fill a unit, but from 225 residues on its LDS no longer holds them (two sweeps with 2 / 4, ms: 2048
+// chains of 160 4.1 / 4.9, of 200 6.5 / 7.3, of 250 11.5 / 9.6, of 300 14.1 / 11.5; 1280 of 300, five a
+// unit, 8.8 / 9.7).
 int waves_per_chain(int64_t chains, int L, int n_cu) {
   const int64_t per_cu = (chains + n_cu - 1) / n_cu;
   return per_cu <= 1 ? (L > 256 ? 16 : 8) : per_cu <= 2 ? 8 : per_cu <= 4 || L > 160 ? 4 : 2;
 }
 
+// ... except that a context of four-chain groups, at most one a unit (1024 chains on 256 units),
+// keeps the shape that amh_info_launches has reported for it, two chains and four wavefronts: two
+// sweeps of 1024 chains of 300 residues take 9.2 ms so, 6.5 with four wavefronts a chain (1023 chains).
 void global_shape(const amh_config* c, int n_cu, int G, int* G_global, int* W_global) {
-  const bool documented = G == 4 && c->n_chains <= 4 * (int64_t)n_cu;
-  *G_global = documented ? 2 : 1;
-  *W_global = documented ? 4 : waves_per_chain(c->n_chains, c->L, n_cu);
+  const bool reported = G == 4 && c->n_chains <= 4 * (int64_t)n_cu;
+  *G_global = reported ? 2 : 1;
+  *W_global = reported ? 4 : waves_per_chain(c->n_chains, c->L, n_cu);
 }
 
 const void* global_fn(int nw, bool batch) {

@@ -179,8 +179,8 @@ __device__ __attribute__((noinline)) double ordered_energy(int L, const gfloat* 
 //     u = (j - i) mod 64.  A list that its LDS does not hold is taken in ranges of u.
 // A tile's forces on a residue, rounded to multiples of 2^-44, and a pair's energy, in multiples of
 // 2^-26 and 2^-70, are added as integers: the totals do not depend on the order of the tiles or
-// on the launch shape.  `ordered` (of the table alone): V comes from
-// ordered_energy instead, and what is returned is a number unless it is NaN.
+// on the launch shape.  `ordered` (a table with deviations beyond these integers): the energies are
+// left out, and the number returned says only whether V is NaN.
 // At 512 conformations of 400 residues (two workgroups of 4 wavefronts a unit, one pair in six
 // inside the last knot) the time goes to the sums (27 %), the marks (20 %), the coordinates
 // (19 %) and the evaluations (17 %): vector instructions, at two wavefronts a SIMD.  Evaluating
