@@ -240,13 +240,17 @@ int conf_threads(int64_t B, int L) {
 }
 
 // Shape of a conformation's workgroup in the gradient and L-BFGS kernels: threads, of which a
-// unit holds 512 (256 registers a lane; 16 wavefronts of 128, with value_grad a call as it is, are
-// slower by a quarter), and
+// unit holds 512 (256 registers a lane; 16 wavefronts of 128 are slower by a quarter), and
 // pairs a wavefront's list holds, as the LDS of the workgroups a unit is to hold allows.  One
-// conformation a unit takes all 512 threads (one of 300 residues 113 us with 256, 86 with 512);
-// more take 256, and from three a unit on 128 where there are three tiles at most (1024 of 64
-// residues 101 us with 256, 62 with 128).  `least`: threads the kernel needs, `extra`: its LDS
-// beyond the gradient's.
+// conformation a unit takes all 512 threads (gradients with 256 and 512, us: one of 200 residues 77
+// and 59, of 300 80 and 57, 256 of 300 164 and 102, 64 of 800 424 and 277; of 100 residues and
+// less the two lie together); more take 256, and from three a unit on 128 where there are three
+// tiles at most (1024 of 16 residues with 256 and 128 34 and 22, of 64 92 and 62, of 100 100 and 82).
+// Where two workgroups with lists of 256 pairs each do not fit a unit (from 471 residues on), it has
+// one of 512 threads: 512 conformations of 500 residues with one of 256 threads, two of them with
+// short lists and one of 512 468, 423 and 336 us, of 540 489, 531 and 341, of 800 911 and 599 (256
+// threads with long lists against 512 with short ones: one of 830 residues 416 and 272).
+// `least`: threads the kernel needs, `extra`: its LDS beyond the gradient's.
 struct GradShape { int threads, cap; size_t lds; };
 
 GradShape grad_shape(int L, int64_t B, int least, size_t extra) {
@@ -255,9 +259,12 @@ GradShape grad_shape(int L, int64_t B, int least, size_t extra) {
   if (s.threads < least) s.threads = least;
   // (the kernels' own 256 bytes are the barrier votes')
   const auto bytes = [&](int cap) { return amh::grad_lds_bytes(L, s.threads / 64, cap) + extra + 256; };
-  if (s.threads == 512 && bytes(512) > kMaxLds) s.threads = 256;
   size_t room = kMaxLds / (512 / s.threads);   // of a workgroup, as many on a unit as it holds
-  if (bytes(256) > room) room = kMaxLds;
+  if (bytes(256) > room) {
+    room = kMaxLds;
+    s.threads = 512;
+    if (bytes(256) > room) s.threads = 256;
+  }
   s.cap = 64;
   while (s.cap < 2048 && bytes(s.cap + 8) <= room) s.cap += 8;
   s.lds = bytes(s.cap) - 256;
