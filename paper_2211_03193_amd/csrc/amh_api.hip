@@ -250,12 +250,16 @@ int conf_threads(int64_t B, int L) {
 // one of 512 threads: 512 conformations of 500 residues with one of 256 threads, two of them with
 // short lists and one of 512 468, 423 and 336 us, of 540 489, 531 and 341, of 800 911 and 599 (256
 // threads with long lists against 512 with short ones: one of 830 residues 416 and 272).
+// `few`: the wavefronts share tiles, where there are three at most and as many wavefronts (64
+// residues: 512 conformations 34 us against 54 with a tile a wavefront, 1024 43 against 61), from
+// 9 residues on (2: 13.1 against 12.4, 8: 13.9 and 13.8, 12: 14.9 against 16.1).  With six tiles,
+// 130 to 192 residues, and 8 wavefronts it is slower (200 conformations of 180 77 against 69).
 // `least`: threads the kernel needs, `extra`: its LDS beyond the gradient's.
-struct GradShape { int threads, cap; size_t lds; };
+struct GradShape { int threads, cap; size_t lds; bool few; };
 
 GradShape grad_shape(int L, int64_t B, int least, size_t extra) {
   const int n_cu = compute_units();
-  GradShape s{B <= n_cu ? 512 : B > 2 * (int64_t)n_cu && L <= 128 ? 128 : 256, 0, 0};
+  GradShape s{B <= n_cu ? 512 : B > 2 * (int64_t)n_cu && L <= 128 ? 128 : 256, 0, 0, false};
   if (s.threads < least) s.threads = least;
   // (the kernels' own 256 bytes are the barrier votes')
   const auto bytes = [&](int cap) { return amh::grad_lds_bytes(L, s.threads / 64, cap) + extra + 256; };
@@ -268,6 +272,7 @@ GradShape grad_shape(int L, int64_t B, int least, size_t extra) {
   s.cap = 64;
   while (s.cap < 2048 && bytes(s.cap + 8) <= room) s.cap += 8;
   s.lds = bytes(s.cap) - 256;
+  s.few = L > 8 && L <= (s.threads >= 256 ? 128 : 64);
   return s;
 }
 
@@ -549,9 +554,9 @@ amh_status minimize_impl(amh_ctx* x, double* s_dev, int32_t B, const amh_lbfgs_o
   const size_t lds = shape.lds;
   P.cap = shape.cap;
   if (lds > kMaxLds) return sfail(AMH_E_INVAL, "L=%d needs %zu bytes of LDS for L-BFGS", L, lds);
-  HIP_OK(hipFuncSetAttribute((const void*)amh::lbfgs_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)lds));
-  hipLaunchKernelGGL(amh::lbfgs_kernel, dim3(B), dim3(shape.threads), lds, x->stream, P);
+  const auto kernel = shape.few ? amh::lbfgs_kernel<true> : amh::lbfgs_kernel<false>;
+  HIP_OK(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  hipLaunchKernelGGL(kernel, dim3(B), dim3(shape.threads), lds, x->stream, P);
   HIP_OK(hipGetLastError());
   if (!s_dev) {
     amh::ConfParams cp{};
@@ -917,9 +922,9 @@ amh_status amh_grad(amh_ctx* x, const double* s_dev, int32_t B, double* V_out_de
   const size_t lds = shape.lds;
   P.cap = shape.cap;
   if (lds > kMaxLds) return sfail(AMH_E_INVAL, "L=%d needs %zu bytes of LDS for the gradient", P.L, lds);
-  HIP_OK(hipFuncSetAttribute((const void*)amh::grad_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)lds));
-  hipLaunchKernelGGL(amh::grad_kernel, dim3(B), dim3(shape.threads), lds, x->stream, P);
+  const auto kernel = shape.few ? amh::grad_kernel<true> : amh::grad_kernel<false>;
+  HIP_OK(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  hipLaunchKernelGGL(kernel, dim3(B), dim3(shape.threads), lds, x->stream, P);
   HIP_OK(hipGetLastError());
   return AMH_OK;
 }

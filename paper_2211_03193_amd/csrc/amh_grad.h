@@ -70,7 +70,7 @@ inline size_t lbfgs_lds_bytes(int L, int W, int cap, int m, int M) {
 }
 inline size_t lbfgs_work_doubles(int L, int m) { return (5 + 2 * (size_t)m) * 2 * (size_t)L; }
 
-__global__ void grad_kernel(GradParams P);
-__global__ void lbfgs_kernel(LbfgsParams P);
+template <bool FEW> __global__ void grad_kernel(GradParams P);
+template <bool FEW> __global__ void lbfgs_kernel(LbfgsParams P);
 
 }  // namespace amh

@@ -183,15 +183,24 @@ __device__ __attribute__((noinline)) double ordered_energy(int L, const gfloat* 
 // left out, and the number returned says only whether V is NaN.
 // At 512 conformations of 400 residues (two workgroups of 4 wavefronts a unit, one pair in six
 // inside the last knot) the time goes to the sums (27 %), the marks (20 %), the coordinates
-// (19 %) and the evaluations (17 %): vector instructions, at two wavefronts a SIMD.  Evaluating
-// all pairs, absent and far ones too, one a lane and step: 291 us, now 244; 64 of 800 630, now
-// 291; one of 300 146, now 86; 1024 of 300 355, now 294; 128 of 200 minimised for 20
-// iterations 4.4 ms, now 2.2.
-__device__ double value_grad(const double* __restrict__ s, int L, const float* __restrict__ table,
+// (19 %) and the evaluations (17 %): vector instructions, at two wavefronts a SIMD.  (Inlined, with
+// LDS reads instead of flat ones and 130 registers instead of 248, it takes 1 to 10 % longer, 128
+// minimisations of 200 residues 7 %.)  Evaluating all pairs, absent and far ones too, one a lane
+// and step: 290 us, now 250; 64 of 800 665, now 278; one of 300 152, now 56; 1024 of 300 368, now
+// 283; 128 of 200 minimised for 20 iterations 4.4 ms, now 2.3.
+//
+// FEW (up to three tiles, no more than wavefronts): folded chains of up to 128 residues have most
+// of their pairs inside the last knot and one dense tile, which one wavefront would take while the
+// others wait (70 of 88 thousand cycles at 64 residues).  So the wavefronts share every tile's
+// marks, evaluations and sums, with barriers between: conformations of 64 residues, with all pairs
+// evaluated / a tile a wavefront / tiles shared, 1 of them 38 / 39 / 24 us, 512 43 / 54 / 34; 200 of
+// 100 48 / 50 / 36, of 128 51 / 57 / 39.  Pairs beyond the common list are left to the other way.
+template <bool FEW>
+__device__ __attribute__((noinline)) double value_grad(const double* __restrict__ s, int L, const float* __restrict__ table,
                              int stride, int nb, double d_min, double w, double vfar, bool ordered, double* x64, double* ft,
                              float4* sph, unsigned char* pairs, int cap, long long* vacc,
                              double* __restrict__ g) {
-  const int tid = threadIdx.x, T = blockDim.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, T = blockDim.x, lane = tid & 63, wave = tid >> 6, W = T >> 6;
   const double dfar = d_min + w * ((double)nb - 0.5), d2far = dfar * dfar;   // the last knot
   const double inv_w = 1.0 / w, first = d_min + 0.5 * w;
   const float rcut = (float)dfar + 0.05f;   // (0.05 A: far above float32 rounding)
@@ -217,7 +226,227 @@ __device__ double value_grad(const double* __restrict__ s, int L, const float* _
   unsigned short* const code = base + 64;
   // retire every memory operation before the tiles (the NeRF's spill stores among them)
   __builtin_amdgcn_s_waitcnt(0);
-  for (;;) {
+  double whole = 0.0, part = 0.0;   // energies of the pairs, multiples of 2^-26 and of 2^-70
+  struct Tile { int off, i0, j0; };
+  // 64 pairs: ends, distance, stencil base and taps, issued one step ahead of their
+  // evaluation (the flat read of a pair's code waits for the gather before it, which
+  // therefore overlaps that step's arithmetic only)
+  struct Pair {
+    double inv_d, t;
+    int b;
+    bool use;
+    float q0, q1, q2, q3, qn;
+  };
+  auto prep = [&](const Tile& tl, const unsigned short* list, int count, int k) {
+    Pair a;
+    a.use = k < count;
+    const int cd = a.use ? list[k] : 0;
+    const int pi = tl.i0 + (cd & 63), pj = a.use ? tl.j0 + (((cd & 63) + (cd >> 6)) & 63) : 0;
+    const double* xa = atom(x64, pi, 3);
+    const double* xb = atom(x64, pj, 3);
+    const double d2 = pair_dist2(xb[0] - xa[0], xb[1] - xa[1], xb[2] - xa[2]);
+    // distance through the hardware reciprocal square root and two Newton steps
+    a.inv_d = a.use && d2 > 0.0 ? rsqrt64(d2) : 0.0;
+    a.t = fma(d2, a.inv_d, -first) * inv_w;
+    a.b = stencil_base(a.t, nb);
+    const gfloat* r = gtable + (size_t)(a.use ? pair_row(pi, pj, L) : 0) * stride;
+    a.q0 = r[a.b]; a.q1 = r[a.b + 1]; a.q2 = r[a.b + 2]; a.q3 = r[a.b + 3];
+    a.qn = r[nb];
+    return a;
+  };
+  auto eval = [&](const Pair& a, double* q, int k) {
+    if (!a.use) return;
+    double E, dE;
+    spline64_ed((double)a.q0, (double)a.q1, (double)a.q2, (double)a.q3, a.t, a.b, nb, inv_w, E, dE);
+    // deviation e + low from the no-contact value, exactly (Knuth's two-sum), in multiples
+    // of 2^-26 and of 2^-70: every digit of a pair's energy down to these
+    double e = E, low = 0.0;
+    two_sum(e, low, -(double)a.qn);
+    const double n = rint(e * 0x1p26);   // (sums of integers below 2^53)
+    whole += n;
+    part += rint((fma(n, -0x1p-26, e) + low) * 0x1p70);
+    q[k] = a.inv_d > 0.0 ? dE * a.inv_d : 0.0;
+  };
+  // dV/dx_j = +q (x_j - x_i), dV/dx_i = -q (x_j - x_i): the steps of `left` added to the force on
+  // this lane's row (whose pairs lie in the list from k on) ...
+  // (two a step, so that their reads overlap; an absent one adds zero)
+  auto add_row = [&](const Tile& tl, const double* q, unsigned long long left, int k, double ix, double iy, double iz,
+                     double& rx, double& ry, double& rz) {
+    while (left != 0) {
+      const int ua = __builtin_ctzll(left);
+      left &= left - 1;
+      const bool two = left != 0;
+      const int ub = two ? __builtin_ctzll(left) : ua;
+      left &= left - 1;
+      const double* xa = atom(x64, tl.j0 + ((lane + ua) & 63), 3);
+      const double* xb = atom(x64, tl.j0 + ((lane + ub) & 63), 3);
+      const double qa = -q[k], qb = two ? -q[k + 1] : 0.0;
+      rx = fma(xa[0] - ix, qa, rx); ry = fma(xa[1] - iy, qa, ry); rz = fma(xa[2] - iz, qa, rz);
+      rx = fma(xb[0] - ix, qb, rx); ry = fma(xb[1] - iy, qb, ry); rz = fma(xb[2] - iz, qb, rz);
+      k += 2;
+    }
+  };
+  // ... and to that on its column
+  auto add_col = [&](const Tile& tl, const double* q, const unsigned long long* mk, const unsigned short* bs,
+                     unsigned long long left, double jx, double jy, double jz, double& cx, double& cy, double& cz) {
+    while (left != 0) {
+      const int ua = __builtin_ctzll(left), ra = (lane - ua) & 63;
+      left &= left - 1;
+      const bool two = left != 0;
+      const int ub = two ? __builtin_ctzll(left) : ua, rb = (lane - ub) & 63;
+      left &= left - 1;
+      const double* xa = atom(x64, tl.i0 + ra, 3);
+      const double* xb = atom(x64, tl.i0 + rb, 3);
+      const double qa = q[bs[ra] + (int)__popcll(mk[ra] & ((1ull << ua) - 1))];
+      const double qv = q[bs[rb] + (int)__popcll(mk[rb] & ((1ull << ub) - 1))], qb = two ? qv : 0.0;
+      cx = fma(jx - xa[0], qa, cx); cy = fma(jy - xa[1], qa, cy); cz = fma(jz - xa[2], qa, cz);
+      cx = fma(jx - xb[0], qb, cx); cy = fma(jy - xb[1], qb, cy); cz = fma(jz - xb[2], qb, cz);
+    }
+  };
+  bool done = false;
+  if constexpr (FEW) {   // fewer tiles than wavefronts: they share each tile
+    auto tile_at = [&](int t) {
+      int off = 0, I = t;   // J - I, I
+      while (I >= nb64 - off) { I -= nb64 - off; ++off; }
+      return Tile{off, 64 * I, 64 * (I + off)};
+    };
+    // marks of the 8 columns from jq on: `mine` of this lane's row, `rows` of column lane & 7
+    auto mark8 = [&](const float4& si, double ix, double iy, double iz, bool present, int jq, unsigned int& mine,
+                     unsigned long long& rows) {
+      mine = 0;
+      rows = 0;
+      const float4 sq = sph[jq >> 3];
+      const float dx = si.x - sq.x, dy = si.y - sq.y, dz = si.z - sq.z, lim = rcut + si.w + sq.w;
+      if (__ballot(present && !(dx * dx + dy * dy + dz * dz > lim * lim)) == 0) return;
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {   // (NaN distances are evaluated, so V turns NaN)
+        const double* x = atom(x64, jq + r < L ? jq + r : 0, 3);
+        const bool use = !(pair_dist2(x[0] - ix, x[1] - iy, x[2] - iz) >= d2far);
+        const unsigned long long bal = __ballot(use);
+        mine |= use ? 1u << r : 0u;
+        if ((lane & 7) == r) rows = bal;
+      }
+    };
+    // marks by column and by row -> by the step u
+    auto by_step = [&](const Tile& tl, unsigned long long near, unsigned long long column, unsigned long long& row,
+                       unsigned long long& col) {
+      if (tl.j0 + 64 > L) near &= (1ull << (L - tl.j0)) - 1;
+      if (tl.j0 + lane >= L) column = 0;
+      if (tl.off == 0) {
+        near &= ~1ull << lane;
+        column &= (1ull << lane) - 1;
+      }
+      const unsigned long long rev = __brevll(column);
+      const int by = (lane + 1) & 63;
+      row = near >> lane | near << ((64 - lane) & 63);
+      col = rev << by | rev >> ((64 - by) & 63);
+    };
+    // list position of the row's first pair of m, and the number of all rows' pairs
+    auto place = [&](unsigned long long m, int& at, int& count) {
+      const int n = (int)__popcll(m);
+      at = count = 0;
+#pragma unroll
+      for (int b = 0; b < 7; ++b) {
+        const unsigned long long bal = __ballot((n >> b) & 1);
+        at += (int)__builtin_amdgcn_mbcnt_hi((unsigned)(bal >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0)) << b;
+        count += (int)__popcll(bal) << b;
+      }
+    };
+    const double lim = 0x1p13;   // |tile sum| < 2^13: a residue's total stays below 2^19
+    auto add_force = [&](int k, double x, double y, double z) {
+      lds_add(facc + 6 * k, fixed44(x));
+      lds_add(facc + 6 * k + 1, fixed44(y));
+      lds_add(facc + 6 * k + 2, fixed44(z));
+    };
+    // the wavefronts' list memory: per tile its marks (of row i by column, then by step), its list
+    // positions and its columns' marks, then one list of all tiles' pairs
+    unsigned long long* const all_marks = reinterpret_cast<unsigned long long*>(pairs);
+    unsigned long long* const columns = all_marks + 64 * ntile;
+    unsigned short* const all_base = reinterpret_cast<unsigned short*>(columns + 64 * ntile);
+    double* const all_qs = reinterpret_cast<double*>(all_base + 64 * ntile);
+    const int room = ((int)grad_pair_bytes(cap) * W - 1152 * ntile) / 10;   // pairs of the list
+    unsigned short* const all_code = reinterpret_cast<unsigned short*>(all_qs + room);
+    int* const counts = reinterpret_cast<int*>(vacc + 3);
+    // marks, 8 columns an item
+    for (int e = wave; e < 8 * ntile; e += W) {
+      const Tile tl = tile_at(e >> 3);
+      const int q = 8 * (e & 7), i = tl.i0 + lane;
+      const double* xp = atom(x64, i < L ? i : 0, 3);
+      unsigned int mine = 0;
+      unsigned long long rows = 0;
+      if (tl.j0 + q < L)
+        mark8(sph[i < L ? i >> 3 : 0], i < L ? xp[0] : 1e300, xp[1], xp[2], i < L, tl.j0 + q, mine, rows);
+      const int k = 64 * (e >> 3) + lane;
+      reinterpret_cast<unsigned char*>(all_marks + k)[e & 7] = (unsigned char)mine;
+      if ((lane >> 3) == (e & 7)) columns[k] = rows;
+    }
+    __syncthreads();
+    // the steps of the tile sides that this wavefront will add; list positions, a tile a wavefront
+    unsigned long long mask[2] = {0, 0};
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int e = wave + h * W, k = 64 * (e >> 1) + lane;   // tile and side
+      if (e >= 2 * ntile) continue;
+      unsigned long long row, col;
+      by_step(tile_at(e >> 1), all_marks[k], columns[k], row, col);
+      mask[h] = e & 1 ? col : row;
+    }
+    unsigned long long row = 0;
+    int at = 0;
+    if (wave < ntile) {
+      unsigned long long col;
+      int count;
+      by_step(tile_at(wave), all_marks[64 * wave + lane], columns[64 * wave + lane], row, col);
+      place(row, at, count);
+      if (lane == 0) counts[wave] = count;
+    }
+    __syncthreads();
+    int total = 0;
+    for (int t = 0; t < ntile; ++t) {
+      if (t == wave) at += total;
+      total += counts[t];
+    }
+    done = total <= room;
+    if (done) {
+      if (wave < ntile) {
+        all_marks[64 * wave + lane] = row;
+        all_base[64 * wave + lane] = (unsigned short)at;
+        for (unsigned long long left = row; left != 0; left &= left - 1)
+          all_code[at++] = (unsigned short)(lane | (__builtin_ctzll(left) << 6));
+      }
+      __syncthreads();
+      // evaluations, 64 pairs of a tile an item
+      for (int t = 0, from = 0, k = wave; t < ntile; from += counts[t], ++t) {
+        const int n = counts[t];
+        for (; 64 * k < n; k += W) {
+          const Pair A = prep(tile_at(t), all_code + from, n, 64 * k + lane);
+          eval(A, all_qs + from, 64 * k + lane);
+        }
+        k -= (n + 63) >> 6;
+      }
+      if (!ordered && whole == whole) {   // (a NaN pair's coordinates make a sum NaN, too)
+        lds_add(vacc, (long long)whole);
+        lds_add(vacc + 2, (long long)part);
+      }
+      __syncthreads();
+      // sums, a side of a tile an item
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int e = wave + h * W, t64 = 64 * (e >> 1);
+        if (e >= 2 * ntile || __ballot(mask[h] != 0) == 0) continue;
+        const Tile tl = tile_at(e >> 1);
+        const int k = (e & 1 ? tl.j0 : tl.i0) + lane;
+        const double* xp = atom(x64, k < L ? k : 0, 3);
+        double fx = 0.0, fy = 0.0, fz = 0.0;
+        if (e & 1) add_col(tl, all_qs, all_marks + t64, all_base + t64, mask[h], xp[0], xp[1], xp[2], fx, fy, fz);
+        else add_row(tl, all_qs, mask[h], all_base[t64 + lane], xp[0], xp[1], xp[2], fx, fy, fz);
+        const bool fits = fabs(fx) < lim && fabs(fy) < lim && fabs(fz) < lim;
+        wide = wide || !fits;
+        if (fits && mask[h] != 0) add_force(k, fx, fy, fz);
+      }
+    }
+  }
+  while (!done) {
     int tile = 0;
     if (lane == 0)
       tile = (int)__hip_atomic_fetch_add((__attribute__((address_space(3))) int*)(vacc + 1), 1, __ATOMIC_RELAXED,
@@ -226,7 +455,8 @@ __device__ double value_grad(const double* __restrict__ s, int L, const float* _
     if (tile >= ntile) break;
     int off = 0, I = tile;   // J - I, I
     while (I >= nb64 - off) { I -= nb64 - off; ++off; }
-    const int i0 = 64 * I, j0 = 64 * (I + off), i = i0 + lane, j = j0 + lane;
+    const Tile tl{off, 64 * I, 64 * (I + off)};
+    const int i0 = tl.i0, j0 = tl.j0, i = i0 + lane, j = j0 + lane;
     const double* xp = atom(x64, i < L ? i : 0, 3);
     // (absent rows stand far off; absent columns and those up to the row drop out of the marks)
     const double ix = i < L ? xp[0] : 1e300, iy = xp[1], iz = xp[2];
@@ -263,7 +493,8 @@ __device__ double value_grad(const double* __restrict__ s, int L, const float* _
     const unsigned long long row = near >> lane | near << ((64 - lane) & 63), col = rev << by | rev >> ((64 - by) & 63);
     xp = atom(x64, j < L ? j : 0, 3);
     const double jx = xp[0], jy = xp[1], jz = xp[2];
-    double rx = 0.0, ry = 0.0, rz = 0.0, cx = 0.0, cy = 0.0, cz = 0.0, whole = 0.0, part = 0.0;
+    double rx = 0.0, ry = 0.0, rz = 0.0, cx = 0.0, cy = 0.0, cz = 0.0;
+    whole = part = 0.0;
     for (int u0 = 0, width = 64; u0 < 64; u0 += width, width = 64 - u0) {
       unsigned long long range, m;   // steps [u0, u0 + width), as many as the list holds
       int at, count;                 // the row's first pair in the list, all pairs
@@ -291,87 +522,19 @@ __device__ double value_grad(const double* __restrict__ s, int L, const float* _
           code[k++] = (unsigned short)(lane | (__builtin_ctzll(left) << 6));
       }
       wave_sync();
-      // 64 pairs: ends, distance, stencil base and taps, issued one step ahead of their
-      // evaluation (the flat read of a pair's code waits for the gather before it, which
-      // therefore overlaps that step's arithmetic only)
-      struct Pair {
-        double inv_d, t;
-        int b;
-        bool use;
-        float q0, q1, q2, q3, qn;
-      };
-      auto prep = [&](int k) {
-        Pair a;
-        a.use = k < count;
-        const int cd = a.use ? code[k] : 0;
-        const int pi = i0 + (cd & 63), pj = a.use ? j0 + (((cd & 63) + (cd >> 6)) & 63) : 0;
-        const double* xa = atom(x64, pi, 3);
-        const double* xb = atom(x64, pj, 3);
-        const double d2 = pair_dist2(xb[0] - xa[0], xb[1] - xa[1], xb[2] - xa[2]);
-        // distance through the hardware reciprocal square root and two Newton steps
-        a.inv_d = a.use && d2 > 0.0 ? rsqrt64(d2) : 0.0;
-        a.t = fma(d2, a.inv_d, -first) * inv_w;
-        a.b = stencil_base(a.t, nb);
-        const gfloat* r = gtable + (size_t)(a.use ? pair_row(pi, pj, L) : 0) * stride;
-        a.q0 = r[a.b]; a.q1 = r[a.b + 1]; a.q2 = r[a.b + 2]; a.q3 = r[a.b + 3];
-        a.qn = r[nb];
-        return a;
-      };
-      auto eval = [&](const Pair& a, int k) {
-        if (!a.use) return;
-        double E, dE;
-        spline64_ed((double)a.q0, (double)a.q1, (double)a.q2, (double)a.q3, a.t, a.b, nb, inv_w, E, dE);
-        // deviation e + low from the no-contact value, exactly (Knuth's two-sum), in multiples
-        // of 2^-26 and of 2^-70: every digit of a pair's energy down to these
-        double e = E, low = 0.0;
-        two_sum(e, low, -(double)a.qn);
-        const double n = rint(e * 0x1p26);   // (sums of integers below 2^53)
-        whole += n;
-        part += rint((fma(n, -0x1p-26, e) + low) * 0x1p70);
-        qs[k] = a.inv_d > 0.0 ? dE * a.inv_d : 0.0;
-      };
       // two records in turn, so that no gathered value is copied
-      Pair A = prep(lane);
+      Pair A = prep(tl, code, count, lane);
       for (int k = lane;; k += 128) {
-        const Pair B = prep(k + 64);
-        eval(A, k);
+        const Pair B = prep(tl, code, count, k + 64);
+        eval(A, qs, k);
         if (k - lane + 64 >= count) break;
-        A = prep(k + 128);
-        eval(B, k + 64);
+        A = prep(tl, code, count, k + 128);
+        eval(B, qs, k + 64);
         if (k - lane + 128 >= count) break;
       }
       wave_sync();
-      // dV/dx_j = +q (x_j - x_i), dV/dx_i = -q (x_j - x_i)
-      // (two a step, so that their reads overlap; an absent one adds zero)
-      {
-        int k = at;
-        for (unsigned long long left = m; left != 0;) {
-          const int ua = __builtin_ctzll(left);
-          left &= left - 1;
-          const bool two = left != 0;
-          const int ub = two ? __builtin_ctzll(left) : ua;
-          left &= left - 1;
-          const double* xa = atom(x64, j0 + ((lane + ua) & 63), 3);
-          const double* xb = atom(x64, j0 + ((lane + ub) & 63), 3);
-          const double qa = -qs[k], qb = two ? -qs[k + 1] : 0.0;
-          rx = fma(xa[0] - ix, qa, rx); ry = fma(xa[1] - iy, qa, ry); rz = fma(xa[2] - iz, qa, rz);
-          rx = fma(xb[0] - ix, qb, rx); ry = fma(xb[1] - iy, qb, ry); rz = fma(xb[2] - iz, qb, rz);
-          k += 2;
-        }
-      }
-      for (unsigned long long left = col & range; left != 0;) {
-        const int ua = __builtin_ctzll(left), ra = (lane - ua) & 63;
-        left &= left - 1;
-        const bool two = left != 0;
-        const int ub = two ? __builtin_ctzll(left) : ua, rb = (lane - ub) & 63;
-        left &= left - 1;
-        const double* xa = atom(x64, i0 + ra, 3);
-        const double* xb = atom(x64, i0 + rb, 3);
-        const double qa = qs[base[ra] + (int)__popcll(marks[ra] & ((1ull << ua) - 1))];
-        const double qv = qs[base[rb] + (int)__popcll(marks[rb] & ((1ull << ub) - 1))], qb = two ? qv : 0.0;
-        cx = fma(jx - xa[0], qa, cx); cy = fma(jy - xa[1], qa, cy); cz = fma(jz - xa[2], qa, cz);
-        cx = fma(jx - xb[0], qb, cx); cy = fma(jy - xb[1], qb, cy); cz = fma(jz - xb[2], qb, cz);
-      }
+      add_row(tl, qs, m, at, ix, iy, iz, rx, ry, rz);
+      add_col(tl, qs, marks, base, col & range, jx, jy, jz, cx, cy, cz);
       wave_sync();
     }
     const double lim = 0x1p13;   // |tile sum| < 2^13: a residue's total stays below 2^19
@@ -469,11 +632,12 @@ __device__ double value_grad(const double* __restrict__ s, int L, const float* _
 
 // value_grad for a kernel whose parameters are P; V by ordered_energy where the table asks for it
 // (called from here and not from value_grad, which a call would cost 2 % of a minimisation).
-template <class Params>
+template <bool FEW, class Params>
 __device__ __forceinline__ double evaluate(const Params& P, const double* s, double* x64, double* ft, float4* sph,
                                            unsigned char* pairs, double* red, double* g) {
-  double V = value_grad(s, P.L, P.table, P.stride, P.nb, P.d_min, P.bin_w, P.vfar, P.ordered, x64, ft, sph, pairs, P.cap,
-                        reinterpret_cast<long long*>(red), g);
+  long long* const vacc = reinterpret_cast<long long*>(red);
+  double V = value_grad<FEW>(s, P.L, P.table, P.stride, P.nb, P.d_min, P.bin_w, P.vfar, P.ordered, x64, ft, sph, pairs, P.cap,
+                             vacc, g);
   if (P.ordered && V == V) {
     if (threadIdx.x < 64) {
       const double dfar = P.d_min + P.bin_w * ((double)P.nb - 0.5);
@@ -493,6 +657,7 @@ __device__ __forceinline__ double evaluate(const Params& P, const double* s, dou
 // Left free, the compiler gives the NeRF scan 271 registers and every kernel one wavefront
 // per SIMD; under the cap it spills a little inside that scan, and two workgroups of four
 // wavefronts share each CU (the most their LDS allows at 400 residues).
+template <bool FEW>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) grad_kernel(GradParams P) {
   extern __shared__ __align__(16) unsigned char lds[];
   const int L = P.L;
@@ -502,7 +667,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) g
   unsigned char* pairs = reinterpret_cast<unsigned char*>(sph + ((L + 7) >> 3));
   double* red = reinterpret_cast<double*>(pairs + (blockDim.x >> 6) * grad_pair_bytes(P.cap));
   const int b = blockIdx.x;
-  const double V = evaluate(P, P.s + (size_t)b * 2 * L, x64, ft, sph, pairs, red, P.g ? P.g + (size_t)b * 2 * L : nullptr);
+  const double V = evaluate<FEW>(P, P.s + (size_t)b * 2 * L, x64, ft, sph, pairs, red, P.g ? P.g + (size_t)b * 2 * L : nullptr);
   if (threadIdx.x == 0) {
     if (!isfinite(V)) atomicOr(P.err, kErrGradEnergy);
     if (P.V) P.V[b] = V;
@@ -512,6 +677,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) g
 // ---------------------------------------------------------------------------
 // One chain's L-BFGS.  Workspace rows (n = 2L doubles each): x, g, d, xn, gn, then
 // the curvature pairs S[m], Y[m] kept as a ring (oldest at `head`).
+template <bool FEW>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) lbfgs_kernel(LbfgsParams P) {
   extern __shared__ __align__(16) unsigned char lds[];
   const int L = P.L, n = 2 * L, tid = threadIdx.x, T = blockDim.x;
@@ -542,7 +708,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) l
     if (xtr) xtr[e] = sb[e];
   }
   __syncthreads();
-  double f = evaluate(P, x, x64, ft, sph, pairs, red, g);
+  double f = evaluate<FEW>(P, x, x64, ft, sph, pairs, red, g);
   if (trace && tid == 0) trace[0] = f;
   if (tid == 0) fh[0] = f;
   int k = 0, head = 0, nf = 1, it = 0, status = 1;
@@ -603,7 +769,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) l
     for (int ls = 0; ls < P.max_ls; ++ls) {
       for (int e = tid; e < n; e += T) xn[e] = x[e] + alpha * d[e];
       __syncthreads();
-      fnew = evaluate(P, xn, x64, ft, sph, pairs, red, gn);
+      fnew = evaluate<FEW>(P, xn, x64, ft, sph, pairs, red, gn);
       if (fnew <= fref + P.c1 * alpha * gd) { ok = true; break; }
       alpha *= P.shrink;
     }
@@ -656,5 +822,10 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) l
     if (P.status) P.status[b] = status;
   }
 }
+
+template __global__ void grad_kernel<false>(GradParams);
+template __global__ void grad_kernel<true>(GradParams);
+template __global__ void lbfgs_kernel<false>(LbfgsParams);
+template __global__ void lbfgs_kernel<true>(LbfgsParams);
 
 }  // namespace amh
