@@ -252,7 +252,8 @@ int conf_threads(int64_t B, int L) {
 // threads with long lists against 512 with short ones: one of 830 residues 416 and 272).
 // `few`: the wavefronts share tiles, where there are three at most and as many wavefronts (64
 // residues: 512 conformations 34 us against 54 with a tile a wavefront, 1024 43 against 61), from
-// 9 residues on (2: 13.1 against 12.4, 8: 13.9 and 13.8, 12: 14.9 against 16.1).  With six tiles,
+// 9 residues on (2: 13.1 against 12.4, 8: 13.9 and 13.8, 12: 14.9 against 16.1), and where their
+// list holds any one tile (it does with the LDS of today's shapes).  With six tiles,
 // 130 to 192 residues, and 8 wavefronts it is slower (200 conformations of 180 77 against 69).
 // `least`: threads the kernel needs, `extra`: its LDS beyond the gradient's.
 struct GradShape { int threads, cap; size_t lds; bool few; };
@@ -272,7 +273,9 @@ GradShape grad_shape(int L, int64_t B, int least, size_t extra) {
   s.cap = 64;
   while (s.cap < 2048 && bytes(s.cap + 8) <= room) s.cap += 8;
   s.lds = bytes(s.cap) - 256;
-  s.few = L > 8 && L <= (s.threads >= 256 ? 128 : 64);
+  const int ntile = L <= 64 ? 1 : 3;
+  s.few = L > 8 && L <= (s.threads >= 256 ? 128 : 64) &&
+          amh::grad_shared_pairs(s.threads / 64, s.cap, ntile) >= (ntile == 1 ? 2016 : 4096);
   return s;
 }
 

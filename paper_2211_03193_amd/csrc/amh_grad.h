@@ -61,6 +61,11 @@ inline bool ordered_energies(float dev_max) { return !(1.3 * (double)dev_max < 6
 
 // A wavefront's list of cap pairs (a multiple of 8, 64 at least).
 __host__ __device__ inline size_t grad_pair_bytes(int cap) { return 10 * (size_t)cap + 640; }
+// Pairs of the one list that W wavefronts sharing ntile tiles make of theirs (beside 1152 bytes of
+// marks and positions a tile).
+__host__ __device__ inline int grad_shared_pairs(int W, int cap, int ntile) {
+  return ((int)grad_pair_bytes(cap) * W - 1152 * ntile) / 10;
+}
 inline size_t grad_lds_bytes(int L, int W, int cap) {
   return 8 * (12 * (size_t)L + 6 * ((size_t)L + 1) + 3 * (kReduceThreads / 64)) + 16 * (size_t)((L + 7) / 8) +
          W * grad_pair_bytes(cap);

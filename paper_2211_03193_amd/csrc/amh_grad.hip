@@ -194,7 +194,7 @@ __device__ __attribute__((noinline)) double ordered_energy(int L, const gfloat* 
 // others wait (70 of 88 thousand cycles at 64 residues).  So the wavefronts share every tile's
 // marks, evaluations and sums, with barriers between: conformations of 64 residues, with all pairs
 // evaluated / a tile a wavefront / tiles shared, 1 of them 38 / 39 / 24 us, 512 43 / 54 / 34; 200 of
-// 100 48 / 50 / 36, of 128 51 / 57 / 39.  Pairs beyond the common list are left to the other way.
+// 100 48 / 50 / 36, of 128 51 / 57 / 39.
 template <bool FEW>
 __device__ __attribute__((noinline)) double value_grad(const double* __restrict__ s, int L, const float* __restrict__ table,
                              int stride, int nb, double d_min, double w, double vfar, bool ordered, double* x64, double* ft,
@@ -303,7 +303,6 @@ __device__ __attribute__((noinline)) double value_grad(const double* __restrict_
       cx = fma(jx - xb[0], qb, cx); cy = fma(jy - xb[1], qb, cy); cz = fma(jz - xb[2], qb, cz);
     }
   };
-  bool done = false;
   if constexpr (FEW) {   // fewer tiles than wavefronts: they share each tile
     auto tile_at = [&](int t) {
       int off = 0, I = t;   // J - I, I
@@ -364,7 +363,7 @@ __device__ __attribute__((noinline)) double value_grad(const double* __restrict_
     unsigned long long* const columns = all_marks + 64 * ntile;
     unsigned short* const all_base = reinterpret_cast<unsigned short*>(columns + 64 * ntile);
     double* const all_qs = reinterpret_cast<double*>(all_base + 64 * ntile);
-    const int room = ((int)grad_pair_bytes(cap) * W - 1152 * ntile) / 10;   // pairs of the list
+    const int room = grad_shared_pairs(W, cap, ntile);
     unsigned short* const all_code = reinterpret_cast<unsigned short*>(all_qs + room);
     int* const counts = reinterpret_cast<int*>(vacc + 3);
     // marks, 8 columns an item
@@ -401,14 +400,15 @@ __device__ __attribute__((noinline)) double value_grad(const double* __restrict_
       if (lane == 0) counts[wave] = count;
     }
     __syncthreads();
-    int total = 0;
-    for (int t = 0; t < ntile; ++t) {
-      if (t == wave) at += total;
-      total += counts[t];
-    }
-    done = total <= room;
-    if (done) {
-      if (wave < ntile) {
+    // as many tiles at a time as the list holds (one at least; the rule of FEW sees to that)
+    for (int t0 = 0, t1; t0 < ntile; t0 = t1) {
+      int total = 0;
+      for (t1 = t0; t1 < ntile && (t1 == t0 || total + counts[t1] <= room); ++t1) {
+        if (t1 == wave) at += total;
+        total += counts[t1];
+      }
+      if (t0 > 0) __syncthreads();   // (the list has been read)
+      if (t0 <= wave && wave < t1) {
         all_marks[64 * wave + lane] = row;
         all_base[64 * wave + lane] = (unsigned short)at;
         for (unsigned long long left = row; left != 0; left &= left - 1)
@@ -416,7 +416,7 @@ __device__ __attribute__((noinline)) double value_grad(const double* __restrict_
       }
       __syncthreads();
       // evaluations, 64 pairs of a tile an item
-      for (int t = 0, from = 0, k = wave; t < ntile; from += counts[t], ++t) {
+      for (int t = t0, from = 0, k = wave; t < t1; from += counts[t], ++t) {
         const int n = counts[t];
         for (; 64 * k < n; k += W) {
           const Pair A = prep(tile_at(t), all_code + from, n, 64 * k + lane);
@@ -424,29 +424,29 @@ __device__ __attribute__((noinline)) double value_grad(const double* __restrict_
         }
         k -= (n + 63) >> 6;
       }
-      if (!ordered && whole == whole) {   // (a NaN pair's coordinates make a sum NaN, too)
-        lds_add(vacc, (long long)whole);
-        lds_add(vacc + 2, (long long)part);
-      }
       __syncthreads();
       // sums, a side of a tile an item
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const int e = wave + h * W, t64 = 64 * (e >> 1);
-        if (e >= 2 * ntile || __ballot(mask[h] != 0) == 0) continue;
-        const Tile tl = tile_at(e >> 1);
+        const int e = wave + h * W, t = e >> 1;
+        if (t < t0 || t >= t1 || __ballot(mask[h] != 0) == 0) continue;
+        const Tile tl = tile_at(t);
         const int k = (e & 1 ? tl.j0 : tl.i0) + lane;
         const double* xp = atom(x64, k < L ? k : 0, 3);
         double fx = 0.0, fy = 0.0, fz = 0.0;
-        if (e & 1) add_col(tl, all_qs, all_marks + t64, all_base + t64, mask[h], xp[0], xp[1], xp[2], fx, fy, fz);
-        else add_row(tl, all_qs, mask[h], all_base[t64 + lane], xp[0], xp[1], xp[2], fx, fy, fz);
+        if (e & 1) add_col(tl, all_qs, all_marks + 64 * t, all_base + 64 * t, mask[h], xp[0], xp[1], xp[2], fx, fy, fz);
+        else add_row(tl, all_qs, mask[h], all_base[64 * t + lane], xp[0], xp[1], xp[2], fx, fy, fz);
         const bool fits = fabs(fx) < lim && fabs(fy) < lim && fabs(fz) < lim;
         wide = wide || !fits;
         if (fits && mask[h] != 0) add_force(k, fx, fy, fz);
       }
     }
+    if (!ordered && whole == whole) {   // (a NaN pair's coordinates make a sum NaN, too)
+      lds_add(vacc, (long long)whole);
+      lds_add(vacc + 2, (long long)part);
+    }
   }
-  while (!done) {
+  while (!FEW) {
     int tile = 0;
     if (lane == 0)
       tile = (int)__hip_atomic_fetch_add((__attribute__((address_space(3))) int*)(vacc + 1), 1, __ATOMIC_RELAXED,

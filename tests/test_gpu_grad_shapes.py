@@ -38,8 +38,8 @@ def test_grad_of_long_chains_at_every_workgroup_size(L):
 @pytest.mark.parametrize("L", [8, 9, 64, 90, 128])
 def test_grad_of_coils(L):
     """Coils with every pair inside the last knot: a tile to a wavefront and tiles shared by 8, 4
-    and 2 wavefronts; 128 residues overflow the list that four wavefronts share.  The same bits at
-    every size, energies as the oracle's."""
+    and 2 wavefronts; with 128 residues and four wavefronts the list holds two of the three tiles at a
+    time.  The same bits at every size, energies as the oracle's."""
     gu.say("gradients of coils, L", L)
     w = sy.CFG1.replace(L=L, n_chains=1, protein_seed=L, noise_seed=L + 1)
     s_ref, y = gu.protein(w)
