@@ -29,14 +29,15 @@
 //     integer count of these, exactly and so in any order: the sums do not depend on the
 //     launch shape.
 // Measured against global sweeps that rotated all atoms in LDS (128 bytes a residue), took
-// one tile at a time and wrote the next rotation after the decision, with a third barrier:
-// 1024 chains of 300 residues (2 chains and 4 wavefronts a workgroup) 6.8 -> 4.3 ms a
-// sweep; 128 chains of 300 2.9 -> 1.7 ms; 64 of 800 27.7 -> 12.1 ms; one of 64 residues
-// 370 -> 250 us.  What bounds it is instructions: a wavefront alone issues one in 5 to 8
-// cycles (8 where it needs the one before), and with two a SIMD the vector units are busy
-// 52 % of the time at 1024 chains of 300 residues (1518 instructions a wavefront and
-// proposal).  Four wavefronts a SIMD fit (the helper's state is in LDS and the randoms are
-// drawn in a call, 128 registers instead of 226): 1500 chains of 250 residues 3.3 -> 2.3 ms.
+// one tile at a time and wrote the next rotation after the decision, with a third barrier
+// (one sweep of chains near a minimum, called from the host): 1024 chains of 300 residues
+// (2 chains and 4 wavefronts a workgroup) 9.1 -> 5.9 ms; 128 chains of 300 3.4 -> 1.8; 1500 of
+// 250 11.9 -> 4.8; 64 of 800 10.1 -> 5.4; one of 64 residues 0.43 -> 0.28.  What bounds it is
+// instructions: a wavefront alone issues one in 5 to 8 cycles (8 where it needs the one before),
+// and with two a SIMD the vector units are busy for about half of the time (1024 chains of 300
+// residues over a whole annealed run: 770 vector instructions a wavefront and proposal).  Four
+// wavefronts a SIMD fit (the helper's state is in LDS and the randoms are drawn in a call, 128
+// registers instead of 226): 1500 chains of 250 residues 3.3 -> 2.3 ms for the step that did it.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
